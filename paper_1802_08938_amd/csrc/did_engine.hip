@@ -275,7 +275,7 @@ int64_t engine_bytes(const Shape& s, int R, bool x_copied, int refresh) {
   if (s.thin) {
     t += b(didk::thin_blocks(s) * didk::thin_slots_for(s) * 8);
   } else {
-    t += b(didk::vgram_blocks(s) * NP * 8) + b(KP * N * 4) + b(didk::cq_bytes(s)) + b(didk::bsc_floats(s.KP) * 4) + b((int64_t)R * KP * s.Mpad * 4) +
+    t += b(didk::vgram_blocks(s) * NP * 8) + b(didk::h_elems(s) * 4) + b(didk::cq_bytes(s)) + b(didk::bsc_floats(s.KP) * 4) + b((int64_t)R * KP * s.Mpad * 4) +
          b((int64_t)(R + 1) * 8) + b(didk::colpass_blocks(s) * 8);
   }
   t += b(kHistCap * 8) + b(8) + b(8);  // fhist, fobj, tdev
@@ -444,7 +444,7 @@ int setup(did_ctx* h, const void* Xv, int64_t M, int64_t N, int32_t K, const did
     if ((rc = dalloc(h, &h->tpart, didk::thin_blocks(s) * didk::thin_slots_for(s)))) return rc;
   } else {
     if ((rc = dalloc(h, &h->Vpart, didk::vgram_blocks(s) * NP))) return rc;
-    if ((rc = dalloc(h, &h->H, (int64_t)s.KP * N))) return rc;
+    if ((rc = dalloc(h, &h->H, didk::h_elems(s)))) return rc;
     unsigned char* cq = nullptr;
     if ((rc = dalloc(h, &cq, didk::cq_bytes(s)))) return rc;
     h->Cq = cq;

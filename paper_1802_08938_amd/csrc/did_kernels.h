@@ -42,6 +42,9 @@ constexpr inline int cq_units(int KP) { return cq_units_e(KP) + cq_units_w(KP); 
 inline int64_t n_tiles32(const Shape& s) { return (s.N + 31) / 32; }
 // bytes of the packed C buffer
 inline int64_t cq_bytes(const Shape& s) { return n_tiles32(s) * cq_units(s.KP) * 16; }
+// floats of H = B^T E: per 32-column tile, K rounded up to a multiple of 4 rows of 32 floats;
+// the sweep reads K rounded up to a multiple of 16 rows, so 12 more follow the last tile
+inline int64_t h_elems(const Shape& s) { return n_tiles32(s) * 32 * ((s.K + 3) / 4 * 4) + 12 * 32; }
 // Column scales of B for the H-order operands (Bsc), and row scales of C for the W-order
 // operands (Csc): floats [0, KP) hold the maxima (gathered by the kernel that changes the
 // factor), [KP, 2 KP) the inverse scales.
@@ -111,7 +114,8 @@ hipError_t bupdate(const Shape& s, float* B, const double* W, const double* V, _
 int bupdate_blocks(const Shape& s);
 
 // Column pass: E = X - BC per 32-column tile, one partial of sum E^2 per block, and
-// (with_h = 1) H = B^T E written as KP x N floats, row kk contiguous (index kk * N + j).
+// (with_h = 1) H = B^T E (h_elems floats: row k of tile T at (T * K4 + k) * 32, K4 = K rounded
+// up to a multiple of 4).
 // C enters through its packed pieces Cq.
 hipError_t colpass(const Shape& s, const void* X, const void* Cq, const _Float16* Bq, const float* Bsc,
                    float* Hout, double* fpart, int with_h, hipStream_t st);

@@ -3,7 +3,7 @@
 // One DID iteration (Alg. 3 of Gao & Chu, AAAI-18) is carried out as
 //   colpass column pass over X: E = X - B C (MFMA), f partial = sum E^2 (float64),
 //           H = B^T E (MFMA),
-//   sweep   the coordinate sweep over the rows of C (float64, one thread per column),
+//   sweep   the coordinate sweep over the rows of C (float64),
 //   vgram   V = tril(C C^T) partials of the updated C (MFMA, float64 sums),
 //   rowpass row pass over X: E' = X - B C' (MFMA) and W = E' C'^T per column range (MFMA),
 //   reduce  fixed-order sums of the V, W and f partials (the paper's one Allreduce),
@@ -198,40 +198,35 @@ __device__ __forceinline__ void block_copy(float* dst, const float* src, int n) 
 // in LDS as Ct[j * K + kk] (j relative to j0); every thread builds whole 16-byte units, so
 // the global stores are coalesced.  All threads of the block call it, after Ct is
 // complete; it takes 256 ints of LDS scratch (cs) from the caller.
-// DELTA: the values are a signed change of C (the carried-residual form packs delta C into
-// its own buffer of E-order units only, tile stride CqL<KP>::E): the column scales come
-// from the largest magnitude and no row maxima are gathered.
-template <int KP, bool DELTA = false>
+template <int KP>
 __device__ __forceinline__ void pack_block(f32x4* __restrict__ Cq, float* __restrict__ cmax, int64_t j0, int nv,
                                            const float* Ct, int K, int64_t ntiles, int* cs) {
   constexpr int KS = KP / 16;
   constexpr int UE0 = CqL<KP>::E0;
-  constexpr int UT = DELTA ? CqL<KP>::E : CqL<KP>::T;  // units per tile of the target buffer
+  constexpr int UT = CqL<KP>::T;  // units per tile of the target buffer
   constexpr int GE = 8 * KS * 64;  // E groups per block: (tile, s, half, jj)
   const int tid = threadIdx.x;     // cs[j]: scale exponent of column j0 + j
   const int64_t T0 = j0 >> 5;
   {
     float mx = 0.0f;
     if (tid < nv)
-      for (int kk = 0; kk < K; ++kk) mx = fmaxf(mx, DELTA ? fabsf(Ct[tid * K + kk]) : Ct[tid * K + kk]);
+      for (int kk = 0; kk < K; ++kk) mx = fmaxf(mx, Ct[tid * K + kk]);
     int sc = scale_exp(mx);
-    if constexpr (!DELTA) {
-      // a tile's 32 columns are 32 consecutive lanes: when the scales of its nonzero columns
-      // lie within kUniformSpread of each other, every column takes the smallest, so that
-      // the passes scale the tile's products with one multiplier (the tile is then flagged
-      // by the sign of its first inverse scale, below)
-      const bool has = tid < nv && mx > 0.0f;
-      int smin = has ? sc : INT_MAX, smax = has ? sc : INT_MIN;
+    // a tile's 32 columns are 32 consecutive lanes: when the scales of its nonzero columns
+    // lie within kUniformSpread of each other, every column takes the smallest, so that
+    // the passes scale the tile's products with one multiplier (the tile is then flagged
+    // by the sign of its first inverse scale, below)
+    const bool has = tid < nv && mx > 0.0f;
+    int smin = has ? sc : INT_MAX, smax = has ? sc : INT_MIN;
 #pragma unroll
-      for (int off = 1; off < 32; off <<= 1) {
-        smin = min(smin, __shfl_xor(smin, off, 64));
-        smax = max(smax, __shfl_xor(smax, off, 64));
-      }
-      if (smin <= smax && smax - smin <= kUniformSpread) sc = smin;
+    for (int off = 1; off < 32; off <<= 1) {
+      smin = min(smin, __shfl_xor(smin, off, 64));
+      smax = max(smax, __shfl_xor(smax, off, 64));
     }
+    if (smin <= smax && smax - smin <= kUniformSpread) sc = smin;
     cs[tid] = sc;
   }
-  if (!DELTA && tid < K) {  // row maxima over the block's columns (C >= 0: integer order = float order)
+  if (tid < K) {  // row maxima over the block's columns (C >= 0: integer order = float order)
     float mx = 0.0f;
     for (int j = 0; j < nv; ++j) mx = fmaxf(mx, Ct[j * K + tid]);
     if (mx > 0.0f) atomicMax(reinterpret_cast<int*>(cmax) + tid, __float_as_int(mx));
@@ -260,7 +255,7 @@ __device__ __forceinline__ void pack_block(f32x4* __restrict__ Cq, float* __rest
       f32x4 w;
 #pragma unroll
       for (int e = 0; e < 4; ++e) w[e] = pow2f(-cs[32 * tb + 4 * u + e]);
-      if (!DELTA && u == 0) {  // all 32 columns on one scale: the sign of the first flags it
+      if (u == 0) {  // all 32 columns on one scale: the sign of the first flags it
         bool same = true;
         for (int j = 1; j < 32; ++j) same = same && cs[32 * tb + j] == cs[32 * tb];
         if (same) w[0] = -w[0];
@@ -787,8 +782,8 @@ hipError_t bupdate(const Shape& s, float* B, const double* W, const double* V, _
 // chunk is added.  Powers of two commute with rounding, so the scales change no result
 // beyond the splits themselves.  The packed B run of chunk c+1 is staged into LDS (double
 // buffer shared by the four waves) and the X tile of chunk c+1 is loaded into registers
-// while chunk c is computed.  H is written as KP x N with row kk contiguous over the
-// columns.
+// while chunk c is computed.  H is written per 32-column tile, K rounded up to a multiple
+// of 4 rows of 32 floats each (what a wave of the sweep reads is then contiguous).
 //
 // RW (the carried-residual form): the E-order operand and the row scales of each chunk
 // come from BqE (delta B in a carried iteration, B in a refresh iteration) while the
@@ -891,7 +886,7 @@ __device__ __forceinline__ void colpass_body(const XT* __restrict__ X, int64_t M
     f32x16 v;
     if constexpr (x_is_tiled<XT>::value) {  // tiled copy XC
       // A wave past the last tile reads tile 0, in bounds (no branch in the chunk loop);
-      // its f partial is dropped and its H stores are masked by col < N.
+      // its f partial is dropped and it stores no H.
       return ld_tile(X + ((tileok ? T : 0) * nchunks + c) * 1024, l);
     } else {  // column-major float32 X
       const int64_t m0 = c * 32;
@@ -1040,14 +1035,16 @@ __device__ __forceinline__ void colpass_body(const XT* __restrict__ X, int64_t M
     if (c + 1 < nchunks) step(c + 1, x1, x0);
   }
 
-  if (WITH_H && colok) {  // row kk of H contiguous over columns: coalesced stores
+  if (WITH_H && tileok) {  // the tile's rows of H, 32 columns each (zeros past K and N)
     const float* ku = Bsc + KP;  // 2^-u_kk
+    const int K4 = (K + 3) / 4 * 4;
+    float* ht = Hout + T * (K4 * 32) + lc;
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int kk = 32 * b + row32(i, half);
-        Hout[(int64_t)kk * N + col] = ldexpf(H[b][i], -vcur) * ku[kk];
+        if (kk < K4) ht[kk * 32] = ldexpf(H[b][i], -vcur) * ku[kk];
       }
   }
 
@@ -1158,118 +1155,379 @@ hipError_t colpass(const Shape& s, const void* X, const void* Cqv, const _Float1
 }
 
 // ------------------------------------------------------------------ coordinate sweep
-// One thread per column j.  With h = B^T e_j from the column pass and G = B^T B in LDS, the
-// coordinates are updated in ascending order in float64:
+// With h = B^T e_j from the column pass and G = B^T B, the coordinates of a column are
+// updated in ascending order in float64:
 //   c_kj := [c_kj + h_k / G_kk]_+,  then h_q -= G_qk (c_kj^new - c_kj^old) for q > k,
-// (a true division, so that cancellations the closed form makes exact stay exact),
 // which is eq. up:c with b_q^T e_j kept up to date through inner products; a coordinate
-// with G_kk = 0 (zero column of B) is skipped.  The block's 256 columns of C (contiguous
-// in memory) are staged through LDS so that global loads and stores are coalesced, and
-// each updated column is repacked into Cq for the row pass and the next column pass.
-// With CqD (the carried-residual form) the block also packs delta C = C' - C (float32
-// difference of the stored values) into CqD's E-order units, for the row pass's update of
-// the carried residual.
-template <int KP, bool G_IN_LDS>
-__device__ __forceinline__ void sweep_body(const float* __restrict__ Hin, float* __restrict__ C,
-                                           f32x4* __restrict__ Cq, float* __restrict__ Csc, int64_t N, int K,
-                                           const double* __restrict__ G, int64_t bid,
-                                           f32x4* __restrict__ CqD = nullptr) {
-  // G = B^T B (KP x KP, both halves stored) is the same for every lane.  The single-instance
-  // kernel reads it directly: uniform addresses into memory the kernel does not write, which
-  // the compiler serves with scalar loads, so the FMAs below take G from scalar registers.
-  // The grouped kernels (whose pointers come from the descriptor table, after earlier work
-  // items stored to memory) stage its strictly lower triangle in LDS instead and read the
-  // diagonal from memory: without the diagonal, two blocks of the K > 32 class fit per CU.
-  __shared__ double Gs[G_IN_LDS ? KP * (KP - 1) / 2 : 1];  // strictly lower triangle, rows r >= 1
-  __shared__ int cs_own[G_IN_LDS ? 1 : 256];                // packing scratch (else in Gs, see below)
-  extern __shared__ float Ct[];                             // the block's columns, stride K (256 * K floats)
-  const int tid = threadIdx.x;
-  if constexpr (G_IN_LDS) {
-    for (int q = tid; q < KP * (KP - 1) / 2; q += 256) {
-      int a, b;
-      pair_of(q, a, b);  // a >= b; entry (a + 1, b) of G
-      Gs[q] = G[(a + 1) * KP + b];
-    }
-  }
-  // G[r][c] for r > c
-  auto gl = [&](int r, int c) -> double {
-    if constexpr (G_IN_LDS)
-      return Gs[(r - 1) * r / 2 + c];
-    else
-      return G[c * KP + r];  // row c of the symmetric G: contiguous in r
-  };
+// with G_kk = 0 (zero column of B) is skipped.
+//
+// What bounds it: the chain of K coordinates (latency) while N is small; at large N the
+// float64 work (K^2 / 2 FMAs per column: matrix and vector float64 have the same rate here
+// and do not overlap) and the H, C and Cq traffic.  The running h of a wave's columns sit in
+// the accumulator layout of v_mfma_f64_16x16x4 (subtile u of 16 columns: lane 16 g + n holds
+// coordinates 4 r + g of column 16 u + n), so that four coordinates are updated at a time:
+// permlane swaps bring a column's four sums into one lane, which forms the four updates;
+// their changes, moved back, are the B operand of one float64 MFMA per subtile and 16 later
+// coordinates (A operand: G, in the lane order it has in memory).
+//
+// A wave takes U subtiles: U = 4 (a 4 x 4 transpose, one column per lane) does a step's
+// updates for 64 columns at once, the form for large N; U = 1 (every lane of a column forms
+// its four updates) has a quarter of the MFMAs per step and four times the waves, the form
+// while those still find idle SIMDs (sweep_u).  (One thread per column, with K running sums
+// and G read by scalar loads, waited on those loads at every coordinate and read and packed
+// its columns through serial LDS loops.)  us per launch
+// before and after: 500 x 2000, K = 10: 19.0, 4.8; 3809 x 2248, K = 49: 60.6, 11.6; 784 x
+// 70000, K = 16: 25.6, 10.7; 1868 x 40000, K = 60: 69.0, 24.8; N = 10^6, K = 50: 397, 277.
+//
+// Division: h / G_kk is formed from the correctly rounded reciprocal, one residual fma and
+// one correction (Markstein's method: the correctly rounded quotient, so that cancellations
+// the closed form makes exact stay exact), with v_div_fixup for the special operands.  A
+// skipped coordinate takes G_kk = inf: its quotient is 0.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-  const int64_t j0 = bid * 256;
-  const int nv = (int)((N - j0) < 256 ? (N - j0) : 256);
-  const int ne = nv * K;
-  const int64_t col = j0 + tid;
-  // the column's h, loaded while the block stages its columns of C
-  float hf[KP];
-  if (tid < nv) {
+// 4 x 4 transpose of x[0..3] across the wave's four rows of 16 lanes: x[i] of row g becomes
+// x[g] of row i.
+__device__ __forceinline__ void transpose4(double (&x)[4]) {
+  unsigned w[4][2];
 #pragma unroll
-    for (int k = 0; k < KP; ++k) hf[k] = Hin[(int64_t)k * N + col];
+  for (int i = 0; i < 4; ++i) {
+    const uint64_t v = __builtin_bit_cast(uint64_t, x[i]);
+    w[i][0] = (unsigned)v;
+    w[i][1] = (unsigned)(v >> 32);
   }
-  block_copy(Ct, C + j0 * K, ne);
-  __syncthreads();
-  if (tid < nv) {
-    double h[KP];
 #pragma unroll
-    for (int k = 0; k < KP; ++k) h[k] = (double)hf[k];
-    float* cl = Ct + tid * K;
+  for (int e = 0; e < 2; ++e) {
 #pragma unroll
-    for (int k = 0; k < KP; ++k) {
-      if (k < K) {
-        const double nk = G[k * KP + k];
-        if (nk > 0.0) {
-          const double cold = (double)cl[k];
-          double cn = cold + h[k] / nk;
-          cn = cn > 0.0 ? cn : 0.0;
-          const double d = cn - cold;
-          cl[k] = (float)cn;
+    for (int i = 0; i < 4; i += 2) {  // odd rows of w[i] against even rows of w[i + 1]
+      const auto t = __builtin_amdgcn_permlane16_swap(w[i][e], w[i + 1][e], false, false);
+      w[i][e] = t[0];
+      w[i + 1][e] = t[1];
+    }
 #pragma unroll
-          for (int q = k + 1; q < KP; ++q) h[q] -= gl(q, k) * d;
-        }
-      }
+    for (int i = 0; i < 2; ++i) {  // rows 2, 3 of w[i] against rows 0, 1 of w[i + 2]
+      const auto t = __builtin_amdgcn_permlane32_swap(w[i][e], w[i + 2][e], false, false);
+      w[i][e] = t[0];
+      w[i + 2][e] = t[1];
     }
   }
-  __syncthreads();
-  // the packing scratch reuses Gs once the sweep is done (the barrier above): with its own
-  // 1 kB the grouped K > 32 kernel would no longer fit two blocks per CU
-  int* cs = G_IN_LDS ? reinterpret_cast<int*>(Gs) : cs_own;
-  if (CqD) {  // carried-residual form: C' packed, then Ct := C' - C packed into CqD
-    pack_block<KP>(Cq, Csc, j0, nv, Ct, K, (N + 31) / 32, cs);
-    __syncthreads();
-    constexpr int G = 16;  // loads of the old values issued ahead, as in block_copy
-    int e = tid;
-    for (; e + (G - 1) * 256 < ne; e += G * 256) {
-      float co[G];
 #pragma unroll
-      for (int u = 0; u < G; ++u) co[u] = C[j0 * K + e + u * 256];
-#pragma unroll
-      for (int u = 0; u < G; ++u) {
-        const float cn = Ct[e + u * 256];
-        C[j0 * K + e + u * 256] = cn;
-        Ct[e + u * 256] = cn - co[u];
-      }
-    }
-    for (; e < ne; e += 256) {
-      const float cn = Ct[e], co = C[j0 * K + e];
-      C[j0 * K + e] = cn;
-      Ct[e] = cn - co;
-    }
-    __syncthreads();
-    pack_block<KP, true>(CqD, nullptr, j0, nv, Ct, K, (N + 31) / 32, cs);
-    return;
-  }
-  block_copy(C + j0 * K, Ct, ne);
-  pack_block<KP>(Cq, Csc, j0, nv, Ct, K, (N + 31) / 32, cs);
+  for (int i = 0; i < 4; ++i) x[i] = __builtin_bit_cast(double, ((uint64_t)w[i][1] << 32) | (uint64_t)w[i][0]);
 }
 
-template <int KP>
-__global__ __launch_bounds__(256) void k_sweep(const float* __restrict__ Hin, float* __restrict__ C,
+// x of the four lanes of a column (rows 0..3 of the wave), in each of them.
+__device__ __forceinline__ void gather4(double x, double (&o)[4]) {
+  o[0] = o[1] = o[2] = o[3] = x;
+  transpose4(o);
+}
+
+// Ordering of a wave's own LDS traffic between its lanes (no instruction).
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Operands of the four coordinates 4 s .. 4 s + 3 of each step of the coupled updates with
+// the symmetric matrix A (G for the columns of C), in LDS: gd[s][0..3] reciprocals and
+// [4..7] values of A's diagonal (0 and inf for a skipped coordinate), [8..13] A(1,0), A(2,0),
+// A(2,1), A(3,0), A(3,1), A(3,2).
+template <int NT>
+struct TriOps {
+  alignas(16) double gd[4 * NT][14];
+};
+
+template <int NT>
+__device__ __forceinline__ void tri_stage(TriOps<NT>& o, const double* __restrict__ A, int lda) {
+  const int tid = threadIdx.x;
+  if (tid < 64 * NT) {
+    const int s = tid >> 4, e = tid & 15;
+    if (e < 14) {
+      int a, b;
+      if (e < 8) {
+        a = b = e & 3;
+      } else {
+        const int q = e - 8;  // (1,0) (2,0) (2,1) (3,0) (3,1) (3,2)
+        a = q < 1 ? 1 : (q < 3 ? 2 : 3);
+        b = q - a * (a - 1) / 2;
+      }
+      double v = A[(4 * s + a) * lda + 4 * s + b];
+      if (e < 8) {
+        const bool on = v > 0.0;
+        v = e < 4 ? (on ? 1.0 / v : 0.0) : (on ? v : __builtin_inf());
+      }
+      o.gd[s][e] = v;
+    }
+  }
+}
+
+// The four coordinates of one step for one line: sums hv, old values co (float32); returns
+// the new float32 values in cn and minus the float64 changes in d.  The change is formed as
+// max(h / A_ii, -old) (what [old + h / A_ii]_+ - old is), which keeps the dependent chain at
+// six operations per coordinate.
+__device__ __forceinline__ void tri_step(const double (&gd)[14], double (&hv)[4], const f32x4& co, f32x4& cn,
+                                         double (&d)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const double old = (double)co[i];
+    double q = hv[i] * gd[i];
+    q = fma(fma(-q, gd[4 + i], hv[i]), gd[i], q);
+    q = __builtin_amdgcn_div_fixup(q, gd[4 + i], hv[i]);
+    const double c = q > -old ? q : -old;
+    cn[i] = (float)(old + c);
+    d[i] = -c;
+#pragma unroll
+    for (int j = i + 1; j < 4; ++j) hv[j] -= gd[8 + j * (j - 1) / 2 + i] * c;
+  }
+}
+
+// The chain of one wave's 16 U lines (columns of C, rows of B).  On entry h[u][b] holds the
+// sums of subtile u (16 lines) and coordinates 16 b .. 16 b + 15 in the MFMA accumulator
+// layout (values past K are not used), and ct points at the lane's line in LDS (lane l's own
+// line for U = 4, line l % 16 for U = 1), which is updated in place.  Returns the line's
+// largest new value; step(s, new, old) is called once per step of four coordinates.
+//
+// The loop over 16-coordinate blocks is rolled: the remaining blocks of h move down one
+// place per turn.
+template <int NT, int U, class Step>
+__device__ __forceinline__ float tri_chain(const TriOps<NT>& ops, f64x4 (&h)[U][NT], const double* __restrict__ A,
+                                           int lda, int K, float* ct, Step step) {
+  static_assert(U == 4 || U == 1, "");
+  const int l = threadIdx.x & 63, g = l >> 4;
+  const double* Al = A + g * lda + (l & 15);  // A[l / 16][l % 16]
+  float mx = 0.0f;
+#pragma clang loop unroll(disable)
+  for (int sb = 0; sb < NT; ++sb) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int s = 4 * sb + r;
+      if (4 * s < K) {
+        double ga[NT];  // A is symmetric: 16 consecutive lanes read 16 consecutive entries of a row
+#pragma unroll
+        for (int b = (r == 3 ? 1 : 0); b < NT; ++b) ga[b] = Al[4 * s * lda + 16 * min(sb + b, NT - 1)];
+        double gd[14], x[4], d[4];
+#pragma unroll
+        for (int e = 0; e < 14; ++e) gd[e] = ops.gd[s][e];
+        f32x4* const cp = reinterpret_cast<f32x4*>(ct + 4 * s);
+        const f32x4 co = *cp;
+        if constexpr (U == 4) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) x[u] = h[u][0][r];
+          transpose4(x);
+        } else {
+          gather4(h[0][0][r], x);
+        }
+        f32x4 cn;
+        tri_step(gd, x, co, cn, d);
+        if (U == 4 || g == 0) *cp = cn;
+        step(s, cn, co);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mx = fmaxf(mx, cn[i]);
+        if constexpr (U == 4)
+          transpose4(d);
+        else  // this lane's own coordinate 4 s + g
+          d[0] = g < 2 ? (g == 0 ? d[0] : d[1]) : (g == 2 ? d[2] : d[3]);
+#pragma unroll
+        for (int b = (r == 3 ? 1 : 0); b < NT; ++b)
+          if (sb + b < NT) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+              h[u][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[b], d[u], h[u][b], 0, 0, 0);
+          }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int b = 0; b + 1 < NT; ++b) h[u][b] = h[u][b + 1];
+  }
+  return mx;
+}
+
+// Scale of a column (lane) of a 32-column tile (half a wave) from the column's largest
+// magnitude mx: when the scales of the tile's nonzero columns lie within kUniformSpread of
+// each other, every column takes the smallest, so that the passes scale the tile's products
+// with one multiplier; one: whether all 32 columns share one scale.
+__device__ __forceinline__ int tile_scale(float mx, bool& one) {
+  int sc = scale_exp(mx);
+  int smin = mx > 0.0f ? sc : INT_MAX, smax = mx > 0.0f ? sc : INT_MIN;
+#pragma unroll
+  for (int off = 1; off < 32; off <<= 1) {
+    smin = min(smin, __shfl_xor(smin, off, 64));
+    smax = max(smax, __shfl_xor(smax, off, 64));
+  }
+  one = smin > smax;  // an all-zero tile: every scale is 0
+  if (smin <= smax && smax - smin <= kUniformSpread) {
+    sc = smin;
+    one = true;
+  }
+  return sc;
+}
+
+// Floats per line of the lines' values in LDS: K rounded up to a multiple of 4 whose
+// quarter is odd, so that 16-byte accesses of a wave's lanes to their lines are free of
+// bank conflicts.
+__host__ __device__ inline int line_ld(int K) {
+  const int q = (K + 3) / 4;
+  return 4 * (q | 1);
+}
+
+// E-order units p = p0, p0 + dp, ... of line jj of a 32-line tile, from the line in LDS
+// times m.  Units whose coordinates all lie past K stay zero.
+__device__ __forceinline__ void pack_e(f32x4* __restrict__ tile, const float* ct, int jj, float m, int K, int p0,
+                                       int dp) {
+#pragma clang loop unroll(disable)
+  for (int p = p0; 8 * p < K; p += dp) {
+    const f32x4 a = *reinterpret_cast<const f32x4*>(ct + 8 * p);
+    f32x4 b = f32x4{0, 0, 0, 0};
+    if (8 * p + 4 < K) b = *reinterpret_cast<const f32x4*>(ct + 8 * p + 4);
+    float v[8];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      v[t] = a[t] * m;
+      v[4 + t] = b[t] * m;
+    }
+    const Split2 sp = split2(v);
+    f32x4* dst = tile + (p >> 1) * 128 + jj + 32 * (p & 1);
+    dst[0] = f16_as_f32x4(sp.p[0]);
+    dst[64] = f16_as_f32x4(sp.p[1]);
+  }
+}
+
+// Subtiles per wave of an instance's sweep: one while a wave per 16 columns still finds
+// idle SIMDs.  us per launch at U = 1 and U = 4: 9.8 and 14.0 at N = 9000, K = 40; 29.9 and
+// 24.8 at N = 40000, K = 60; batches of mixed N, which fill the GPU together, prefer U = 4
+// from N = 8192 on (39.8 us per grouped launch at a line of 32768, 33.3 at 8192).
+__host__ __device__ inline int sweep_u(int64_t N) { return N <= 16384 ? 1 : 4; }
+inline int64_t sweep_blocks(int64_t N) { return (N + 64 * sweep_u(N) - 1) / (64 * sweep_u(N)); }
+
+// LDS of a sweep block beside its lines (64 U columns, and as many changes in the carried form)
+template <int NT>
+struct SweepLds {
+  TriOps<NT> ops;
+  float mx[4][64];    // largest C' per coordinate, per wave
+  float lmx[2][256];  // largest magnitude per line: C', and delta C in the carried form
+};
+inline size_t sweep_dyn_lds(int K, int u, bool rw) { return (size_t)64 * u * line_ld(K) * sizeof(float) * (rw ? 2 : 1); }
+
+// Sweep of the 64 U columns of block bid.  H is stored per 32-column tile (h_elems; row k of
+// a tile is 32 consecutive floats; columns past N hold zeros).  The updated columns go back
+// to C and, scaled and split, to the E-order units of Cq; the rows' maxima are added to
+// Csc[0, KP).  With RW (the carried-residual form) delta C = C' - C (float32 difference of the
+// stored values) is packed into CqD's E-order units too.
+template <int KP, int NT, int U, bool RW>
+__device__ __forceinline__ void sweep_body(SweepLds<NT>& S, float* lines, const float* __restrict__ Hin,
+                                           float* __restrict__ C, f32x4* __restrict__ Cq, float* __restrict__ Csc,
+                                           int64_t N, int K, const double* __restrict__ G, int64_t bid,
+                                           f32x4* __restrict__ CqD) {
+  constexpr int NL = 64 * U;             // lines per block
+  constexpr int CPI = NT <= 2 ? 2 : 1;   // lines per load of C (64 lanes over 64 / CPI coordinates)
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+  const int64_t nt = (N + 31) / 32, j0 = bid * NL, T0 = bid * (NL / 32);
+  const int nv = N - j0 < NL ? (int)(N - j0) : NL;  // the block's columns
+  const int K4 = (K + 3) / 4 * 4;
+  const int LD = line_ld(K);
+  float* const Cb = C + j0 * K;
+  f64x4 h[U][NT];
+  {  // lane 16 g + n: row 4 s + g, column n of the subtile (rows past K are read, not used; a
+     // subtile past the last tile reads that tile again)
+    float hn[U][4 * NT];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int sub = U == 4 ? 4 * wave + u : wave;
+      const int64_t T = T0 + (sub >> 1) < nt ? T0 + (sub >> 1) : nt - 1;
+      const float* const ht = Hin + T * (K4 * 32) + 16 * (sub & 1) + (l >> 4) * 32 + (l & 15);
+#pragma unroll
+      for (int s = 0; s < 4 * NT; ++s) hn[u][s] = ht[s * 128];
+    }
+    // the block's columns of C into LDS, coalesced and all in flight at once; zeros past N
+    constexpr int LPW = 16 * U / CPI;
+    const int kk = l & (64 / CPI - 1), c0 = wave * CPI + (CPI == 2 ? l >> 5 : 0);
+    float v[LPW];
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) v[i] = Cb[(uint32_t)(min(c0 + 4 * CPI * i, nv - 1) * K + min(kk, K - 1))];
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+      const int j = c0 + 4 * CPI * i;
+      if (kk < LD) lines[j * LD + kk] = (kk < K && j < nv) ? v[i] : 0.0f;
+    }
+    tri_stage<NT>(S.ops, G, KP);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int s = 0; s < 4 * NT; ++s) h[u][s >> 2][s & 3] = (double)hn[u][s];
+  }
+  __syncthreads();
+  {
+    const int line = U == 4 ? 64 * wave + l : 16 * wave + (l & 15);
+    float* const ct = lines + line * LD;
+    float md = 0.0f;
+    const float mx = tri_chain<NT, U>(S.ops, h, G, KP, K, ct, [&](int s, const f32x4& cn, const f32x4& co) {
+      if constexpr (RW) {
+        f32x4 dc;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          dc[i] = cn[i] - co[i];
+          md = fmaxf(md, fabsf(dc[i]));
+        }
+        if (U == 4 || l < 16) *reinterpret_cast<f32x4*>(ct + NL * LD + 4 * s) = dc;
+      }
+    });
+    if (U == 4 || l < 16) {
+      S.lmx[0][line] = mx;
+      if constexpr (RW) S.lmx[1][line] = md;
+    }
+  }
+  __syncthreads();
+  // scale and pack: line tid % NL, its units dealt over the threads that share it
+  {
+    const int j = tid % NL, jj = j & 31;
+    const int64_t T = T0 + (j >> 5);
+    const bool ok = j < nv;
+    bool one;
+    const int sc = tile_scale(ok ? S.lmx[0][j] : 0.0f, one);
+    if (T < nt) {
+      f32x4* const tile = Cq + T * CqL<KP>::T;
+      pack_e(tile, lines + j * LD, jj, pow2f(sc), K, tid / NL, 256 / NL);
+      if (tid < NL) {  // inverse scales; the sign of column 0's flags a shared scale
+        const float inv = pow2f(-sc);
+        reinterpret_cast<float*>(tile + CqL<KP>::E0)[jj] = (one && jj == 0) ? -inv : inv;
+      }
+      if constexpr (RW) {
+        f32x4* const td = CqD + T * CqL<KP>::E;
+        const int sd = scale_exp(ok ? S.lmx[1][j] : 0.0f);
+        pack_e(td, lines + (NL + j) * LD, jj, pow2f(sd), K, tid / NL, 256 / NL);
+        if (tid < NL) reinterpret_cast<float*>(td + CqL<KP>::E0)[jj] = pow2f(-sd);
+      }
+    }
+  }
+  // C' back, coalesced, and its rows' maxima (C >= 0: integer order = float order)
+  {
+    const int kk = l & (64 / CPI - 1), c0 = wave * CPI + (CPI == 2 ? l >> 5 : 0);
+    float cmax = 0.0f;
+    if (kk < K) {
+#pragma unroll 8
+      for (int c = c0; c < nv; c += 4 * CPI) {
+        const float v = lines[c * LD + kk];
+        cmax = fmaxf(cmax, v);
+        Cb[(uint32_t)(c * K + kk)] = v;
+      }
+    }
+    if constexpr (CPI == 2) cmax = fmaxf(cmax, __shfl_xor(cmax, 32, 64));
+    S.mx[wave][l] = cmax;
+    __syncthreads();
+    if (tid < K) {
+      const float m = fmaxf(fmaxf(S.mx[0][tid], S.mx[1][tid]), fmaxf(S.mx[2][tid], S.mx[3][tid]));
+      if (m > 0.0f) atomicMax(reinterpret_cast<int*>(Csc) + tid, __float_as_int(m));
+    }
+  }
+}
+
+template <int KP, int NT, int U, bool RW>
+__global__ __launch_bounds__(256, 2) void k_sweep(const float* __restrict__ Hin, float* __restrict__ C,
                                                f32x4* __restrict__ Cq, float* __restrict__ Csc, int64_t N, int K,
                                                const double* __restrict__ G, f32x4* __restrict__ CqD) {
-  sweep_body<KP, false>(Hin, C, Cq, Csc, N, K, G, blockIdx.x, CqD);
+  __shared__ SweepLds<NT> S;
+  extern __shared__ __align__(16) float lines[];
+  sweep_body<KP, NT, U, RW>(S, lines, Hin, C, Cq, Csc, N, K, G, blockIdx.x, CqD);
 }
 
 // E order of 256 columns of C (block bid), and their contribution to the row maxima.
@@ -1307,16 +1565,38 @@ static hipError_t packw(const Shape& s, const float* C, f32x4* Cq, float* Csc, h
   return hipGetLastError();
 }
 
+template <int KP, int NT, int U>
+static void sweep_launch_u(const Shape& s, const float* Hin, float* C, f32x4* q, float* Csc, const double* G,
+                           f32x4* qd, hipStream_t st) {
+  const unsigned g = (unsigned)sweep_blocks(s.N);
+  if (qd)
+    k_sweep<KP, NT, U, true><<<g, 256, sweep_dyn_lds(s.K, U, true), st>>>(Hin, C, q, Csc, s.N, s.K, G, qd);
+  else
+    k_sweep<KP, NT, U, false><<<g, 256, sweep_dyn_lds(s.K, U, false), st>>>(Hin, C, q, Csc, s.N, s.K, G, nullptr);
+}
+
+template <int KP, int NT>
+static void sweep_launch(const Shape& s, const float* Hin, float* C, f32x4* q, float* Csc, const double* G, f32x4* qd,
+                         hipStream_t st) {
+  if (sweep_u(s.N) == 1)
+    sweep_launch_u<KP, NT, 1>(s, Hin, C, q, Csc, G, qd, st);
+  else
+    sweep_launch_u<KP, NT, 4>(s, Hin, C, q, Csc, G, qd, st);
+}
+
 hipError_t sweep(const Shape& s, const float* Hin, float* C, void* Cq, float* Csc, const double* G,
                  hipStream_t st, void* CqD) {
-  const unsigned g = (unsigned)((s.N + 255) / 256);
   f32x4* q = static_cast<f32x4*>(Cq);
   f32x4* qd = static_cast<f32x4*>(CqD);
   k_zero_f32<<<1, 64, 0, st>>>(Csc, s.KP);
-  if (s.KP == 32)
-    k_sweep<32><<<g, 256, 256 * s.K * sizeof(float), st>>>(Hin, C, q, Csc, s.N, s.K, G, qd);
+  if (s.K <= 16)
+    sweep_launch<32, 1>(s, Hin, C, q, Csc, G, qd, st);
+  else if (s.K <= 32)
+    sweep_launch<32, 2>(s, Hin, C, q, Csc, G, qd, st);
+  else if (s.K <= 48)
+    sweep_launch<64, 3>(s, Hin, C, q, Csc, G, qd, st);
   else
-    k_sweep<64><<<g, 256, 256 * s.K * sizeof(float), st>>>(Hin, C, q, Csc, s.N, s.K, G, qd);
+    sweep_launch<64, 4>(s, Hin, C, q, Csc, G, qd, st);
   return packw(s, C, q, Csc, st);
 }
 
@@ -1910,6 +2190,11 @@ __device__ __forceinline__ int ginst_find(const GTable* __restrict__ g, int st, 
   return lo;
 }
 
+template <typename T>
+__device__ __forceinline__ T* as_global(T* p) {
+  return (T*)(__attribute__((address_space(1))) T*)p;
+}
+
 #define DID_GROUP_LOOP(ST)                                                     \
   const int64_t total_ = g->total[ST];                                        \
   for (int64_t w_ = blockIdx.x; w_ < total_; w_ += gridDim.x) {               \
@@ -1944,9 +2229,30 @@ __global__ __launch_bounds__(256) void kg_reduce_f(const GTable* __restrict__ g)
 }
 
 template <int KP>
-__global__ __launch_bounds__(256) void kg_sweep(const GTable* __restrict__ g) {
+__global__ __launch_bounds__(256, 2) void kg_sweep(const GTable* __restrict__ g) {
+  constexpr int NL = KP / 16 - 1;  // 16-coordinate blocks of the class's smaller half
+  __shared__ union {
+    SweepLds<NL> lo;
+    SweepLds<NL + 1> hi;
+  } S;
+  extern __shared__ __align__(16) float lines[];
   DID_GROUP_LOOP(GS_SWEEP)
-  sweep_body<KP, true>(d.H, d.C, static_cast<f32x4*>(d.Cq), d.Csc, d.N, d.K, d.G, bid);
+  // the table's pointers are generic: as global ones the many loads take scalar bases
+  const float* H = as_global(d.H);
+  float* C = as_global(d.C);
+  f32x4* Cq = as_global(static_cast<f32x4*>(d.Cq));
+  const double* G = as_global(d.G);
+  if (d.K <= 16 * NL) {
+    if (sweep_u(d.N) == 1)
+      sweep_body<KP, NL, 1, false>(S.lo, lines, H, C, Cq, d.Csc, d.N, d.K, G, bid, nullptr);
+    else
+      sweep_body<KP, NL, 4, false>(S.lo, lines, H, C, Cq, d.Csc, d.N, d.K, G, bid, nullptr);
+  } else {
+    if (sweep_u(d.N) == 1)
+      sweep_body<KP, NL + 1, 1, false>(S.hi, lines, H, C, Cq, d.Csc, d.N, d.K, G, bid, nullptr);
+    else
+      sweep_body<KP, NL + 1, 4, false>(S.hi, lines, H, C, Cq, d.Csc, d.N, d.K, G, bid, nullptr);
+  }
   DID_GROUP_END
 }
 
@@ -2024,7 +2330,7 @@ void ginst_items(const Shape& s, int R, int64_t items[GS_N]) {
   const int64_t R8 = ((int64_t)R + 7) / 8 * 8;
   items[GS_COL] = colpass_blocks(s);
   items[GS_REDF] = 1;
-  items[GS_SWEEP] = (s.N + 255) / 256;
+  items[GS_SWEEP] = sweep_blocks(s.N);
   items[GS_PACKW] = (s.N + 255) / 256;
   items[GS_VGRAM] = vgram_blocks(s);
   items[GS_REDV] = (np + kSymPairs - 1) / kSymPairs;
@@ -2050,7 +2356,7 @@ static hipError_t group_grids_t(int64_t grids[GS_N]) {
   };
   if ((e = occ((const void*)kg_colpass<KP, XT, WPB>, 64 * WPB, 0, &grids[GS_COL])) != hipSuccess) return e;
   if ((e = occ((const void*)kg_reduce_f, 256, 0, &grids[GS_REDF])) != hipSuccess) return e;
-  if ((e = occ((const void*)kg_sweep<KP>, 256, 256 * KP * sizeof(float), &grids[GS_SWEEP])) != hipSuccess) return e;
+  if ((e = occ((const void*)kg_sweep<KP>, 256, sweep_dyn_lds(KP, 4, false), &grids[GS_SWEEP])) != hipSuccess) return e;
   if ((e = occ((const void*)kg_packw<KP>, 256, 0, &grids[GS_PACKW])) != hipSuccess) return e;
   if ((e = occ((const void*)kg_vgram<KP>, 256, 0, &grids[GS_VGRAM])) != hipSuccess) return e;
   if ((e = occ((const void*)kg_reduce_v<KP>, 256, 0, &grids[GS_REDV])) != hipSuccess) return e;
@@ -2082,7 +2388,7 @@ template <int KP, typename XT, int WPB>
 static void group_iteration_t(const GTable* t, const int64_t* gr, hipStream_t st) {
   kg_colpass<KP, XT, WPB><<<(unsigned)gr[GS_COL], 64 * WPB, 0, st>>>(t);
   kg_reduce_f<<<(unsigned)gr[GS_REDF], 256, 0, st>>>(t);
-  kg_sweep<KP><<<(unsigned)gr[GS_SWEEP], 256, 256 * KP * sizeof(float), st>>>(t);
+  kg_sweep<KP><<<(unsigned)gr[GS_SWEEP], 256, sweep_dyn_lds(KP, 4, false), st>>>(t);
   kg_packw<KP><<<(unsigned)gr[GS_PACKW], 256, 0, st>>>(t);
   kg_vgram<KP><<<(unsigned)gr[GS_VGRAM], 256, 0, st>>>(t);
   kg_reduce_v<KP><<<(unsigned)gr[GS_REDV], 256, 0, st>>>(t);

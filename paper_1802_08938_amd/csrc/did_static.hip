@@ -72,7 +72,7 @@ int64_t carve_static(did_ctx& c, unsigned char* base, int64_t R) {
   c.V = w.take<double>((int64_t)s.KP * s.KP);
   c.W = w.take<double>((int64_t)s.KP * s.Mpad);
   c.Vpart = w.take<double>(didk::vgram_blocks(s) * NP);
-  c.H = w.take<float>((int64_t)s.KP * s.N);
+  c.H = w.take<float>(didk::h_elems(s));
   c.Cq = w.take<unsigned char>(didk::cq_bytes(s));
   c.Csc = w.take<float>(didk::bsc_floats(s.KP));
   c.Wpart = w.take<float>(R * s.KP * s.Mpad);

@@ -1,0 +1,42 @@
+"""The coordinate sweep and the B update at the edges of their blocks: both forms of the
+sweep (16 columns per wave up to N = 16384, 64 beyond), ragged last tiles and blocks, each
+count of 16-coordinate blocks, against the FP64 oracle after one iteration.
+
+The bars are check_factors' (1e-5 normwise, 1e-4 per line): the chains run in float64, so
+only the float32 products in H and W contribute, as on every other shape."""
+
+import numpy as np
+import pytest
+
+import oracle
+import paper_1802_08938_amd as did
+from tests._gpu import announce, check_factors, run_gpu, require_gpu
+from workloads import as_oracle_input, serving_x, to_f32_colmajor
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (40, 65, 4),        # one step of four coordinates, a second block of one column
+    (70, 257, 15),      # K just below one 16-block
+    (129, 127, 17),     # K just above one, M and N one off a block
+    (65, 16384, 5),     # the last N with 16 columns per wave
+    (64, 16385, 33),    # the first with 64, its last tile a single column
+    (66, 16433, 49),    # an odd number of tiles: a wave's second tile does not exist
+    (80, 16640, 64),    # whole blocks, largest K
+    (515, 90, 48),      # ragged blocks of rows of B, K at a whole number of 16-blocks
+])
+@pytest.mark.parametrize("refresh", [1, 2])
+def test_sweep_and_b_update_block_edges(M, N, K, refresh):
+    torch = require_gpu()
+    X32 = to_f32_colmajor(serving_x(M, N, K, seed=M + N + K))
+    o = did.did_default_opts()
+    o.refresh_every = refresh
+    announce(f"block edges M={M} N={N} K={K} refresh_every={refresh}")
+    out = run_gpu(torch, X32, K, iters=(1, 2), opts=o)
+    B0, C0 = out["init"]
+    X = as_oracle_input(X32)
+    for t in (1, 2):
+        Bo, Co, _ = oracle.did_run(X, B0, C0, t)
+        assert np.all(out[t][0] >= 0.0) and np.all(out[t][1] >= 0.0)
+        check_factors(out[t][0], Bo, out[t][1], Co, label=f"{M}x{N} K={K} refresh={refresh} t={t}")
