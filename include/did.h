@@ -388,7 +388,7 @@ int did_server_free(did_server s);
  * Every intermediate buffer lives in one static device array of DID_STATIC_SCRATCH_BYTES
  * (128 MiB; each device the library runs on holds it until the process ends): the call
  * makes no device allocation, no memset and no host round trip.  At K > 32 an instance
- * needs about 772 bytes per column of X, 1028 bytes per row, and 256 bytes per row for
+ * needs at most about 772 bytes per column of X, 1028 bytes per row, and 256 bytes per row for
  * each of the row pass's column ranges (half of each at K <= 32); one that does not fit
  * returns DID_EINVAL with the size it needs (fewer ranges, a smaller row_blocks, shrink it).
  * Shapes of the thin-matrix path (M <= 16, K <= 8, M <= 8 or K <= 4) return DID_EINVAL.

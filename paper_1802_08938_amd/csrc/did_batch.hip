@@ -160,6 +160,7 @@ void fill_inst(GInst& d, did_ctx* h, double* fcur) {
   d.vec4 = s.vec4;
   d.R = h->R;
   d.nsg = (int)((s.nchunks + 3) / 4);
+  d.csplit = s.csplit;
 }
 
 // Rewrite the group tables for the current members and, if the set of non-empty groups

@@ -126,7 +126,13 @@ int tuned_col_waves(int64_t M, int64_t N, int KP, int xkind);
 int check_shape(int64_t M, int64_t N, int32_t K);
 int make_shape(didk::Shape& s, int64_t M, int64_t N, int32_t K, const did_opts& o);
 int row_target(const didk::Shape& s, const did_opts& o);
-void range_params(int64_t N, int64_t nchunks, int n_blocks, int row_blocks, int64_t* T, int64_t* P, int64_t* S);
+// The work split of an MFMA-path instance and its scratch buffer, which holds the column
+// pass's partials of H at 0, and later the W partials at wofs and the V partials at vofs.
+struct WorkPlan {
+  int64_t T = 0, P = 1, S = 1, R = 1;  // range_bounds(T, P, S) gives R column ranges of the row pass
+  int64_t wofs = 0, vofs = 0, bytes = 0;
+};
+WorkPlan plan_work(didk::Shape& s, int n_blocks, int row_blocks);  // also sets s.csplit
 hipError_t refresh_b_derived(did_ctx* h);  // pack B and form G = B^T B
 hipError_t pack_c(did_ctx* h);             // pack C after it was set from outside the sweep
 int iterate_mfma(did_ctx* h, int32_t n);   // n iterations of the MFMA path on h's buffers

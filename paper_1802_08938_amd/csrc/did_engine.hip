@@ -175,32 +175,59 @@ void release(did_ctx* h) {
   delete h;
 }
 
-// Parameters of the row pass's column ranges (didk::range_bounds): T tiles, P blocks (the
-// paper's shards), at most S sub-ranges per block; W partials are summed in ascending
-// range order.
-void range_params(int64_t N, int64_t nchunks, int n_blocks, int row_blocks, int64_t* T, int64_t* P, int64_t* S) {
-  *T = (N + 31) / 32;
-  const int64_t slab_groups = (nchunks + 3) / 4;
+// The work split of an instance (see WorkPlan).  Parameters of the row pass's column ranges
+// (didk::range_bounds): T tiles, P blocks (the paper's shards), at most S sub-ranges per block;
+// W partials are summed in ascending range order.
+//
+// The partials of H (live from the column pass to the sweep) and of W and V (from there to
+// the B update) share one scratch buffer.  Its size is bounded by what the unsplit column pass and
+// ranges of at least 16 tiles take with separate buffers of KP rows, so that the finer splits
+// need no more device memory than those.
+WorkPlan plan_work(Shape& s, int n_blocks, int row_blocks) {
+  WorkPlan w;
+  const int64_t T = (s.N + 31) / 32, slab_groups = (s.nchunks + 3) / 4, NP = didk::n_pairs(s.KP);
+  w.T = T;
+  w.P = n_blocks > 0 ? std::min<int64_t>(n_blocks, T) : 1;
   // about row_blocks blocks of (range, slab group).  The default, N / 256 within
   // [512, 4096], follows measurements across shapes: wide X wants several rounds of
   // resident blocks (5000 x 10^6: 9.77 ms per iteration at 4096 against 10.98 at 512),
   // narrower X fewer, longer ranges, whose W partials cost less to write and sum
   // (500 x 150000: 0.258 ms at 512 against 0.303 at 4096).
-  const int64_t target = row_blocks > 0 ? row_blocks : std::min<int64_t>(4096, std::max<int64_t>(512, N / 256));
-  int64_t want = (target + slab_groups - 1) / slab_groups;
-  // at least 16 tiles (512 columns) per range: the W partials (R x KP x M floats) then
-  // stay below a sixteenth of X for K <= 64
-  want = std::max<int64_t>(1, std::min<int64_t>(want, std::max<int64_t>(1, *T / 16)));
-  *P = n_blocks > 0 ? std::min<int64_t>(n_blocks, *T) : 1;
-  *S = std::max<int64_t>(1, (want + *P - 1) / *P);
+  const int64_t target = row_blocks > 0 ? row_blocks : std::min<int64_t>(4096, std::max<int64_t>(512, s.N / 256));
+  const int64_t want = (target + slab_groups - 1) / slab_groups;
+  // Ranges of at least max(4, K / 6) tiles, where the W partials (written and read: 8 K M
+  // bytes a range) come to about 40 % of a range's X.  With 16 tiles a narrow X left the row
+  // pass a few dozen blocks; us per row pass at 16, 8 and 4 tiles: 500 x 2000, K = 10: 31.2,
+  // 16.2, 11.2; 600 x 9000, K = 40: 35.2, 22.0, 18.6; 3809 x 2248, K = 49: 36.4, 31.4, 31.2.
+  // 24 uneven jobs in one batch pay for their partials instead (row passes and W sums 886,
+  // 925, 927 us).
+  auto ranges = [&](int64_t least, int64_t* S) {
+    const int64_t n = std::max<int64_t>(1, std::min<int64_t>(want, std::max<int64_t>(1, T / least)));
+    *S = std::max<int64_t>(1, (n + w.P - 1) / w.P);
+    return didk::range_bounds(T, w.P, *S, nullptr);
+  };
+  const int64_t vbytes = didk::vgram_blocks(s) * NP * 8, nb = (s.N + 127) / 128;
+  int64_t S0;
+  const int64_t R0 = ranges(16, &S0);
+  const int64_t bound = s.KP * s.N * 4 + vbytes + R0 * s.KP * s.Mpad * 4 + R0 * 8;
+  auto rows = [&](int64_t R) { return (R * s.K * s.Mpad * 4 + 255) / 256 * 256; };
+  w.R = ranges(std::max<int64_t>(4, s.K / 6), &w.S);
+  while (w.S > S0 && rows(w.R) + vbytes + w.R * 8 + 16384 > bound)  // (16 kB: more f partials)
+    w.R = didk::range_bounds(T, w.P, --w.S, nullptr);
+  const int64_t hs = didk::h_stride(s.N, s.K) * 4 + nb * 8;  // a share's H and f partials
+  s.csplit = didk::column_split(s, (bound - w.R * 8 - 4096) / hs);
+  // unsplit, H keeps a place of its own where the bound allows it
+  const int64_t hbytes = (didk::h_elems(s) * 4 + 255) / 256 * 256;
+  if (s.csplit == 1 && hbytes + rows(w.R) + vbytes + w.R * 8 <= bound) w.wofs = hbytes;
+  w.vofs = w.wofs + rows(w.R);
+  w.bytes = std::max(hbytes, w.vofs + vbytes);
+  return w;
 }
 
 // The R + 1 tile bounds of the column ranges.
-std::vector<int64_t> make_ranges(int64_t N, int64_t nchunks, int n_blocks, int row_blocks) {
-  int64_t T, P, S;
-  range_params(N, nchunks, n_blocks, row_blocks, &T, &P, &S);
-  std::vector<int64_t> b((size_t)didk::range_bounds(T, P, S, nullptr) + 1);
-  didk::range_bounds(T, P, S, b.data());
+std::vector<int64_t> make_ranges(const WorkPlan& w) {
+  std::vector<int64_t> b((size_t)w.R + 1);
+  didk::range_bounds(w.T, w.P, w.S, b.data());
   return b;
 }
 
@@ -226,6 +253,7 @@ int make_shape(Shape& s, int64_t M, int64_t N, int32_t K, const did_opts& o) {
   s.KP = K <= 32 ? 32 : 64;
   s.nchunks = (M + 31) / 32;
   s.Mpad = s.nchunks * 32;
+  s.csplit = 1;  // until plan_work
   s.xbf16 = o.x_dtype == DID_BF16;
   s.xtiled = s.xbf16 || o.x_tiled;
   s.thin = (M <= 16 && K <= 8 && (M <= 8 || K <= 4)) ? 1 : 0;
@@ -262,7 +290,7 @@ int row_target(const Shape& s, const did_opts& o) {
 }
 
 // Device bytes the engine allocates for an instance (the plan setup follows).
-int64_t engine_bytes(const Shape& s, int R, bool x_copied, int refresh) {
+int64_t engine_bytes(const Shape& s, const WorkPlan& w, bool x_copied, int refresh) {
   const int64_t M = s.M, N = s.N, K = s.K, KP = s.KP, NP = didk::n_pairs(s.KP);
   auto b = [](int64_t n) { return n > 0 ? n : 1; };
   int64_t t = b(4);  // flag
@@ -275,8 +303,8 @@ int64_t engine_bytes(const Shape& s, int R, bool x_copied, int refresh) {
   if (s.thin) {
     t += b(didk::thin_blocks(s) * didk::thin_slots_for(s) * 8);
   } else {
-    t += b(didk::vgram_blocks(s) * NP * 8) + b(didk::h_elems(s) * 4) + b(didk::cq_bytes(s)) + b(didk::bsc_floats(s.KP) * 4) + b((int64_t)R * KP * s.Mpad * 4) +
-         b((int64_t)(R + 1) * 8) + b(didk::colpass_blocks(s) * 8);
+    t += b(w.bytes) + b(didk::cq_bytes(s)) + b(didk::bsc_floats(s.KP) * 4) + b((w.R + 1) * 8) +
+         b(didk::colpass_blocks(s) * 8);
   }
   t += b(kHistCap * 8) + b(8) + b(8);  // fhist, fobj, tdev
   if (refresh > 1) t += b(M * N * 4) + b(didk::packed_b_elems(s) * 2) + b(didk::cqd_bytes(s));  // R, BqD, CqD
@@ -290,13 +318,13 @@ int setup(did_ctx* h, const void* Xv, int64_t M, int64_t N, int32_t K, const did
   if ((rc = make_shape(s, M, N, K, o))) return rc;
   h->algorithm = o.algorithm;
   if (hipGetDevice(&h->dev) != hipSuccess) return fail(DID_EDEVICE, "no HIP device");
+  const WorkPlan w = plan_work(s, o.n_blocks, row_target(s, o));
   {  // the arena: the engine's bytes for this instance plus alignment slack per buffer
     const char* gz = getenv("DID_DEBUG_GUARD_ZONES");
     h->guards = gz && atoi(gz) != 0;
     const bool xdev0 = is_device_ptr(Xv);
     const bool x_copied = !s.xtiled && !(xdev0 && o.borrow_x);
-    const int R0 = s.thin ? 1 : (int)make_ranges(N, s.nchunks, o.n_blocks, row_target(s, o)).size() - 1;
-    const size_t cap = (size_t)engine_bytes(s, R0, x_copied, o.refresh_every) +
+    const size_t cap = (size_t)engine_bytes(s, w, x_copied, o.refresh_every) +
                        64 * (256 + (h->guards ? (size_t)DID_GUARD_ZONE_BYTES : 0));
     void* q = nullptr;
     size_t qcap = cap;
@@ -430,8 +458,8 @@ int setup(did_ctx* h, const void* Xv, int64_t M, int64_t N, int32_t K, const did
   }
 
   const int NP = didk::n_pairs(s.KP);
-  const std::vector<int64_t> rb = make_ranges(N, s.nchunks, o.n_blocks, row_target(s, o));
-  h->R = (int)rb.size() - 1;
+  const std::vector<int64_t> rb = make_ranges(w);
+  h->R = (int)w.R;
   if ((rc = dalloc(h, &h->B, M * K))) return rc;
   if ((rc = dalloc(h, &h->C, (int64_t)K * N))) return rc;
   if ((rc = dalloc(h, &h->Bq, didk::packed_b_elems(s)))) return rc;
@@ -443,13 +471,15 @@ int setup(did_ctx* h, const void* Xv, int64_t M, int64_t N, int32_t K, const did
   if (s.thin) {
     if ((rc = dalloc(h, &h->tpart, didk::thin_blocks(s) * didk::thin_slots_for(s)))) return rc;
   } else {
-    if ((rc = dalloc(h, &h->Vpart, didk::vgram_blocks(s) * NP))) return rc;
-    if ((rc = dalloc(h, &h->H, didk::h_elems(s)))) return rc;
+    unsigned char* work = nullptr;
+    if ((rc = dalloc(h, &work, w.bytes))) return rc;
+    h->H = reinterpret_cast<float*>(work);
+    h->Wpart = reinterpret_cast<float*>(work + w.wofs);
+    h->Vpart = reinterpret_cast<double*>(work + w.vofs);
     unsigned char* cq = nullptr;
     if ((rc = dalloc(h, &cq, didk::cq_bytes(s)))) return rc;
     h->Cq = cq;
     if ((rc = dalloc(h, &h->Csc, didk::bsc_floats(s.KP)))) return rc;
-    if ((rc = dalloc(h, &h->Wpart, (int64_t)h->R * s.KP * s.Mpad))) return rc;
     if ((rc = dalloc(h, &h->rbounds, (int64_t)rb.size()))) return rc;
     if ((rc = dalloc(h, &h->fpart, didk::colpass_blocks(s)))) return rc;
   }
@@ -1002,8 +1032,8 @@ int did_mem_estimate(int64_t M, int64_t N, int32_t K, const did_opts* opts, int3
   if (opts) o = *opts;
   Shape s{};
   if ((rc = make_shape(s, M, N, K, o))) return rc;
-  const int R = s.thin ? 1 : (int)make_ranges(N, s.nchunks, o.n_blocks, row_target(s, o)).size() - 1;
-  *bytes = engine_bytes(s, R, !(x_on_device && o.borrow_x), o.refresh_every);
+  const WorkPlan w = plan_work(s, o.n_blocks, row_target(s, o));
+  *bytes = engine_bytes(s, w, !(x_on_device && o.borrow_x), o.refresh_every);
   return DID_OK;
 }
 

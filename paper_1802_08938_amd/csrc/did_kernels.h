@@ -18,6 +18,7 @@ struct Shape {
   int xtiled;        // X is stored in tile order (always for bf16; float32 on request)
   int thin;          // thin-matrix path (M <= 16, K <= 8, M <= 8 or K <= 4): one fused pass per iteration
   int cwpb;          // waves per column-pass block (4 or 8): the block's 32 cwpb columns share one staged B
+  int csplit;        // column pass: the rows of X are split over this many blocks per column tile
   int64_t thin_grid; // thin path: blocks per launch (one wave of resident blocks)
 };
 
@@ -42,9 +43,11 @@ constexpr inline int cq_units(int KP) { return cq_units_e(KP) + cq_units_w(KP); 
 inline int64_t n_tiles32(const Shape& s) { return (s.N + 31) / 32; }
 // bytes of the packed C buffer
 inline int64_t cq_bytes(const Shape& s) { return n_tiles32(s) * cq_units(s.KP) * 16; }
-// floats of H = B^T E: per 32-column tile, K rounded up to a multiple of 4 rows of 32 floats;
-// the sweep reads K rounded up to a multiple of 16 rows, so 12 more follow the last tile
-inline int64_t h_elems(const Shape& s) { return n_tiles32(s) * 32 * ((s.K + 3) / 4 * 4) + 12 * 32; }
+// floats of one H = B^T E: per 32-column tile, K rounded up to a multiple of 4 rows of 32 floats
+__host__ __device__ inline int64_t h_stride(int64_t N, int K) { return (N + 31) / 32 * 32 * ((K + 3) / 4 * 4); }
+// floats of the column pass's csplit partials of H; the sweep reads K rounded up to a multiple
+// of 16 rows, so 12 more follow the last tile
+inline int64_t h_elems(const Shape& s) { return s.csplit * h_stride(s.N, s.K) + 12 * 32; }
 // Column scales of B for the H-order operands (Bsc), and row scales of C for the W-order
 // operands (Csc): floats [0, KP) hold the maxima (gathered by the kernel that changes the
 // factor), [KP, 2 KP) the inverse scales.
@@ -114,12 +117,16 @@ hipError_t bupdate(const Shape& s, float* B, const double* W, const double* V, _
 int bupdate_blocks(const Shape& s);
 
 // Column pass: E = X - BC per 32-column tile, one partial of sum E^2 per block, and
-// (with_h = 1) H = B^T E (h_elems floats: row k of tile T at (T * K4 + k) * 32, K4 = K rounded
-// up to a multiple of 4).
+// (with_h = 1) csplit partials of H = B^T E, each over a share of the rows (h_elems floats: row
+// k of tile T of partial p at p * h_stride + (T * K4 + k) * 32, K4 = K rounded up to a
+// multiple of 4).
 // C enters through its packed pieces Cq.
 hipError_t colpass(const Shape& s, const void* X, const void* Cq, const _Float16* Bq, const float* Bsc,
                    float* Hout, double* fpart, int with_h, hipStream_t st);
-int64_t colpass_blocks(const Shape& s);  // blocks of 32 cwpb columns
+int64_t colpass_blocks(const Shape& s);  // blocks of 32 cwpb columns and 1 / csplit of the rows
+
+// row shares of the column pass, at most max_split
+int column_split(const Shape& s, int64_t max_split);
 
 // Carried-residual form (refresh_every > 1) of the two passes; R is the column-major
 // float32 residual (M x N, ld M), carried across iterations.
@@ -149,7 +156,7 @@ hipError_t packc(const Shape& s, const float* C, void* Cq, float* Csc, hipStream
 hipError_t vgram(const Shape& s, const void* Cq, const float* Csc, double* Vpart, hipStream_t st);
 int64_t vgram_blocks(const Shape& s);
 
-// Row pass: W partial per column range r: Wpart[r] = (X - BC)[:, range] C[:, range]^T.
+// Row pass: W partial per column range r (K x Mpad floats): Wpart[r] = (X - BC)[:, range] C[:, range]^T.
 // Range r covers 32-column tiles [tb[r], tb[r+1]); C enters through Cq.
 hipError_t rowpass(const Shape& s, const void* X, const void* Cq, const float* Csc, const _Float16* Bq, float* Wpart,
                    const int64_t* tb, int R, hipStream_t st);
@@ -195,7 +202,7 @@ struct GInst {
   int64_t* tdev;  // iteration counter (index into fhist)
   double* fcur;   // latest objective, for the host
   int64_t M, N, nchunks, Mpad, hist_cap, vblocks, colblocks, bupblocks;
-  int K, vec4, R, nsg;
+  int K, vec4, R, nsg, csplit;
 };
 
 struct GTable {

@@ -794,9 +794,9 @@ template <int KP, bool WITH_H, typename XT, bool RW = false, int WPB = 4>
 __device__ __forceinline__ void colpass_body(const XT* __restrict__ X, int64_t M, int64_t N, int K,
                                              const f32x4* __restrict__ Cq, const _Float16* __restrict__ Bq,
                                              const float* __restrict__ Bsc, float* __restrict__ Hout,
-                                             double* __restrict__ fpart, int64_t nchunks, int vec4, int64_t bid,
-                                             const _Float16* __restrict__ BqE = nullptr, float* Rout = nullptr,
-                                             int rvec4 = 0) {
+                                             double* __restrict__ fpart, int64_t nchunks, int vec4, int csplit,
+                                             int64_t bid, const _Float16* __restrict__ BqE = nullptr,
+                                             float* Rout = nullptr, int rvec4 = 0) {
   constexpr int NB = KP / 32;
   constexpr int KS = KP / 16;
   constexpr int UE = BqL<KP>::E;      // 16-byte units of the E operand per chunk
@@ -810,7 +810,10 @@ __device__ __forceinline__ void colpass_body(const XT* __restrict__ X, int64_t M
   // the wave index is uniform: from a scalar register, so that wave-based addresses stay scalar
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, half = l >> 5,
             lc = l & 31;
-  const int64_t T = bid * WPB + wave;  // this wave's 32-column tile
+  // block bid: share bid / ncb of the rows (chunks c0 .. c1 - 1) of column block bid % ncb
+  const int64_t ncb = (N + 32 * WPB - 1) / (32 * WPB), share = bid / ncb;
+  const int64_t c0 = nchunks * share / csplit, c1 = nchunks * (share + 1) / csplit;
+  const int64_t T = (bid - share * ncb) * WPB + wave;  // this wave's 32-column tile
   const int64_t j0 = T * 32;
   const int64_t col = j0 + lc;
   const bool colok = col < N;
@@ -918,8 +921,8 @@ __device__ __forceinline__ void colpass_body(const XT* __restrict__ X, int64_t M
   // its X tile into xn (the two tiles alternate roles from one chunk to the next, so
   // nothing is copied).
   auto step = [&](int64_t c, const f32x16& xc, f32x16& xn) {
-    const int buf = (int)(c & 1);
-    const int64_t cn = c + 1 < nchunks ? c + 1 : c;
+    const int buf = (int)((c - c0) & 1);
+    const int64_t cn = c + 1 < c1 ? c + 1 : c;
     gload(cn);
     xn = xload(cn);
     // E of the chunk, a value of its own (not written over the X tile, which would make the
@@ -1025,20 +1028,20 @@ __device__ __forceinline__ void colpass_body(const XT* __restrict__ X, int64_t M
     __syncthreads();
   };
 
-  f32x16 x0 = xload(0);
-  gload(0);
+  f32x16 x0 = xload(c0);
+  gload(c0);
   sstore(0);
   __syncthreads();
   f32x16 x1;
-  for (int64_t c = 0; c < nchunks; c += 2) {
+  for (int64_t c = c0; c < c1; c += 2) {
     step(c, x0, x1);
-    if (c + 1 < nchunks) step(c + 1, x1, x0);
+    if (c + 1 < c1) step(c + 1, x1, x0);
   }
 
   if (WITH_H && tileok) {  // the tile's rows of H, 32 columns each (zeros past K and N)
     const float* ku = Bsc + KP;  // 2^-u_kk
     const int K4 = (K + 3) / 4 * 4;
-    float* ht = Hout + T * (K4 * 32) + lc;
+    float* ht = Hout + share * h_stride(N, K) + T * (K4 * 32) + lc;
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -1067,8 +1070,9 @@ __global__ __launch_bounds__(64 * WPB, 8 / WPB) void k_colpass(const XT* __restr
                                                                const f32x4* __restrict__ Cq,
                                                                const _Float16* __restrict__ Bq,
                                                                const float* __restrict__ Bsc, float* __restrict__ Hout,
-                                                               double* __restrict__ fpart, int64_t nchunks, int vec4) {
-  colpass_body<KP, WITH_H, XT, false, WPB>(X, M, N, K, Cq, Bq, Bsc, Hout, fpart, nchunks, vec4, blockIdx.x);
+                                                               double* __restrict__ fpart, int64_t nchunks, int vec4,
+                                                               int csplit) {
+  colpass_body<KP, WITH_H, XT, false, WPB>(X, M, N, K, Cq, Bq, Bsc, Hout, fpart, nchunks, vec4, csplit, blockIdx.x);
 }
 
 // The carried-residual form of the column pass (always forms H).
@@ -1078,13 +1082,40 @@ __global__ __launch_bounds__(256, 2) void k_colpass_rw(const XT* X, int64_t M, i
                                                        const _Float16* __restrict__ BqE,
                                                        const float* __restrict__ Bsc, float* __restrict__ Hout,
                                                        double* __restrict__ fpart, int64_t nchunks, int vec4,
-                                                       float* R, int rvec4) {
-  colpass_body<KP, true, XT, true>(X, M, N, K, Cq, Bq, Bsc, Hout, fpart, nchunks, vec4, blockIdx.x, BqE, R, rvec4);
+                                                       int csplit, float* R, int rvec4) {
+  colpass_body<KP, true, XT, true>(X, M, N, K, Cq, Bq, Bsc, Hout, fpart, nchunks, vec4, csplit, blockIdx.x, BqE, R,
+                                   rvec4);
 }
 
 int64_t colpass_blocks(const Shape& s) {
   const int64_t cols = 32 * (int64_t)(s.cwpb == 8 ? 8 : 4);
-  return (s.N + cols - 1) / cols;
+  return (s.N + cols - 1) / cols * s.csplit;
+}
+
+// Row shares of the column pass.  A block walks its rows chunk by chunk, so a narrow X leaves
+// most of the GPU idle (N = 575: 5 blocks), and one a little past a whole round of resident
+// blocks (2 per CU) pays for a second (N = 70000: 547 blocks).  Each share costs a prologue
+// and a partial of H (about 3 chunks' time) and its reading by the sweep; the smallest
+// estimate over shares of at least 4 chunks is taken, within max_split (the caller's scratch).
+// us per column pass at one share and as
+// chosen: 10304 x 575, K = 25: 502, 30.6; 3809 x 2248, K = 49: 307, 35.9; 500 x 2000, K = 10:
+// 25.6, 11.4; 600 x 9000, K = 40: 43.7, 21.6; 784 x 70000, K = 16: 79.2, 62.0; 1868 x 40000,
+// K = 60: 95.6, 91.
+int column_split(const Shape& s, int64_t max_split) {
+  const int64_t nb = (s.N + 127) / 128, resident = 512;
+  const int64_t most = std::min<int64_t>(std::min<int64_t>(max_split, s.nchunks / 4), 64);
+  int best = 1;
+  const double share = 0.5 + (double)s.N * s.K / 1.05e6;
+  double cost = 0.0;
+  for (int64_t p = 1; p <= std::max<int64_t>(most, 1); ++p) {
+    const double rounds = (double)((nb * p + resident - 1) / resident);
+    const double t = rounds * ((double)((s.nchunks + p - 1) / p) + 3.0) + share * (double)p;
+    if (p == 1 || t < cost) {
+      best = (int)p;
+      cost = t;
+    }
+  }
+  return best;
 }
 
 template <typename XT, int WPB>
@@ -1093,14 +1124,14 @@ static void colpass_launch_w(const Shape& s, const XT* X, const f32x4* C, const 
   const unsigned g = (unsigned)colpass_blocks(s);
   if (s.KP == 32) {
     if (with_h)
-      k_colpass<32, true, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Hout, fpart, s.nchunks, s.vec4);
+      k_colpass<32, true, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Hout, fpart, s.nchunks, s.vec4, s.csplit);
     else
-      k_colpass<32, false, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Hout, fpart, s.nchunks, s.vec4);
+      k_colpass<32, false, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Hout, fpart, s.nchunks, s.vec4, s.csplit);
   } else {
     if (with_h)
-      k_colpass<64, true, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Hout, fpart, s.nchunks, s.vec4);
+      k_colpass<64, true, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Hout, fpart, s.nchunks, s.vec4, s.csplit);
     else
-      k_colpass<64, false, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Hout, fpart, s.nchunks, s.vec4);
+      k_colpass<64, false, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Hout, fpart, s.nchunks, s.vec4, s.csplit);
   }
 }
 
@@ -1120,9 +1151,9 @@ static void colpass_rw_launch(const Shape& s, const XT* X, int vec4, const f32x4
   const unsigned g = (unsigned)colpass_blocks(s);
   const int rvec4 = (s.M % 4 == 0) && ((reinterpret_cast<uintptr_t>(R) & 15) == 0);
   if (s.KP == 32)
-    k_colpass_rw<32, XT><<<g, 256, 0, st>>>(X, s.M, s.N, s.K, C, Bq, BqE, Bsc, Hout, fpart, s.nchunks, vec4, R, rvec4);
+    k_colpass_rw<32, XT><<<g, 256, 0, st>>>(X, s.M, s.N, s.K, C, Bq, BqE, Bsc, Hout, fpart, s.nchunks, vec4, s.csplit, R, rvec4);
   else
-    k_colpass_rw<64, XT><<<g, 256, 0, st>>>(X, s.M, s.N, s.K, C, Bq, BqE, Bsc, Hout, fpart, s.nchunks, vec4, R, rvec4);
+    k_colpass_rw<64, XT><<<g, 256, 0, st>>>(X, s.M, s.N, s.K, C, Bq, BqE, Bsc, Hout, fpart, s.nchunks, vec4, s.csplit, R, rvec4);
 }
 
 hipError_t colpass_carry(const Shape& s, const void* X, int refresh, const void* Cqv, const _Float16* Bq,
@@ -1408,16 +1439,17 @@ struct SweepLds {
 };
 inline size_t sweep_dyn_lds(int K, int u, bool rw) { return (size_t)64 * u * line_ld(K) * sizeof(float) * (rw ? 2 : 1); }
 
-// Sweep of the 64 U columns of block bid.  H is stored per 32-column tile (h_elems; row k of
-// a tile is 32 consecutive floats; columns past N hold zeros).  The updated columns go back
+// Sweep of the 64 U columns of block bid.  H comes as csplit partials (added in float64 in
+// order), each stored per 32-column tile (h_stride floats; row k of a tile is 32 consecutive
+// floats; columns past N hold zeros).  The updated columns go back
 // to C and, scaled and split, to the E-order units of Cq; the rows' maxima are added to
 // Csc[0, KP).  With RW (the carried-residual form) delta C = C' - C (float32 difference of the
 // stored values) is packed into CqD's E-order units too.
 template <int KP, int NT, int U, bool RW>
 __device__ __forceinline__ void sweep_body(SweepLds<NT>& S, float* lines, const float* __restrict__ Hin,
-                                           float* __restrict__ C, f32x4* __restrict__ Cq, float* __restrict__ Csc,
-                                           int64_t N, int K, const double* __restrict__ G, int64_t bid,
-                                           f32x4* __restrict__ CqD) {
+                                           int csplit, float* __restrict__ C, f32x4* __restrict__ Cq,
+                                           float* __restrict__ Csc, int64_t N, int K, const double* __restrict__ G,
+                                           int64_t bid, f32x4* __restrict__ CqD) {
   constexpr int NL = 64 * U;             // lines per block
   constexpr int CPI = NT <= 2 ? 2 : 1;   // lines per load of C (64 lanes over 64 / CPI coordinates)
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
@@ -1430,14 +1462,17 @@ __device__ __forceinline__ void sweep_body(SweepLds<NT>& S, float* lines, const 
   {  // lane 16 g + n: row 4 s + g, column n of the subtile (rows past K are read, not used; a
      // subtile past the last tile reads that tile again)
     float hn[U][4 * NT];
+    auto hload = [&](int64_t p) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int sub = U == 4 ? 4 * wave + u : wave;
-      const int64_t T = T0 + (sub >> 1) < nt ? T0 + (sub >> 1) : nt - 1;
-      const float* const ht = Hin + T * (K4 * 32) + 16 * (sub & 1) + (l >> 4) * 32 + (l & 15);
+      for (int u = 0; u < U; ++u) {
+        const int sub = U == 4 ? 4 * wave + u : wave;
+        const int64_t T = T0 + (sub >> 1) < nt ? T0 + (sub >> 1) : nt - 1;
+        const float* const ht = Hin + p * h_stride(N, K) + T * (K4 * 32) + 16 * (sub & 1) + (l >> 4) * 32 + (l & 15);
 #pragma unroll
-      for (int s = 0; s < 4 * NT; ++s) hn[u][s] = ht[s * 128];
-    }
+        for (int s = 0; s < 4 * NT; ++s) hn[u][s] = ht[s * 128];
+      }
+    };
+    hload(0);
     // the block's columns of C into LDS, coalesced and all in flight at once; zeros past N
     constexpr int LPW = 16 * U / CPI;
     const int kk = l & (64 / CPI - 1), c0 = wave * CPI + (CPI == 2 ? l >> 5 : 0);
@@ -1454,6 +1489,14 @@ __device__ __forceinline__ void sweep_body(SweepLds<NT>& S, float* lines, const 
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int s = 0; s < 4 * NT; ++s) h[u][s >> 2][s & 3] = (double)hn[u][s];
+#pragma unroll U == 1 ? 4 : 1
+    for (int p = 1; p < csplit; ++p) {
+      hload(p);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int s = 0; s < 4 * NT; ++s) h[u][s >> 2][s & 3] += (double)hn[u][s];
+    }
   }
   __syncthreads();
   {
@@ -1522,12 +1565,13 @@ __device__ __forceinline__ void sweep_body(SweepLds<NT>& S, float* lines, const 
 }
 
 template <int KP, int NT, int U, bool RW>
-__global__ __launch_bounds__(256, 2) void k_sweep(const float* __restrict__ Hin, float* __restrict__ C,
-                                               f32x4* __restrict__ Cq, float* __restrict__ Csc, int64_t N, int K,
-                                               const double* __restrict__ G, f32x4* __restrict__ CqD) {
+__global__ __launch_bounds__(256, 2) void k_sweep(const float* __restrict__ Hin, int csplit,
+                                                  float* __restrict__ C, f32x4* __restrict__ Cq,
+                                                  float* __restrict__ Csc, int64_t N, int K,
+                                                  const double* __restrict__ G, f32x4* __restrict__ CqD) {
   __shared__ SweepLds<NT> S;
   extern __shared__ __align__(16) float lines[];
-  sweep_body<KP, NT, U, RW>(S, lines, Hin, C, Cq, Csc, N, K, G, blockIdx.x, CqD);
+  sweep_body<KP, NT, U, RW>(S, lines, Hin, csplit, C, Cq, Csc, N, K, G, blockIdx.x, CqD);
 }
 
 // E order of 256 columns of C (block bid), and their contribution to the row maxima.
@@ -1570,9 +1614,9 @@ static void sweep_launch_u(const Shape& s, const float* Hin, float* C, f32x4* q,
                            f32x4* qd, hipStream_t st) {
   const unsigned g = (unsigned)sweep_blocks(s.N);
   if (qd)
-    k_sweep<KP, NT, U, true><<<g, 256, sweep_dyn_lds(s.K, U, true), st>>>(Hin, C, q, Csc, s.N, s.K, G, qd);
+    k_sweep<KP, NT, U, true><<<g, 256, sweep_dyn_lds(s.K, U, true), st>>>(Hin, s.csplit, C, q, Csc, s.N, s.K, G, qd);
   else
-    k_sweep<KP, NT, U, false><<<g, 256, sweep_dyn_lds(s.K, U, false), st>>>(Hin, C, q, Csc, s.N, s.K, G, nullptr);
+    k_sweep<KP, NT, U, false><<<g, 256, sweep_dyn_lds(s.K, U, false), st>>>(Hin, s.csplit, C, q, Csc, s.N, s.K, G, nullptr);
 }
 
 template <int KP, int NT>
@@ -1720,9 +1764,10 @@ hipError_t vgram(const Shape& s, const void* Cq, const float* Csc, double* Vpart
 // (both operand orders, already split and scaled) is copied into LDS for the next tile
 // (double buffer shared by the four waves; straight from global memory into LDS, with no
 // staging registers) and X of the next tile is prefetched into registers.
-// Blocks map to (range, slab group) so that all slab groups of a range run on one XCD
-// (blocks are dealt to the eight XCDs round-robin): the range's C' tiles are then fetched
-// into a single L2.
+// Blocks are dealt to the eight XCDs round-robin; each XCD takes an equal run of the (range,
+// slab group) pairs, ranges first, so that the slab groups of a range share its C' tiles in
+// one L2 (whole ranges per XCD left XCDs idle at few ranges: 10304 x 575, K = 25, 4 ranges,
+// 34.6 us; 22.0 as runs).
 //
 // RW (the carried-residual form): X is the column-major float32 residual R = X - B C of
 // the column pass, the E-order operand of each tile comes from CqE (delta C, stride
@@ -1744,9 +1789,9 @@ __device__ __forceinline__ void rowpass_body(const XT* __restrict__ X, int64_t M
   constexpr int64_t UC = BqL<KP>::C;   // units per packed B chunk
   constexpr int UBS = BqL<KP>::S;      // the chunk's 32 row scales
   __shared__ f32x4 sc[2][UT];
-  const int id = (int)bid, xcd = id & 7, local = id >> 3;
-  const int r = xcd + 8 * (local / nsg), sg = local % nsg;
-  if (r >= R) return;  // whole block
+  const int64_t total = (int64_t)R * nsg, lin = (bid & 7) * ((total + 7) / 8) + (bid >> 3);
+  if (lin >= total) return;  // whole block
+  const int r = (int)(lin / nsg), sg = (int)(lin - (int64_t)r * nsg);
   // the wave index is uniform: from a scalar register, so that wave-based addresses stay scalar
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, half = l >> 5,
             lc = l & 31;
@@ -1932,14 +1977,14 @@ __device__ __forceinline__ void rowpass_body(const XT* __restrict__ X, int64_t M
     }
   }
   if (active) {
-    float* wp = Wpart + (int64_t)r * KP * Mpad;
+    float* wp = Wpart + (int64_t)r * K * Mpad;
     const float* inv = Csc + KP;  // 2^-w_kk
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int kk = 32 * b + row32(i, half);
-        wp[(int64_t)kk * Mpad + m0 + lc] = ldexpf(WT[b][i], -vcur) * inv[kk];
+        if (kk < K) wp[(int64_t)kk * Mpad + m0 + lc] = ldexpf(WT[b][i], -vcur) * inv[kk];
       }
   }
 }
@@ -1968,8 +2013,7 @@ hipError_t rowpass_carry(const Shape& s, float* Rr, const void* Cqv, const void*
   const f32x4* Cq = static_cast<const f32x4*>(Cqv);
   const f32x4* CqD = static_cast<const f32x4*>(CqDv);
   const int nsg = (int)((s.nchunks + 3) / 4);
-  const int R8 = (R + 7) / 8 * 8;
-  const unsigned g = (unsigned)((int64_t)nsg * R8);
+  const unsigned g = (unsigned)(((int64_t)nsg * R + 7) / 8 * 8);
   if (s.KP == 32)
     k_rowpass_rw<32><<<g, 256, 0, st>>>(Rr, s.M, s.N, s.K, Cq, CqD, Csc, Bq, Wpart, s.Mpad, s.nchunks, tb, R, nsg);
   else
@@ -1981,8 +2025,7 @@ template <typename XT>
 static void rowpass_launch(const Shape& s, const XT* X, const f32x4* Cq, const float* Csc, const _Float16* Bq,
                            float* Wpart, const int64_t* tb, int R, hipStream_t st) {
   const int nsg = (int)((s.nchunks + 3) / 4);
-  const int R8 = (R + 7) / 8 * 8;
-  const unsigned g = (unsigned)((int64_t)nsg * R8);
+  const unsigned g = (unsigned)(((int64_t)nsg * R + 7) / 8 * 8);
   if (s.KP == 32)
     k_rowpass<32, XT><<<g, 256, 0, st>>>(X, s.M, s.N, s.K, Cq, Csc, Bq, Wpart, s.Mpad, s.nchunks, tb, R, nsg);
   else
@@ -2033,7 +2076,7 @@ __global__ __launch_bounds__(256) void k_reduce_w(const float* __restrict__ Wpar
 }
 
 hipError_t reduce_w(const Shape& s, const float* Wpart, int R, double* W, hipStream_t st) {
-  const int64_t n = (int64_t)s.KP * s.Mpad;
+  const int64_t n = (int64_t)s.K * s.Mpad;
   k_reduce_w<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(Wpart, R, n, W);
   return hipGetLastError();
 }
@@ -2210,7 +2253,7 @@ template <int KP, typename XT, int WPB>
 __global__ __launch_bounds__(64 * WPB, 8 / WPB) void kg_colpass(const GTable* __restrict__ g) {
   DID_GROUP_LOOP(GS_COL)
   colpass_body<KP, true, XT, false, WPB>(static_cast<const XT*>(d.X), d.M, d.N, d.K, static_cast<const f32x4*>(d.Cq),
-                                         d.Bq, d.Bsc, d.H, d.fpart, d.nchunks, d.vec4, bid);
+                                         d.Bq, d.Bsc, d.H, d.fpart, d.nchunks, d.vec4, d.csplit, bid);
   DID_GROUP_END
 }
 
@@ -2244,14 +2287,14 @@ __global__ __launch_bounds__(256, 2) void kg_sweep(const GTable* __restrict__ g)
   const double* G = as_global(d.G);
   if (d.K <= 16 * NL) {
     if (sweep_u(d.N) == 1)
-      sweep_body<KP, NL, 1, false>(S.lo, lines, H, C, Cq, d.Csc, d.N, d.K, G, bid, nullptr);
+      sweep_body<KP, NL, 1, false>(S.lo, lines, H, d.csplit, C, Cq, d.Csc, d.N, d.K, G, bid, nullptr);
     else
-      sweep_body<KP, NL, 4, false>(S.lo, lines, H, C, Cq, d.Csc, d.N, d.K, G, bid, nullptr);
+      sweep_body<KP, NL, 4, false>(S.lo, lines, H, d.csplit, C, Cq, d.Csc, d.N, d.K, G, bid, nullptr);
   } else {
     if (sweep_u(d.N) == 1)
-      sweep_body<KP, NL + 1, 1, false>(S.hi, lines, H, C, Cq, d.Csc, d.N, d.K, G, bid, nullptr);
+      sweep_body<KP, NL + 1, 1, false>(S.hi, lines, H, d.csplit, C, Cq, d.Csc, d.N, d.K, G, bid, nullptr);
     else
-      sweep_body<KP, NL + 1, 4, false>(S.hi, lines, H, C, Cq, d.Csc, d.N, d.K, G, bid, nullptr);
+      sweep_body<KP, NL + 1, 4, false>(S.hi, lines, H, d.csplit, C, Cq, d.Csc, d.N, d.K, G, bid, nullptr);
   }
   DID_GROUP_END
 }
@@ -2291,7 +2334,7 @@ __global__ __launch_bounds__(256) void kg_reduce_w(const GTable* __restrict__ g)
   DID_GROUP_LOOP(GS_REDW)
   // the column maxima of B start from zero for the B update that follows
   if (bid == 0 && threadIdx.x < KP) d.Bsc[threadIdx.x] = 0.0f;
-  reduce_w_body(d.Wpart, d.R, (int64_t)KP * d.Mpad, d.W, bid);
+  reduce_w_body(d.Wpart, d.R, (int64_t)d.K * d.Mpad, d.W, bid);
   DID_GROUP_END
 }
 
@@ -2327,15 +2370,14 @@ __global__ __launch_bounds__(64) void kg_advance(const GTable* __restrict__ g) {
 void ginst_items(const Shape& s, int R, int64_t items[GS_N]) {
   const int64_t np = n_pairs(s.KP);
   const int64_t nsg = (s.nchunks + 3) / 4;
-  const int64_t R8 = ((int64_t)R + 7) / 8 * 8;
   items[GS_COL] = colpass_blocks(s);
   items[GS_REDF] = 1;
   items[GS_SWEEP] = sweep_blocks(s.N);
   items[GS_PACKW] = (s.N + 255) / 256;
   items[GS_VGRAM] = vgram_blocks(s);
   items[GS_REDV] = (np + kSymPairs - 1) / kSymPairs;
-  items[GS_ROW] = nsg * R8;
-  items[GS_REDW] = ((int64_t)s.KP * s.Mpad + 255) / 256;
+  items[GS_ROW] = (nsg * R + 7) / 8 * 8;
+  items[GS_REDW] = ((int64_t)s.K * s.Mpad + 255) / 256;
   items[GS_BUP] = bupdate_blocks(s);
   items[GS_REDG] = (np + kSymPairs - 1) / kSymPairs + bupdate_blocks(s);
   items[GS_ADV] = 1;

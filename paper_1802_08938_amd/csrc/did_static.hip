@@ -61,7 +61,7 @@ struct Carve {
 };
 
 // Lay the buffers of one MFMA-path instance out in the workspace; returns the bytes used.
-int64_t carve_static(did_ctx& c, unsigned char* base, int64_t R) {
+int64_t carve_static(did_ctx& c, unsigned char* base, const WorkPlan& p) {
   const Shape& s = c.s;
   Carve w{base};
   const int NP = didk::n_pairs(s.KP);
@@ -71,12 +71,13 @@ int64_t carve_static(did_ctx& c, unsigned char* base, int64_t R) {
   c.Gpart = w.take<double>((int64_t)didk::bupdate_blocks(s) * NP);
   c.V = w.take<double>((int64_t)s.KP * s.KP);
   c.W = w.take<double>((int64_t)s.KP * s.Mpad);
-  c.Vpart = w.take<double>(didk::vgram_blocks(s) * NP);
-  c.H = w.take<float>(didk::h_elems(s));
+  unsigned char* work = w.take<unsigned char>(p.bytes);
+  c.H = reinterpret_cast<float*>(work);
+  c.Wpart = base ? reinterpret_cast<float*>(work + p.wofs) : nullptr;
+  c.Vpart = base ? reinterpret_cast<double*>(work + p.vofs) : nullptr;
   c.Cq = w.take<unsigned char>(didk::cq_bytes(s));
   c.Csc = w.take<float>(didk::bsc_floats(s.KP));
-  c.Wpart = w.take<float>(R * s.KP * s.Mpad);
-  c.rbounds = w.take<int64_t>(R + 1);
+  c.rbounds = w.take<int64_t>(p.R + 1);
   c.fpart = w.take<double>(didk::colpass_blocks(s));
   c.fobj = w.take<double>(1);  // objective slot when the caller passes no f
   c.tdev = w.take<int64_t>(1);  // device iteration counter (index into the history)
@@ -102,10 +103,8 @@ int did_iterate_static(const float* X, int64_t M, int64_t N, int32_t K, float* B
   did_ctx c;
   if ((rc = make_shape(c.s, M, N, K, o))) return rc;
   if (c.s.thin) return fail(DID_EINVAL, "did_iterate_static runs the MFMA path only (not M <= 16, K <= 8 shapes)");
-  int64_t T, P, S;
-  range_params(N, c.s.nchunks, o.n_blocks, row_target(c.s, o), &T, &P, &S);
-  const int64_t R = didk::range_bounds(T, P, S, nullptr);
-  const int64_t need = carve_static(c, nullptr, R);
+  const WorkPlan p = plan_work(c.s, o.n_blocks, row_target(c.s, o));
+  const int64_t need = carve_static(c, nullptr, p);
   if (need > (int64_t)DID_STATIC_SCRATCH_BYTES)
     return fail(DID_EINVAL, "instance needs " + std::to_string(need) + " bytes of workspace, more than the static " +
                                 std::to_string((int64_t)DID_STATIC_SCRATCH_BYTES) +
@@ -113,7 +112,7 @@ int did_iterate_static(const float* X, int64_t M, int64_t N, int32_t K, float* B
   if (hipGetDevice(&c.dev) != hipSuccess) return fail(DID_EDEVICE, "no HIP device");
   unsigned char* base = nullptr;
   if ((rc = static_workspace(c.dev, &base))) return rc;
-  (void)carve_static(c, base, R);
+  (void)carve_static(c, base, p);
   c.st = static_cast<hipStream_t>(o.stream);
   c.own_stream = false;
   c.use_graph = false;  // a graph would allocate
@@ -123,7 +122,7 @@ int did_iterate_static(const float* X, int64_t M, int64_t N, int32_t K, float* B
   c.s.vec4 = (M % 4 == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0);
   c.B = B;
   c.C = C;
-  c.R = (int)R;
+  c.R = (int)p.R;
   c.fhist = f ? f : c.fobj;
   c.hist_cap = f ? std::max<int64_t>(n, 1) : 1;
   const Shape& s = c.s;
@@ -136,7 +135,7 @@ int did_iterate_static(const float* X, int64_t M, int64_t N, int32_t K, float* B
       (e = didk::zero16(c.Csc, (int64_t)didk::bsc_floats(s.KP) * 4, c.st)) != hipSuccess ||
       (e = didk::zero16(c.V, (int64_t)s.KP * s.KP * 8, c.st)) != hipSuccess ||
       (e = didk::zero16(c.W, (int64_t)s.KP * s.Mpad * 8, c.st)) != hipSuccess ||
-      (e = didk::ranges_on_device(c.rbounds, T, P, S, c.st)) != hipSuccess ||
+      (e = didk::ranges_on_device(c.rbounds, p.T, p.P, p.S, c.st)) != hipSuccess ||
       (e = didk::set_i64(c.tdev, 0, c.st)) != hipSuccess ||
       (e = refresh_b_derived(&c)) != hipSuccess || (e = pack_c(&c)) != hipSuccess)
     return dev_fail(nullptr, e, "did_iterate_static setup");

@@ -10,7 +10,7 @@ import pytest
 
 import oracle
 import paper_1802_08938_amd as did
-from tests._gpu import announce, check_factors, run_gpu, require_gpu
+from tests._gpu import announce, check_factors, check_trajectory, require_gpu, run_gpu
 from workloads import as_oracle_input, serving_x, to_f32_colmajor
 
 pytestmark = pytest.mark.gpu
@@ -40,3 +40,33 @@ def test_sweep_and_b_update_block_edges(M, N, K, refresh):
         Bo, Co, _ = oracle.did_run(X, B0, C0, t)
         assert np.all(out[t][0] >= 0.0) and np.all(out[t][1] >= 0.0)
         check_factors(out[t][0], Bo, out[t][1], Co, label=f"{M}x{N} K={K} refresh={refresh} t={t}")
+
+
+@pytest.mark.parametrize("M,N,K,cw", [
+    (515, 90, 20, 4),     # 17 chunks over 4 shares
+    (2049, 70, 64, 8),    # a last chunk of one row, 8 waves per block
+    (4103, 33, 7, 4),     # many shares of a single column block, two tiles
+    (1200, 1500, 33, 0),  # several column blocks and shares
+])
+def test_column_pass_row_shares(M, N, K, cw):
+    """The column pass split over the rows of X: factors, history and objective against the
+    oracle, and float32 X as given equal to the tiled form bit for bit (the same shares)."""
+    torch = require_gpu()
+    X32 = to_f32_colmajor(serving_x(M, N, K, seed=M + N + K))
+    X = as_oracle_input(X32)
+    announce(f"row shares M={M} N={N} K={K} col_waves={cw}")
+    outs = []
+    for tiled in (0, 1):
+        o = did.did_default_opts()
+        o.col_waves = cw
+        o.x_tiled = tiled
+        outs.append(run_gpu(torch, X32, K, iters=(1, 3), opts=o))
+    out = outs[0]
+    B0, C0 = out["init"]
+    Bo, Co, _ = oracle.did_run(X, B0, C0, 1)
+    check_factors(out[1][0], Bo, out[1][1], Co, label=f"{M}x{N} K={K}")
+    _, _, fo = oracle.did_run(X, B0, C0, 3)
+    check_trajectory(np.append(out["hist"], out["f"]), fo, label=f"{M}x{N} K={K}")
+    for t in (1, 3):
+        np.testing.assert_array_equal(outs[1][t][0], out[t][0])
+        np.testing.assert_array_equal(outs[1][t][1], out[t][1])
