@@ -518,7 +518,7 @@ int setup(did_ctx* h, const void* Xv, int64_t M, int64_t N, int32_t K, const did
 hipError_t refresh_b_derived(did_ctx* h) {
   hipError_t e = didk::bupdate(h->s, h->B, h->W, h->V, h->Bq, h->Bsc, h->Gpart, 0, h->st);
   if (e != hipSuccess) return e;
-  return didk::reduce_sym(h->Gpart, didk::bupdate_blocks(h->s), h->s.KP, h->G, h->st);
+  return didk::reduce_sym(h->Gpart, didk::bupdate_blocks(h->s), didk::g_pairs(h->s.K), h->s.KP, h->G, h->st);
 }
 
 int objective_pass(did_ctx* h) {
@@ -733,7 +733,7 @@ static int enqueue_iteration(did_ctx* h, hipEvent_t* ev, bool one_stream = false
     sv = st2;
   }
   if ((e = didk::vgram(s, h->Cq, h->Csc, h->Vpart, sv)) != hipSuccess) return dev_fail(h, e, "V partials");
-  if ((e = didk::reduce_sym(h->Vpart, didk::vgram_blocks(s), s.KP, h->V, sv)) != hipSuccess)
+  if ((e = didk::reduce_sym(h->Vpart, didk::vgram_blocks(s), didk::n_pairs(s.KP), s.KP, h->V, sv)) != hipSuccess)
     return dev_fail(h, e, "V reduce");
   if (st2 && (e = hipEventRecord(h->ev_v, st2)) != hipSuccess) return dev_fail(h, e, "stream order");
   DID_MARK(3);
@@ -751,7 +751,7 @@ static int enqueue_iteration(did_ctx* h, hipEvent_t* ev, bool one_stream = false
       hipSuccess)
     return dev_fail(h, e, "B update");
   DID_MARK(7);
-  if ((e = didk::reduce_sym(h->Gpart, didk::bupdate_blocks(s), s.KP, h->G, h->st)) != hipSuccess)
+  if ((e = didk::reduce_sym(h->Gpart, didk::bupdate_blocks(s), didk::g_pairs(s.K), s.KP, h->G, h->st)) != hipSuccess)
     return dev_fail(h, e, "G reduce");
   DID_MARK(8);
 #undef DID_MARK
@@ -897,7 +897,7 @@ static int iterate_thin(did_ctx* h, int32_t n) {
         return dev_fail(h, e, "pack B");
     }
     if ((e = mark(7)) != hipSuccess) return dev_fail(h, e, "profile record");
-    if ((e = didk::reduce_sym(h->Gpart, didk::bupdate_blocks(s), s.KP, h->G, h->st)) != hipSuccess)
+    if ((e = didk::reduce_sym(h->Gpart, didk::bupdate_blocks(s), didk::g_pairs(s.K), s.KP, h->G, h->st)) != hipSuccess)
       return dev_fail(h, e, "G reduce");
     if ((e = mark(8)) != hipSuccess) return dev_fail(h, e, "profile record");
     ++h->t;

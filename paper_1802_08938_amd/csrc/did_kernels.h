@@ -32,6 +32,8 @@ constexpr inline int bq_units_chunk(int KP) { return 2 * bq_units_e(KP) + 8; }
 // fp16 entries of the packed B buffer
 inline int64_t packed_b_elems(const Shape& s) { return s.nchunks * (int64_t)bq_units_chunk(s.KP) * 8; }
 inline int n_pairs(int KP) { return KP * (KP + 1) / 2; }
+// pairs (a >= b) of a partial of G: K rounded up to a multiple of 16
+__host__ __device__ constexpr inline int g_pairs(int K) { return (K + 15) / 16 * 16 * ((K + 15) / 16 * 16 + 1) / 2; }
 
 // Packed C: per 32-column tile, C in the two MFMA operand orders, as 16-byte units of eight
 // fp16 values: E order (KP/16 * 2 * 64 units: two pieces of C scaled per column, then 8
@@ -108,7 +110,7 @@ hipError_t scale(float* p, int64_t n, float a, hipStream_t st);
 
 // Pack B into MFMA operand order (Bq, layout above; Bsc: its column scales), optionally
 // applying the incremental B update from the reduced messages W (KP x Mpad, float64) and V
-// (KP x KP, float64) first; writes per-block partials of B^T B into Gpart (n_pairs(KP)
+// (KP x KP, float64) first; writes per-block partials of B^T B into Gpart (g_pairs(K)
 // doubles per block).  The thin path packs nothing (Bq and Bsc may be null there).
 // With BqD (carried-residual form) the change delta B of the update is also packed there
 // (E-order units and row scales, the layout of Bq).
@@ -163,8 +165,8 @@ hipError_t rowpass(const Shape& s, const void* X, const void* Cq, const float* C
 
 // Fixed-order reductions.
 hipError_t reduce_w(const Shape& s, const float* Wpart, int R, double* W, hipStream_t st);
-hipError_t reduce_sym(const double* part, int64_t P, int KP, double* full, hipStream_t st);
-hipError_t reduce_full(const double* part, int64_t P, int KP, double* full, hipStream_t st);
+// (NP pairs per partial)
+hipError_t reduce_sym(const double* part, int64_t P, int NP, int KP, double* full, hipStream_t st);
 hipError_t reduce_f(const double* part, int64_t P, double* out, double scale, hipStream_t st);
 // scale * sum of the partials into fhist[*tdev % cap], then *tdev += 1 (replayable)
 hipError_t reduce_f_hist(const double* part, int64_t P, double* fhist, int64_t cap, int64_t* tdev, double scale,

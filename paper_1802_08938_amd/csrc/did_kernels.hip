@@ -484,187 +484,7 @@ hipError_t validate(const float* p, int64_t n, int vec4, int* flag, hipStream_t 
 // needs the column maxima over all rows, which the B update gathers into Bsc[0, KP) with
 // atomic maxima (exact, so the result does not depend on the order), and is written by
 // k_packh afterwards, which also stores 2^-u_kk into Bsc[KP + kk].
-constexpr int kBupRows = 64;      // rows of B per block (one thread each for the update)
-constexpr int kBupThreads = 256;  // threads per block (all of them form the G partial)
-
-// RW (the carried-residual form): the change delta B = B^{t+1} - B^t of the stored float32
-// values is also packed, as E-order units of -delta B scaled per row with the row's inverse
-// scale, into BqD (the layout of Bq), for the next column pass's update of the residual.
-// HOIST: the row's values of B are all loaded before the first coordinate moves (the
-// single-instance kernel); the grouped kernel loads each as it goes, which keeps it at two
-// waves per SIMD (with the hoisted loads it needs 256 VGPRs).
-template <int KP, bool RW = false, bool HOIST = true>
-__device__ __forceinline__ void bupdate_body(float* __restrict__ B, int64_t M, int K, const double* __restrict__ W,
-                                             int64_t Mpad, const double* __restrict__ V, _Float16* __restrict__ Bq,
-                                             float* __restrict__ bmax, double* __restrict__ Gpart, int update,
-                                             int64_t bid, _Float16* __restrict__ BqD = nullptr) {
-  constexpr int64_t UC = BqL<KP>::C;
-  constexpr int US = BqL<KP>::S;
-  __shared__ float dfl[RW ? KP * kBupRows : 1];  // delta B of the stored values, [i][row]
-  // V is the same for every row.  The whole block stages it in LDS before the update (a
-  // few memory round trips in all), since the update's dependent chain would otherwise wait
-  // on a load of V at every coordinate: V was just written by another kernel, on whichever
-  // XCD, and a scalar load of it misses this XCD's caches.
-  __shared__ double Vs[KP * (KP + 1) / 2];  // lower triangle, row-major pairs
-  __shared__ float Bt[kBupRows * (KP + 1)];
-  const int tid = threadIdx.x;
-  if (update)
-    for (int q = tid; q < KP * (KP + 1) / 2; q += kBupThreads) {
-      int a, b;
-      pair_of(q, a, b);
-      Vs[q] = V[a * KP + b];
-    }
-  auto vv = [&](int a, int b) -> double { return Vs[a * (a + 1) / 2 + b]; };  // V[a][b] for a >= b
-  __syncthreads();
-  const int64_t m = bid * kBupRows + tid;
-  const bool ok = m < M;
-  if (tid < kBupRows) {  // the row update, one thread per row of B
-    float mx = 0.0f;
-    // sq[q] = w_q - sum_{k < i} v_qk delta b_k for the coordinates q not yet updated: once
-    // coordinate i has moved, every later sq[q] takes its term at once, so the terms still
-    // arrive in ascending k (the order of the sum in the update rule) while the dependent
-    // chain per coordinate is one division and one FMA.  A skipped coordinate (v_ii = 0: a
-    // zero row of C, whose row of V is zero too) moves by delta b_i = +0.
-    // The coordinates run to KQ, K rounded up to a multiple of 8 (a compile-time bound, so
-    // that sq stays in registers and no FMA is spent on the padding up to KP).
-    auto rows = [&](auto kq) {
-      constexpr int KQ = decltype(kq)::value;
-      double sq[KP];
-      float bo[KP];  // the row's current values (HOIST)
-      if constexpr (HOIST) {
-#pragma unroll
-        for (int q = 0; q < KQ; ++q) bo[q] = (q < K && ok) ? B[(int64_t)q * M + m] : 0.0f;
-      }
-      if (update) {
-#pragma unroll
-        for (int q = 0; q < KQ; ++q) sq[q] = (q < K && ok) ? W[(int64_t)q * Mpad + m] : 0.0;
-      }
-#pragma unroll
-      for (int i = 0; i < KP; ++i) {
-        float bnew = 0.0f;
-        if (i < KQ && i < K && ok) {
-          double bold;
-          if constexpr (HOIST)
-            bold = (double)bo[i];
-          else
-            bold = (double)B[(int64_t)i * M + m];
-          double bn = bold;
-          if (update) {
-            const double vii = vv(i, i);
-            if (vii > 0.0) {
-              bn = bold + sq[i] / vii;
-              bn = bn > 0.0 ? bn : 0.0;
-            }
-            const double d = bn - bold;
-#pragma unroll
-            for (int q = i + 1; q < KQ; ++q) sq[q] -= vv(q, i) * d;
-          }
-          bnew = (float)bn;
-          if (update) B[(int64_t)i * M + m] = bnew;
-          if constexpr (RW) dfl[i * kBupRows + tid] = (float)((double)bnew - bold);
-        } else if constexpr (RW) {
-          dfl[i * kBupRows + tid] = 0.0f;
-        }
-        Bt[tid * (KP + 1) + i] = bnew;
-        mx = fmaxf(mx, bnew);
-      }
-    };
-    // K <= 32 runs with KP = 32 and 32 < K <= 64 with KP = 64
-    switch ((K + 7) >> 3) {
-      case 1: case 5: rows(std::integral_constant<int, KP == 32 ? 8 : 40>{}); break;
-      case 2: case 6: rows(std::integral_constant<int, KP == 32 ? 16 : 48>{}); break;
-      case 3: case 7: rows(std::integral_constant<int, KP == 32 ? 24 : 56>{}); break;
-      default: rows(std::integral_constant<int, KP>{}); break;
-    }
-    // Scale of row m's E-order operand.  A chunk's 32 rows are 32 consecutive lanes of this
-    // wave; when the scales of its nonzero rows lie within kUniformSpread of each other,
-    // every row takes the smallest (the largest row's), so that the passes scale the
-    // chunk's products with one multiplier: a row then sits at most 2^kUniformSpread below
-    // the top of the fp16 range, and its values keep full accuracy down to
-    // 2^-(17 - kUniformSpread) of its maximum.  Row 0's stored inverse scale then carries
-    // the sign bit as the chunk's flag.
-    int sm = scale_exp(mx);
-    bool uniform = false;
-    {
-      const bool has = ok && mx > 0.0f;
-      int smin = has ? sm : INT_MAX, smax = has ? sm : INT_MIN;
-#pragma unroll
-      for (int off = 1; off < 32; off <<= 1) {  // within the lane's half of the wave
-        smin = min(smin, __shfl_xor(smin, off, 64));
-        smax = max(smax, __shfl_xor(smax, off, 64));
-      }
-      uniform = smin <= smax && smax - smin <= kUniformSpread;
-      if (uniform) sm = smin;
-    }
-    if constexpr (RW) {  // E-order units of -delta B for row m, scaled per row, and the inverse scale
-      if (ok) {
-        float dm = 0.0f;
-#pragma unroll
-        for (int i = 0; i < KP; ++i) dm = fmaxf(dm, fabsf(dfl[i * kBupRows + tid]));
-        const int sd = scale_exp(dm);
-        const float scd = pow2f(sd);
-        const int64_t c = m >> 5;
-        const int r = (int)(m & 31);
-#pragma unroll
-        for (int i = 0; i < KP; ++i) {
-          if (i < K) {
-            const float y = -dfl[i * kBupRows + tid] * scd;
-            const _Float16 hi = (_Float16)y;
-            const _Float16 lo = (_Float16)(y - (float)hi);
-            const int sq = i >> 4, h = (i >> 3) & 1, t = i & 7, l = r + 32 * h;
-            BqD[(c * UC + (sq * 2 + 0) * 64 + l) * 8 + t] = hi;
-            BqD[(c * UC + (sq * 2 + 1) * 64 + l) * 8 + t] = lo;
-          }
-        }
-        reinterpret_cast<float*>(BqD + (c * UC + US) * 8)[r] = pow2f(-sd);
-      }
-    }
-    if (Bq && ok) {  // E-order units of row m and its inverse scale
-      const float sc = pow2f(sm);
-      const int64_t c = m >> 5;
-      const int r = (int)(m & 31);
-#pragma unroll
-      for (int i = 0; i < KP; ++i) {
-        if (i < K) {
-          const float y = -Bt[tid * (KP + 1) + i] * sc;
-          const _Float16 hi = (_Float16)y;
-          const _Float16 lo = (_Float16)(y - (float)hi);
-          const int sq = i >> 4, h = (i >> 3) & 1, t = i & 7, l = r + 32 * h;
-          Bq[(c * UC + (sq * 2 + 0) * 64 + l) * 8 + t] = hi;
-          Bq[(c * UC + (sq * 2 + 1) * 64 + l) * 8 + t] = lo;
-        }
-      }
-      reinterpret_cast<float*>(Bq + (c * UC + US) * 8)[r] = (uniform && r == 0) ? -pow2f(-sm) : pow2f(-sm);
-    }
-  }
-  __syncthreads();
-  if (bmax && tid < K) {  // column maxima over this block's rows (B >= 0: integer order = float order)
-    float mx = 0.0f;
-    for (int r = 0; r < kBupRows; ++r) mx = fmaxf(mx, Bt[r * (KP + 1) + tid]);
-    if (mx > 0.0f) atomicMax(reinterpret_cast<int*>(bmax) + tid, __float_as_int(mx));
-  }
-  // Partial of G = B^T B over this block's rows, float64, pairs (a >= b).
-  constexpr int NP = KP * (KP + 1) / 2;
-  for (int q = tid; q < NP; q += kBupThreads) {
-    int a, b;
-    pair_of(q, a, b);
-    double s0 = 0.0, s1 = 0.0;
-    for (int r = 0; r < kBupRows; r += 2) {
-      s0 += (double)Bt[r * (KP + 1) + a] * (double)Bt[r * (KP + 1) + b];
-      s1 += (double)Bt[(r + 1) * (KP + 1) + a] * (double)Bt[(r + 1) * (KP + 1) + b];
-    }
-    Gpart[bid * NP + q] = s0 + s1;
-  }
-}
-
-template <int KP, bool RW>
-__global__ __launch_bounds__(kBupThreads) void k_bupdate(float* __restrict__ B, int64_t M, int K,
-                                                 const double* __restrict__ W, int64_t Mpad,
-                                                 const double* __restrict__ V, _Float16* __restrict__ Bq,
-                                                 float* __restrict__ bmax, double* __restrict__ Gpart,
-                                                 int update, _Float16* __restrict__ BqD) {
-  bupdate_body<KP, RW>(B, M, K, W, Mpad, V, Bq, bmax, Gpart, update, blockIdx.x, BqD);
-}
+constexpr int kBupRows = 64;  // rows of B per block of the update
 
 // H-order units of the two chunks 2*bid, 2*bid + 1 from B and the column maxima in
 // Bsc[0, KP); block 0 also stores 2^-u_kk into Bsc[KP + kk].  256 threads.
@@ -734,37 +554,6 @@ hipError_t ranges_on_device(int64_t* tb, int64_t T, int64_t P, int64_t S, hipStr
 
 __global__ void k_zero_f32(float* p, int n) {
   if ((int)threadIdx.x < n) p[threadIdx.x] = 0.0f;
-}
-
-int bupdate_blocks(const Shape& s) { return (int)((s.M + kBupRows - 1) / kBupRows); }
-
-hipError_t bupdate(const Shape& s, float* B, const double* W, const double* V, _Float16* Bq, float* Bsc,
-                   double* Gpart, int update, hipStream_t st, _Float16* BqD) {
-  const unsigned g = (unsigned)bupdate_blocks(s);
-  if (s.thin) {
-    Bq = nullptr;
-    Bsc = nullptr;
-    BqD = nullptr;
-  } else {
-    k_zero_f32<<<1, 64, 0, st>>>(Bsc, s.KP);
-  }
-  if (BqD) {
-    if (s.KP == 32)
-      k_bupdate<32, true><<<g, kBupThreads, 0, st>>>(B, s.M, s.K, W, s.Mpad, V, Bq, Bsc, Gpart, update, BqD);
-    else
-      k_bupdate<64, true><<<g, kBupThreads, 0, st>>>(B, s.M, s.K, W, s.Mpad, V, Bq, Bsc, Gpart, update, BqD);
-  } else if (s.KP == 32) {
-    k_bupdate<32, false><<<g, kBupThreads, 0, st>>>(B, s.M, s.K, W, s.Mpad, V, Bq, Bsc, Gpart, update, nullptr);
-  } else {
-    k_bupdate<64, false><<<g, kBupThreads, 0, st>>>(B, s.M, s.K, W, s.Mpad, V, Bq, Bsc, Gpart, update, nullptr);
-  }
-  if (!s.thin) {
-    if (s.KP == 32)
-      k_packh<32><<<g, 256, 0, st>>>(B, s.M, s.K, s.nchunks, Bq, Bsc);
-    else
-      k_packh<64><<<g, 256, 0, st>>>(B, s.M, s.K, s.nchunks, Bq, Bsc);
-  }
-  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ column pass
@@ -1574,6 +1363,200 @@ __global__ __launch_bounds__(256, 2) void k_sweep(const float* __restrict__ Hin,
   sweep_body<KP, NT, U, RW>(S, lines, Hin, csplit, C, Cq, Csc, N, K, G, blockIdx.x, CqD);
 }
 
+// ------------------------------------------------------------------ B update
+// b_mi := [b_mi + (w_mi - sum_{k < i} v_ik delta b_mk) / v_ii]_+ for i ascending, row by row (V
+// only couples the columns of one row): the sweep's chain with W for H and V for G, in the
+// form of 16 rows per wave.  A block takes 64 rows: it updates them in LDS, writes them back
+// and packs them (E order, scaled per row; with RW, the carried-residual form, also the change
+// -delta B = B^t - B^{t+1} of the stored float32 values, into BqD), adds the columns' maxima
+// to bmax and forms its partial of G = B^T B (float64 MFMA, products exact in float64) over
+// 16-coordinate blocks.  update = 0 packs and forms G from B as it is.  Bq may be null (thin path).
+//
+// Bound by the chain's latency.  (One thread per row, a quarter of the block's waves, with V in
+// LDS took 11.4 us at M = 500, K = 10, 47 us at M = 3809, K = 49 and 70 us at M = 5000, K = 50;
+// now 7.9, 19.3 and 28.3 us.)
+template <int NT>
+struct BupLds {
+  TriOps<NT> ops;
+  float mx[4][64];           // largest value per column of B, per wave
+  float lmx[2][kBupRows];    // largest magnitude per row: B, and delta B in the carried form
+};
+inline size_t bup_dyn_lds(int K, bool rw) { return (size_t)kBupRows * line_ld(K) * sizeof(float) * (rw ? 2 : 1); }
+
+template <int KP, int NT, bool RW>
+__device__ __forceinline__ void bupdate_body(BupLds<NT>& S, float* lines, float* __restrict__ B, int64_t M, int K,
+                                             const double* __restrict__ W, int64_t Mpad, const double* __restrict__ V,
+                                             _Float16* __restrict__ Bq, float* __restrict__ bmax,
+                                             double* __restrict__ Gpart, int update, int64_t bid,
+                                             _Float16* __restrict__ BqD) {
+  constexpr int64_t UC = BqL<KP>::C;
+  constexpr int US = BqL<KP>::S;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, g = l >> 4;
+  const int64_t m0 = bid * kBupRows;
+  const int nv = M - m0 < kBupRows ? (int)(M - m0) : kBupRows;  // the block's rows
+  const int LD = line_ld(K);
+  f64x4 h[1][NT];
+  if (update) {  // lane 16 g + n: coordinate 4 s + g of row 16 wave + n
+    const double* const wr = W + (m0 + min(16 * wave + (l & 15), nv - 1));
+#pragma unroll
+    for (int s = 0; s < 4 * NT; ++s) h[0][s >> 2][s & 3] = wr[(int64_t)min(4 * s + g, K - 1) * Mpad];
+    if (16 * wave + (l & 15) >= nv) {  // a row past M: stays zero
+#pragma unroll
+      for (int b = 0; b < NT; ++b) h[0][b] = f64x4{0, 0, 0, 0};
+    }
+  }
+  // the block's rows of B into LDS (lane = row), zeros past M and K
+  for (int k0 = 4 * wave; k0 < LD; k0 += 16) {
+    float v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = B[(int64_t)min(k0 + i, K - 1) * M + m0 + min(l, nv - 1)];
+    f32x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = (l < nv && k0 + i < K) ? v[i] : 0.0f;
+    *reinterpret_cast<f32x4*>(lines + l * LD + k0) = o;
+  }
+  if (update) tri_stage<NT>(S.ops, V, KP);
+  __syncthreads();
+  {
+    const int line = 16 * wave + (l & 15);
+    float* const ct = lines + line * LD;
+    float mx = 0.0f, md = 0.0f;
+    if (update) {
+      mx = tri_chain<NT, 1>(S.ops, h, V, KP, K, ct, [&](int s, const f32x4& cn, const f32x4& co) {
+        if constexpr (RW) {
+          f32x4 dc;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            dc[i] = cn[i] - co[i];
+            md = fmaxf(md, fabsf(dc[i]));
+          }
+          if (l < 16) *reinterpret_cast<f32x4*>(ct + kBupRows * LD + 4 * s) = dc;
+        }
+      });
+    } else {
+      for (int k = 0; k < K; ++k) mx = fmaxf(mx, ct[k]);
+      if constexpr (RW)
+        for (int k = g; k < LD; k += 4) ct[kBupRows * LD + k] = 0.0f;
+    }
+    if (l < 16) {
+      S.lmx[0][line] = mx;
+      if constexpr (RW) S.lmx[1][line] = md;
+    }
+  }
+  __syncthreads();
+  if (update) {  // back to B (lane = row)
+    for (int k = wave; k < K; k += 4) {
+      const float v = lines[l * LD + k];
+      if (l < nv) B[(int64_t)k * M + m0 + l] = v;
+    }
+  }
+  if (Bq) {  // row l: its E-order units are dealt over the four waves
+    const int64_t c = (m0 >> 5) + (l >> 5);
+    const int r = l & 31;
+    bool one;
+    const int sc = tile_scale(l < nv ? S.lmx[0][l] : 0.0f, one);
+    if (l < nv) {
+      f32x4* const u = reinterpret_cast<f32x4*>(Bq) + c * UC;
+      pack_e(u, lines + l * LD, r, -pow2f(sc), K, wave, 4);
+      if (wave == 0) {  // inverse scales; the sign of row 0's flags a scale shared by the chunk
+        const float inv = pow2f(-sc);
+        reinterpret_cast<float*>(u + US)[r] = (one && r == 0) ? -inv : inv;
+      }
+      if constexpr (RW) {
+        f32x4* const ud = reinterpret_cast<f32x4*>(BqD) + c * UC;
+        const int sd = scale_exp(S.lmx[1][l]);
+        pack_e(ud, lines + (kBupRows + l) * LD, r, -pow2f(sd), K, wave, 4);
+        if (wave == 0) reinterpret_cast<float*>(ud + US)[r] = pow2f(-sd);
+      }
+    }
+    // column maxima (B >= 0: integer order = float order)
+    float cm = 0.0f;
+    if (l < K) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) cm = fmaxf(cm, lines[(16 * wave + i) * LD + l]);
+    }
+    S.mx[wave][l] = cm;
+    __syncthreads();
+    if (tid < K) {
+      const float m = fmaxf(fmaxf(S.mx[0][tid], S.mx[1][tid]), fmaxf(S.mx[2][tid], S.mx[3][tid]));
+      if (m > 0.0f) atomicMax(reinterpret_cast<int*>(bmax) + tid, __float_as_int(m));
+    }
+  }
+  // partial of G over the block's rows, blocks (ta >= tb) of 16 x 16 coordinates dealt over the
+  // waves: lane 16 g + n supplies B[4 t + g][16 ta + n] and B[4 t + g][16 tb + n], four rows a step
+  constexpr int NBLK = NT * (NT + 1) / 2, NP = 16 * NT * (16 * NT + 1) / 2;
+#pragma clang loop unroll(disable)
+  for (int q = wave; q < NBLK; q += 4) {
+    const int ta = q < 1 ? 0 : (q < 3 ? 1 : (q < 6 ? 2 : 3)), tb = q - ta * (ta + 1) / 2;
+    const int ka = 16 * ta + (l & 15), kb = 16 * tb + (l & 15);
+    const float* const la = lines + g * LD + min(ka, K - 1);
+    const float* const lb = lines + g * LD + min(kb, K - 1);
+    f64x4 acc = f64x4{0, 0, 0, 0};
+#pragma unroll 4
+    for (int t = 0; t < kBupRows / 4; ++t) {
+      const double x = ka < K ? (double)la[4 * t * LD] : 0.0, y = kb < K ? (double)lb[4 * t * LD] : 0.0;
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int a = 16 * ta + 4 * r + g;
+      if (a >= kb) Gpart[bid * NP + a * (a + 1) / 2 + kb] = acc[r];
+    }
+  }
+}
+
+template <int KP, int NT, bool RW>
+__global__ __launch_bounds__(256, 2) void k_bupdate(float* __restrict__ B, int64_t M, int K,
+                                                    const double* __restrict__ W, int64_t Mpad,
+                                                    const double* __restrict__ V, _Float16* __restrict__ Bq,
+                                                    float* __restrict__ bmax, double* __restrict__ Gpart, int update,
+                                                    _Float16* __restrict__ BqD) {
+  __shared__ BupLds<NT> S;
+  extern __shared__ __align__(16) float lines[];
+  bupdate_body<KP, NT, RW>(S, lines, B, M, K, W, Mpad, V, Bq, bmax, Gpart, update, blockIdx.x, BqD);
+}
+
+int bupdate_blocks(const Shape& s) { return (int)((s.M + kBupRows - 1) / kBupRows); }
+
+template <int KP, int NT>
+static void bupdate_launch(const Shape& s, float* B, const double* W, const double* V, _Float16* Bq, float* Bsc,
+                           double* Gpart, int update, _Float16* BqD, hipStream_t st) {
+  const unsigned g = (unsigned)bupdate_blocks(s);
+  if (BqD)
+    k_bupdate<KP, NT, true><<<g, 256, bup_dyn_lds(s.K, true), st>>>(B, s.M, s.K, W, s.Mpad, V, Bq, Bsc, Gpart, update,
+                                                                     BqD);
+  else
+    k_bupdate<KP, NT, false><<<g, 256, bup_dyn_lds(s.K, false), st>>>(B, s.M, s.K, W, s.Mpad, V, Bq, Bsc, Gpart,
+                                                                      update, nullptr);
+}
+
+hipError_t bupdate(const Shape& s, float* B, const double* W, const double* V, _Float16* Bq, float* Bsc,
+                   double* Gpart, int update, hipStream_t st, _Float16* BqD) {
+  if (s.thin) {
+    Bq = nullptr;
+    Bsc = nullptr;
+    BqD = nullptr;
+  } else {
+    k_zero_f32<<<1, 64, 0, st>>>(Bsc, s.KP);
+  }
+  if (s.K <= 16)
+    bupdate_launch<32, 1>(s, B, W, V, Bq, Bsc, Gpart, update, BqD, st);
+  else if (s.K <= 32)
+    bupdate_launch<32, 2>(s, B, W, V, Bq, Bsc, Gpart, update, BqD, st);
+  else if (s.K <= 48)
+    bupdate_launch<64, 3>(s, B, W, V, Bq, Bsc, Gpart, update, BqD, st);
+  else
+    bupdate_launch<64, 4>(s, B, W, V, Bq, Bsc, Gpart, update, BqD, st);
+  if (!s.thin) {
+    const unsigned g = (unsigned)bupdate_blocks(s);
+    if (s.KP == 32)
+      k_packh<32><<<g, 256, 0, st>>>(B, s.M, s.K, s.nchunks, Bq, Bsc);
+    else
+      k_packh<64><<<g, 256, 0, st>>>(B, s.M, s.K, s.nchunks, Bq, Bsc);
+  }
+  return hipGetLastError();
+}
+
 // E order of 256 columns of C (block bid), and their contribution to the row maxima.
 template <int KP>
 __device__ __forceinline__ void packc_body(const float* __restrict__ C, f32x4* __restrict__ Cq,
@@ -2081,31 +2064,16 @@ hipError_t reduce_w(const Shape& s, const float* Wpart, int R, double* W, hipStr
   return hipGetLastError();
 }
 
-// full[i] = sum_p part[p][i] over KP*KP entries, p ascending.
-__global__ void k_reduce_full(const double* __restrict__ part, int64_t P, int n, double* __restrict__ full) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= n) return;
-  double s = 0.0;
-  for (int64_t p = 0; p < P; ++p) s += part[p * n + q];
-  full[q] = s;
-}
-
-hipError_t reduce_full(const double* part, int64_t P, int KP, double* full, hipStream_t st) {
-  const int n = KP * KP;
-  k_reduce_full<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(part, P, n, full);
-  return hipGetLastError();
-}
-
-// full[a][b] = full[b][a] = sum_p part[p][pair(a,b)] in a fixed order.  A block of 256
+// full[a][b] = full[b][a] = sum_p part[p][pair(a,b)] over the NP pairs of the partials (a < KP;
+// entries of full past them keep their value), in a fixed order.  A block of 256
 // threads takes kSymPairs consecutive pairs with 32 threads each: thread (t, qi) =
 // (tid / 8, tid % 8) adds the partials p = t, t + 32, t + 64, ... in turn, then the 32
 // sums of a pair are combined by a fixed tree (xor shuffles within each wave, then the
 // four waves in order).  Every thread reaches the barrier.
 constexpr int kSymPairs = 8;
-__device__ __forceinline__ void reduce_sym_body(const double* __restrict__ part, int64_t P, int KP,
+__device__ __forceinline__ void reduce_sym_body(const double* __restrict__ part, int64_t P, int NP, int KP,
                                                 double* __restrict__ full, int64_t bid) {
   __shared__ double ws[4][kSymPairs];
-  const int NP = KP * (KP + 1) / 2;
   const int tid = threadIdx.x, qi = tid & (kSymPairs - 1), t = tid / kSymPairs, wave = tid >> 6;
   const int q = (int)bid * kSymPairs + qi;
   double s = 0.0;
@@ -2137,14 +2105,13 @@ __device__ __forceinline__ void reduce_sym_body(const double* __restrict__ part,
   }
 }
 
-__global__ __launch_bounds__(256) void k_reduce_sym(const double* __restrict__ part, int64_t P, int KP,
+__global__ __launch_bounds__(256) void k_reduce_sym(const double* __restrict__ part, int64_t P, int NP, int KP,
                                                     double* __restrict__ full) {
-  reduce_sym_body(part, P, KP, full, blockIdx.x);
+  reduce_sym_body(part, P, NP, KP, full, blockIdx.x);
 }
 
-hipError_t reduce_sym(const double* part, int64_t P, int KP, double* full, hipStream_t st) {
-  const int NP = KP * (KP + 1) / 2;
-  k_reduce_sym<<<(unsigned)((NP + kSymPairs - 1) / kSymPairs), 256, 0, st>>>(part, P, KP, full);
+hipError_t reduce_sym(const double* part, int64_t P, int NP, int KP, double* full, hipStream_t st) {
+  k_reduce_sym<<<(unsigned)((NP + kSymPairs - 1) / kSymPairs), 256, 0, st>>>(part, P, NP, KP, full);
   return hipGetLastError();
 }
 
@@ -2316,7 +2283,7 @@ __global__ __launch_bounds__(256) void kg_vgram(const GTable* __restrict__ g) {
 template <int KP>
 __global__ __launch_bounds__(256) void kg_reduce_v(const GTable* __restrict__ g) {
   DID_GROUP_LOOP(GS_REDV)
-  reduce_sym_body(d.Vpart, d.vblocks, KP, d.V, bid);
+  reduce_sym_body(d.Vpart, d.vblocks, KP * (KP + 1) / 2, KP, d.V, bid);
   DID_GROUP_END
 }
 
@@ -2339,9 +2306,21 @@ __global__ __launch_bounds__(256) void kg_reduce_w(const GTable* __restrict__ g)
 }
 
 template <int KP>
-__global__ __launch_bounds__(kBupThreads) void kg_bupdate(const GTable* __restrict__ g) {
+__global__ __launch_bounds__(256, 2) void kg_bupdate(const GTable* __restrict__ g) {
+  constexpr int NL = KP / 16 - 1;
+  __shared__ union {
+    BupLds<NL> lo;
+    BupLds<NL + 1> hi;
+  } S;
+  extern __shared__ __align__(16) float lines[];
   DID_GROUP_LOOP(GS_BUP)
-  bupdate_body<KP, false, false>(d.B, d.M, d.K, d.W, d.Mpad, d.V, d.Bq, d.Bsc, d.Gpart, 1, bid);
+  float* B = as_global(d.B);
+  const double* W = as_global(d.W);
+  const double* V = as_global(d.V);
+  if (d.K <= 16 * NL)
+    bupdate_body<KP, NL, false>(S.lo, lines, B, d.M, d.K, W, d.Mpad, V, d.Bq, d.Bsc, d.Gpart, 1, bid, nullptr);
+  else
+    bupdate_body<KP, NL + 1, false>(S.hi, lines, B, d.M, d.K, W, d.Mpad, V, d.Bq, d.Bsc, d.Gpart, 1, bid, nullptr);
   DID_GROUP_END
 }
 
@@ -2349,9 +2328,10 @@ template <int KP>
 __global__ __launch_bounds__(256) void kg_reduce_g(const GTable* __restrict__ g) {
   DID_GROUP_LOOP(GS_REDG)
   // the G reduction, then the H-order packing of B: both need only the B update
-  const int64_t ng = (KP * (KP + 1) / 2 + kSymPairs - 1) / kSymPairs;
+  const int np = g_pairs(d.K);
+  const int64_t ng = (np + kSymPairs - 1) / kSymPairs;
   if (bid < ng)
-    reduce_sym_body(d.Gpart, d.bupblocks, KP, d.G, bid);
+    reduce_sym_body(d.Gpart, d.bupblocks, np, KP, d.G, bid);
   else
     packh_body<KP>(d.B, d.M, d.K, d.nchunks, d.Bq, d.Bsc, bid - ng);
   DID_GROUP_END
@@ -2379,7 +2359,7 @@ void ginst_items(const Shape& s, int R, int64_t items[GS_N]) {
   items[GS_ROW] = (nsg * R + 7) / 8 * 8;
   items[GS_REDW] = ((int64_t)s.K * s.Mpad + 255) / 256;
   items[GS_BUP] = bupdate_blocks(s);
-  items[GS_REDG] = (np + kSymPairs - 1) / kSymPairs + bupdate_blocks(s);
+  items[GS_REDG] = (g_pairs(s.K) + kSymPairs - 1) / kSymPairs + bupdate_blocks(s);
   items[GS_ADV] = 1;
 }
 
@@ -2404,7 +2384,7 @@ static hipError_t group_grids_t(int64_t grids[GS_N]) {
   if ((e = occ((const void*)kg_reduce_v<KP>, 256, 0, &grids[GS_REDV])) != hipSuccess) return e;
   if ((e = occ((const void*)kg_rowpass<KP, XT>, 256, 0, &grids[GS_ROW])) != hipSuccess) return e;
   if ((e = occ((const void*)kg_reduce_w<KP>, 256, 0, &grids[GS_REDW])) != hipSuccess) return e;
-  if ((e = occ((const void*)kg_bupdate<KP>, kBupThreads, 0, &grids[GS_BUP])) != hipSuccess) return e;
+  if ((e = occ((const void*)kg_bupdate<KP>, 256, bup_dyn_lds(KP, false), &grids[GS_BUP])) != hipSuccess) return e;
   if ((e = occ((const void*)kg_reduce_g<KP>, 256, 0, &grids[GS_REDG])) != hipSuccess) return e;
   if ((e = occ((const void*)kg_advance, 64, 0, &grids[GS_ADV])) != hipSuccess) return e;
   return hipSuccess;
@@ -2436,7 +2416,7 @@ static void group_iteration_t(const GTable* t, const int64_t* gr, hipStream_t st
   kg_reduce_v<KP><<<(unsigned)gr[GS_REDV], 256, 0, st>>>(t);
   kg_rowpass<KP, XT><<<(unsigned)gr[GS_ROW], 256, 0, st>>>(t);
   kg_reduce_w<KP><<<(unsigned)gr[GS_REDW], 256, 0, st>>>(t);
-  kg_bupdate<KP><<<(unsigned)gr[GS_BUP], kBupThreads, 0, st>>>(t);
+  kg_bupdate<KP><<<(unsigned)gr[GS_BUP], 256, bup_dyn_lds(KP, false), st>>>(t);
   kg_reduce_g<KP><<<(unsigned)gr[GS_REDG], 256, 0, st>>>(t);
   kg_advance<<<(unsigned)gr[GS_ADV], 64, 0, st>>>(t);
 }
