@@ -208,9 +208,9 @@ int did_sync(did_handle h);
  * iterations recorded since the last read into ms[0 .. min(cap, *n_stages)-1], the stage
  * count into *n_stages and the iteration count into *n_iters, and clears the record.
  * did_stage_name(i) names stage i ("column_pass", "row_pass", ...; "" if out of range).
- * On the MFMA path the V partials and their reduction run on a second stream, overlapped
- * with the row pass, so "sweep_v" times the sweep and the packing of the swept C for the
- * row pass, and "reduce_v" is empty.
+ * On the MFMA path "sweep_v" times the sweep and the kernel that packs the swept C for the
+ * row pass and forms the V partials and the objective, "reduce_w" the reductions of W and V,
+ * "reduce_g" that of G with the second packing of B; "reduce_f" and "reduce_v" are empty.
  */
 int did_profile(did_handle h, int32_t enable);
 int did_profile_read(did_handle h, double* ms, int32_t cap, int32_t* n_stages, int64_t* n_iters);

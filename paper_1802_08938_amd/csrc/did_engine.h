@@ -36,10 +36,6 @@ struct did_ctx {
   int dev = 0;
   hipStream_t st = nullptr;
   bool own_stream = false;
-  // MFMA path: a second stream on which the V partials and their reduction run while the
-  // row pass runs on st (both only read the packed C); ev_c: C packed, ev_v: V reduced
-  hipStream_t st2 = nullptr;
-  hipEvent_t ev_c = nullptr, ev_v = nullptr;
   didk::Shape s{};
   bool own_x = true;
   void* X = nullptr;   // float32 (column-major), or the column-pass tiled bf16 copy (s.xbf16)
@@ -95,9 +91,6 @@ struct did_ctx {
   // one captured iteration of the MFMA path, replayed by did_iterate (not in the carried
   // form, not while profiling; never by did_iterate_static, which must not allocate)
   bool use_graph = true;
-  // whether eager iterations may create the second stream (not in did_iterate_static,
-  // whose context lives on the caller's stack and must not create resources)
-  bool may_create_st2 = true;
   bool graph_failed = false;
   hipGraphExec_t gexec = nullptr;
   // per-stage timing: kStages+1 events per profiled iteration

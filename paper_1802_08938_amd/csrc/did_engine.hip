@@ -130,12 +130,8 @@ void release(did_ctx* h) {
   if (!h) return;
   DeviceGuard g(h->dev);
   if (h->st) (void)hipStreamSynchronize(h->st);
-  if (h->st2) (void)hipStreamSynchronize(h->st2);
   if (h->gexec) (void)hipGraphExecDestroy(h->gexec);
   for (hipEvent_t ev : h->prof_events) (void)hipEventDestroy(ev);
-  if (h->ev_c) (void)hipEventDestroy(h->ev_c);
-  if (h->ev_v) (void)hipEventDestroy(h->ev_v);
-  if (h->st2) (void)hipStreamDestroy(h->st2);
   h->prof_events.clear();
   for (void* p : h->allocs) (void)hipFree(p);
   h->allocs.clear();
@@ -206,7 +202,9 @@ WorkPlan plan_work(Shape& s, int n_blocks, int row_blocks) {
     *S = std::max<int64_t>(1, (n + w.P - 1) / w.P);
     return didk::range_bounds(T, w.P, *S, nullptr);
   };
-  const int64_t vbytes = didk::vgram_blocks(s) * NP * 8, nb = (s.N + 127) / 128;
+  // room for a V partial per tile up to 256, of KP coordinates (more than the blocks in use
+  // write: an instance's footprint stays what pools and budgets were sized for)
+  const int64_t vbytes = std::min<int64_t>(T, 256) * NP * 8, nb = (s.N + 127) / 128;
   int64_t S0;
   const int64_t R0 = ranges(16, &S0);
   const int64_t bound = s.KP * s.N * 4 + vbytes + R0 * s.KP * s.Mpad * 4 + R0 * 8;
@@ -518,7 +516,7 @@ int setup(did_ctx* h, const void* Xv, int64_t M, int64_t N, int32_t K, const did
 hipError_t refresh_b_derived(did_ctx* h) {
   hipError_t e = didk::bupdate(h->s, h->B, h->W, h->V, h->Bq, h->Bsc, h->Gpart, 0, h->st);
   if (e != hipSuccess) return e;
-  return didk::reduce_sym(h->Gpart, didk::bupdate_blocks(h->s), didk::g_pairs(h->s.K), h->s.KP, h->G, h->st);
+  return didk::finish_b(h->s, h->Gpart, h->G, h->B, h->Bq, h->Bsc, h->st);
 }
 
 int objective_pass(did_ctx* h) {
@@ -530,7 +528,7 @@ int objective_pass(did_ctx* h) {
       return dev_fail(h, e, "objective pass");
     return DID_OK;
   }
-  if ((e = didk::colpass(h->s, h->X, h->Cq, h->Bq, h->Bsc, h->H, h->fpart, 0, h->st)) != hipSuccess)
+  if ((e = didk::colpass(h->s, h->X, h->Cq, h->Bq, h->Bsc, h->Csc, h->H, h->fpart, 0, h->st)) != hipSuccess)
     return dev_fail(h, e, "objective pass");
   if ((e = didk::reduce_f(h->fpart, didk::colpass_blocks(h->s), h->fobj, 0.5, h->st)) != hipSuccess)
     return dev_fail(h, e, "objective reduce");
@@ -540,7 +538,7 @@ int objective_pass(did_ctx* h) {
 // Repack C after it was changed outside the sweep (the thin path keeps no packed copy).
 hipError_t pack_c(did_ctx* h) {
   if (h->s.thin) return hipSuccess;
-  return didk::packc(h->s, h->C, h->Cq, h->Csc, h->st);
+  return didk::packc(h->s, h->C, h->Cq, h->st);
 }
 
 int apply_init_scale(did_ctx* h) {
@@ -695,12 +693,11 @@ int check_deferred(did_ctx* h) {
   return DID_OK;
 }
 
-// One iteration of the MFMA path on the buffers of h, enqueued on h->st (and, unless
-// one_stream, the V stages on h->st2), with a profiling event before the first and after
-// every stage when ev is given.  The objective goes to fhist at the device iteration
-// counter tdev, so the launches carry no host iteration index (the same launches can be
-// captured once and replayed).
-static int enqueue_iteration(did_ctx* h, hipEvent_t* ev, bool one_stream = false) {
+// One iteration of the MFMA path on the buffers of h, enqueued on h->st, with a profiling
+// event before the first and after every stage when ev is given.  The objective goes to fhist
+// at the device iteration counter tdev, so the launches carry no host iteration index (the
+// same launches can be captured once and replayed).
+static int enqueue_iteration(did_ctx* h, hipEvent_t* ev) {
   const Shape& s = h->s;
   hipError_t e;
 #define DID_MARK(q) \
@@ -710,32 +707,19 @@ static int enqueue_iteration(did_ctx* h, hipEvent_t* ev, bool one_stream = false
   const bool carry = h->refresh > 1;
   DID_MARK(0);
   if (carry)
-    e = didk::colpass_carry(s, h->X, h->t % h->refresh == 0, h->Cq, h->Bq, h->BqD, h->Bsc, h->H, h->fpart, h->Rres,
-                            h->st);
+    e = didk::colpass_carry(s, h->X, h->t % h->refresh == 0, h->Cq, h->Bq, h->BqD, h->Bsc, h->Csc, h->H, h->fpart,
+                            h->Rres, h->st);
   else
-    e = didk::colpass(s, h->X, h->Cq, h->Bq, h->Bsc, h->H, h->fpart, 1, h->st);
+    e = didk::colpass(s, h->X, h->Cq, h->Bq, h->Bsc, h->Csc, h->H, h->fpart, 1, h->st);
   if (e != hipSuccess) return dev_fail(h, e, "column pass");
   DID_MARK(1);
-  if ((e = didk::reduce_f_hist(h->fpart, didk::colpass_blocks(s), h->fhist, h->hist_cap, h->tdev, 0.5, h->st)) !=
-      hipSuccess)
-    return dev_fail(h, e, "objective reduce");
   DID_MARK(2);
   if ((e = didk::sweep(s, h->H, h->C, h->Cq, h->Csc, h->G, h->st, carry ? h->CqD : nullptr)) != hipSuccess)
     return dev_fail(h, e, "sweep");
-  // V = tril(C'C'^T), on the second stream when there is one (overlapped with the row pass
-  // and the W reduction; the B update waits for it)
-  hipStream_t st2 = one_stream ? nullptr : h->st2;
-  hipStream_t sv = h->st;
-  if (st2) {
-    if ((e = hipEventRecord(h->ev_c, h->st)) != hipSuccess ||
-        (e = hipStreamWaitEvent(st2, h->ev_c, 0)) != hipSuccess)
-      return dev_fail(h, e, "stream order");
-    sv = st2;
-  }
-  if ((e = didk::vgram(s, h->Cq, h->Csc, h->Vpart, sv)) != hipSuccess) return dev_fail(h, e, "V partials");
-  if ((e = didk::reduce_sym(h->Vpart, didk::vgram_blocks(s), didk::n_pairs(s.KP), s.KP, h->V, sv)) != hipSuccess)
-    return dev_fail(h, e, "V reduce");
-  if (st2 && (e = hipEventRecord(h->ev_v, st2)) != hipSuccess) return dev_fail(h, e, "stream order");
+  // the packing of the swept C for the row pass, the V partials and the objective
+  if ((e = didk::packv(s, h->C, h->Cq, h->Csc, h->Vpart, h->fpart, h->fhist, h->hist_cap, h->tdev, h->st)) !=
+      hipSuccess)
+    return dev_fail(h, e, "V partials");
   DID_MARK(3);
   DID_MARK(4);
   if (carry)
@@ -744,14 +728,14 @@ static int enqueue_iteration(did_ctx* h, hipEvent_t* ev, bool one_stream = false
     e = didk::rowpass(s, h->XR, h->Cq, h->Csc, h->Bq, h->Wpart, h->rbounds, h->R, h->st);
   if (e != hipSuccess) return dev_fail(h, e, "row pass");
   DID_MARK(5);
-  if ((e = didk::reduce_w(s, h->Wpart, h->R, h->W, h->st)) != hipSuccess) return dev_fail(h, e, "W reduce");
+  if ((e = didk::reduce_wv(s, h->Wpart, h->R, h->W, h->Vpart, h->V, h->st)) != hipSuccess)
+    return dev_fail(h, e, "W and V reduce");
   DID_MARK(6);
-  if (st2 && (e = hipStreamWaitEvent(h->st, h->ev_v, 0)) != hipSuccess) return dev_fail(h, e, "stream order");
   if ((e = didk::bupdate(s, h->B, h->W, h->V, h->Bq, h->Bsc, h->Gpart, 1, h->st, carry ? h->BqD : nullptr)) !=
       hipSuccess)
     return dev_fail(h, e, "B update");
   DID_MARK(7);
-  if ((e = didk::reduce_sym(h->Gpart, didk::bupdate_blocks(s), didk::g_pairs(s.K), s.KP, h->G, h->st)) != hipSuccess)
+  if ((e = didk::finish_b(s, h->Gpart, h->G, h->B, h->Bq, h->Bsc, h->st)) != hipSuccess)
     return dev_fail(h, e, "G reduce");
   DID_MARK(8);
 #undef DID_MARK
@@ -759,14 +743,9 @@ static int enqueue_iteration(did_ctx* h, hipEvent_t* ev, bool one_stream = false
 }
 
 // Iterations of the MFMA path on the buffers of h (shared by did_iterate and the
-// allocation-free did_iterate_static).  With a second stream (h->st2) the V partials and
-// their reduction overlap the row pass; without one they run in order on h->st.  Without
-// profiling, two or more iterations of the refresh-every-iteration form replay one
-// captured iteration (a hipGraph kept by the handle), which removes the host launch cost
-// that bounds small shapes.  The captured iteration runs on h->st alone: a capture that
-// forks onto a second stream and joins back left the device memory its kernels use
-// allocated after hipGraphExecDestroy and hipFree (measured on ROCm 7.2), so the V stages
-// give up their overlap with the row pass there.
+// allocation-free did_iterate_static).  Without profiling, two or more iterations of the
+// refresh-every-iteration form replay one captured iteration (a hipGraph kept by the handle),
+// which removes the host launch cost that bounds small shapes.
 int iterate_mfma(did_ctx* h, int32_t n) {
   hipError_t e;
   if (n <= 0) return DID_OK;
@@ -777,7 +756,7 @@ int iterate_mfma(did_ctx* h, int32_t n) {
         (void)hipGetLastError();
         h->graph_failed = true;
       } else {
-        const int rc = enqueue_iteration(h, nullptr, true);
+        const int rc = enqueue_iteration(h, nullptr);
         e = hipStreamEndCapture(h->st, &g);
         if (rc) {
           if (g) (void)hipGraphDestroy(g);
@@ -797,14 +776,6 @@ int iterate_mfma(did_ctx* h, int32_t n) {
       h->t += n;
       return DID_OK;
     }
-  }
-  // the second stream and its events, made on the first eager iteration (a handle that only
-  // replays its graph or runs inside a batch never needs them)
-  if (!h->st2 && h->may_create_st2) {
-    if ((e = hipStreamCreateWithFlags(&h->st2, hipStreamNonBlocking)) != hipSuccess ||
-        (e = hipEventCreateWithFlags(&h->ev_c, hipEventDisableTiming)) != hipSuccess ||
-        (e = hipEventCreateWithFlags(&h->ev_v, hipEventDisableTiming)) != hipSuccess)
-      return dev_fail(h, e, "second stream");
   }
   for (int32_t it = 0; it < n; ++it) {
     hipEvent_t* ev = nullptr;
@@ -897,7 +868,7 @@ static int iterate_thin(did_ctx* h, int32_t n) {
         return dev_fail(h, e, "pack B");
     }
     if ((e = mark(7)) != hipSuccess) return dev_fail(h, e, "profile record");
-    if ((e = didk::reduce_sym(h->Gpart, didk::bupdate_blocks(s), didk::g_pairs(s.K), s.KP, h->G, h->st)) != hipSuccess)
+    if ((e = didk::finish_b(s, h->Gpart, h->G, h->B, h->Bq, h->Bsc, h->st)) != hipSuccess)
       return dev_fail(h, e, "G reduce");
     if ((e = mark(8)) != hipSuccess) return dev_fail(h, e, "profile record");
     ++h->t;

@@ -122,8 +122,9 @@ int bupdate_blocks(const Shape& s);
 // (with_h = 1) csplit partials of H = B^T E, each over a share of the rows (h_elems floats: row
 // k of tile T of partial p at p * h_stride + (T * K4 + k) * 32, K4 = K rounded up to a
 // multiple of 4).
-// C enters through its packed pieces Cq.
-hipError_t colpass(const Shape& s, const void* X, const void* Cq, const _Float16* Bq, const float* Bsc,
+// C enters through its packed pieces Cq.  With H the maxima in Bsc and Csc are cleared for the
+// sweep and the B update that follow.
+hipError_t colpass(const Shape& s, const void* X, const void* Cq, const _Float16* Bq, float* Bsc, float* Csc,
                    float* Hout, double* fpart, int with_h, hipStream_t st);
 int64_t colpass_blocks(const Shape& s);  // blocks of 32 cwpb columns and 1 / csplit of the rows
 
@@ -138,7 +139,7 @@ int column_split(const Shape& s, int64_t max_split);
 //   rowpass_carry: E' = R - B dC (dC = C' - C, packed in CqD by the sweep), the W
 //     partials with C' from Cq, and E' stored into R.
 hipError_t colpass_carry(const Shape& s, const void* X, int refresh, const void* Cq, const _Float16* Bq,
-                         const _Float16* BqD, const float* Bsc, float* Hout, double* fpart, float* R,
+                         const _Float16* BqD, float* Bsc, float* Csc, float* Hout, double* fpart, float* R,
                          hipStream_t st);
 hipError_t rowpass_carry(const Shape& s, float* R, const void* Cq, const void* CqD, const float* Csc,
                          const _Float16* Bq, float* Wpart, const int64_t* tb, int Rn, hipStream_t st);
@@ -150,12 +151,14 @@ hipError_t rowpass_carry(const Shape& s, float* R, const void* Cq, const void* C
 hipError_t sweep(const Shape& s, const float* Hin, float* C, void* Cq, float* Csc, const double* G,
                  hipStream_t st, void* CqD = nullptr);
 inline int64_t cqd_bytes(const Shape& s) { return n_tiles32(s) * cq_units_e(s.KP) * 16; }
-// Pack C into Cq (after C was set from outside the sweep).
-hipError_t packc(const Shape& s, const float* C, void* Cq, float* Csc, hipStream_t st);
+// Pack C into Cq's E order (after C was set from outside the sweep).
+hipError_t packc(const Shape& s, const float* C, void* Cq, hipStream_t st);
 
-// V partials: tril(C C^T) per block of tiles from the packed C (float64, n_pairs(KP) per
-// block).
-hipError_t vgram(const Shape& s, const void* Cq, const float* Csc, double* Vpart, hipStream_t st);
+// After the sweep: the W order of C (row scales in Csc), the V partials tril(C C^T) per block
+// of tiles (float64, g_pairs(K) per block), and the objective 0.5 * sum of the f partials into
+// fhist[*tdev % cap], then *tdev += 1 (replayable).
+hipError_t packv(const Shape& s, const float* C, void* Cq, float* Csc, double* Vpart, const double* fpart,
+                 double* fhist, int64_t cap, int64_t* tdev, hipStream_t st);
 int64_t vgram_blocks(const Shape& s);
 
 // Row pass: W partial per column range r (K x Mpad floats): Wpart[r] = (X - BC)[:, range] C[:, range]^T.
@@ -164,13 +167,12 @@ hipError_t rowpass(const Shape& s, const void* X, const void* Cq, const float* C
                    const int64_t* tb, int R, hipStream_t st);
 
 // Fixed-order reductions.
-hipError_t reduce_w(const Shape& s, const float* Wpart, int R, double* W, hipStream_t st);
-// (NP pairs per partial)
-hipError_t reduce_sym(const double* part, int64_t P, int NP, int KP, double* full, hipStream_t st);
+hipError_t reduce_wv(const Shape& s, const float* Wpart, int R, double* W, const double* Vpart, double* V,
+                     hipStream_t st);
 hipError_t reduce_f(const double* part, int64_t P, double* out, double scale, hipStream_t st);
-// scale * sum of the partials into fhist[*tdev % cap], then *tdev += 1 (replayable)
-hipError_t reduce_f_hist(const double* part, int64_t P, double* fhist, int64_t cap, int64_t* tdev, double scale,
-                         hipStream_t st);
+// after the B update: G = B^T B from its partials, and B's H order (column scales in Bsc)
+hipError_t finish_b(const Shape& s, const double* Gpart, double* G, const float* B, _Float16* Bq, float* Bsc,
+                    hipStream_t st);
 // *p = v from a kernel (no memset node, no host memory)
 hipError_t set_i64(int64_t* p, int64_t v, hipStream_t st);
 
@@ -180,7 +182,7 @@ hipError_t set_i64(int64_t* p, int64_t v, hipStream_t st);
 // group's instances; an instance's items are exactly the blocks of its single-instance
 // launch, run by the same device code, so its results do not depend on the batch.
 constexpr int kMaxBatch = 64;  // instances per group
-enum GStage { GS_COL = 0, GS_REDF, GS_SWEEP, GS_PACKW, GS_VGRAM, GS_REDV, GS_ROW, GS_REDW, GS_BUP, GS_REDG, GS_ADV, GS_N };
+enum GStage { GS_COL = 0, GS_SWEEP, GS_PACKV, GS_ROW, GS_REDWV, GS_BUP, GS_FIN, GS_N };
 
 struct GInst {
   const void* X;   // X as the column pass reads it

@@ -171,11 +171,11 @@ struct x_is_tiled {
 //       C[kk][32T + row32(8q + t, l/32)] * 2^w_kk,  kk = 32b + l%32,
 //       with w_kk = scale_exp(max_j C[kk][j]) per row, over all N columns
 //       (A operand of W^T in the row pass; both operands of C C^T).
-// Entries with kk >= K or column >= N are zero.  The E order depends only on the column,
-// so it is written by the kernel that changes C (the sweep, or k_packc); that kernel also
-// gathers the row maxima into Csc[0, KP) with atomic maxima (exact, so the result does not
-// depend on the order), and k_packw writes the W order afterwards, storing 2^-w_kk into
-// Csc[KP + kk].
+// Entries with kk >= K or column >= N are zero.  The E order depends only on the column, so
+// it is written by the kernel that changes C (the sweep, or k_packc).  The sweep also gathers
+// the row maxima into Csc[0, KP) with atomic maxima (exact, so the result does not depend on
+// the order; the column pass before it clears them), and k_packv writes the W order
+// afterwards, storing 2^-w_kk into Csc[KP + kk].
 //
 // dst[e] = src[e] for e = threadIdx.x, threadIdx.x + 256, ... < n (a block of 256 threads
 // copying between global memory and LDS): each thread issues G loads before their stores,
@@ -199,8 +199,8 @@ __device__ __forceinline__ void block_copy(float* dst, const float* src, int n) 
 // the global stores are coalesced.  All threads of the block call it, after Ct is
 // complete; it takes 256 ints of LDS scratch (cs) from the caller.
 template <int KP>
-__device__ __forceinline__ void pack_block(f32x4* __restrict__ Cq, float* __restrict__ cmax, int64_t j0, int nv,
-                                           const float* Ct, int K, int64_t ntiles, int* cs) {
+__device__ __forceinline__ void pack_block(f32x4* __restrict__ Cq, int64_t j0, int nv, const float* Ct, int K,
+                                           int64_t ntiles, int* cs) {
   constexpr int KS = KP / 16;
   constexpr int UE0 = CqL<KP>::E0;
   constexpr int UT = CqL<KP>::T;  // units per tile of the target buffer
@@ -225,11 +225,6 @@ __device__ __forceinline__ void pack_block(f32x4* __restrict__ Cq, float* __rest
     }
     if (smin <= smax && smax - smin <= kUniformSpread) sc = smin;
     cs[tid] = sc;
-  }
-  if (tid < K) {  // row maxima over the block's columns (C >= 0: integer order = float order)
-    float mx = 0.0f;
-    for (int j = 0; j < nv; ++j) mx = fmaxf(mx, Ct[j * K + tid]);
-    if (mx > 0.0f) atomicMax(reinterpret_cast<int*>(cmax) + tid, __float_as_int(mx));
   }
   __syncthreads();
   for (int g = tid; g < GE; g += 256) {
@@ -261,62 +256,6 @@ __device__ __forceinline__ void pack_block(f32x4* __restrict__ Cq, float* __rest
         if (same) w[0] = -w[0];
       }
       Cq[(T0 + tb) * UT + UE0 + u] = w;
-    }
-  }
-}
-
-// W-order units of the eight tiles of columns 256 bid .. 256 bid + 255, read straight from
-// C (each group's eight loads are coalesced across the lanes, which take consecutive
-// coordinates), with the row scales from the maxima in Csc[0, KP); block 0 stores the
-// inverse scales into Csc[KP, 2 KP).  No LDS staging, so that many blocks stay resident.
-template <int KP>
-__device__ __forceinline__ void packw_body(const float* __restrict__ C, f32x4* __restrict__ Cq,
-                                           float* __restrict__ Csc, int64_t N, int K, int64_t bid) {
-  constexpr int NB = KP / 32;
-  constexpr int UE = CqL<KP>::E;
-  constexpr int UT = CqL<KP>::T;
-  constexpr int GW = 8 * NB * 128;  // W groups per block: (tile, b, q, lane)
-  static_assert(GW % 512 == 0, "two groups per thread and step");
-  __shared__ float ws[KP];
-  const int tid = threadIdx.x;
-  const int64_t j0 = bid * 256, T0 = bid * 8, ntiles = (N + 31) / 32;
-  if (tid < KP) {
-    const int w = tid < K ? scale_exp(Csc[tid]) : 0;
-    ws[tid] = pow2f(w);
-    if (bid == 0) Csc[KP + tid] = pow2f(-w);
-  }
-  __syncthreads();
-  // two groups per step (g and g + 256; GW is a multiple of 512): their sixteen loads are
-  // issued before either group is split and stored
-  for (int g0 = tid; g0 < GW; g0 += 512) {
-    float v[2][8];
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int g = g0 + 256 * r;
-      const int tb = g / (NB * 128), rem = g % (NB * 128), bq = rem >> 6, l = rem & 63;
-      const int b = bq >> 1, q = bq & 1;
-      const int kk = 32 * b + (l & 31), h = l >> 5;
-      const bool ok = T0 + tb < ntiles && kk < K;
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const int64_t j = j0 + 32 * tb + row32(8 * q + t, h);
-        v[r][t] = (ok && j < N) ? C[j * K + kk] : 0.0f;
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int g = g0 + 256 * r;
-      const int tb = g / (NB * 128), rem = g % (NB * 128), bq = rem >> 6, l = rem & 63;
-      const int b = bq >> 1, q = bq & 1;
-      if (T0 + tb >= ntiles) continue;
-      const int kk = 32 * b + (l & 31);
-      const float sc = ws[kk];
-#pragma unroll
-      for (int t = 0; t < 8; ++t) v[r][t] *= sc;
-      const Split2 sp = split2(v[r]);
-      f32x4* tile = Cq + (T0 + tb) * UT;
-#pragma unroll
-      for (int p = 0; p < 2; ++p) tile[UE + ((b * 2 + q) * 2 + p) * 64 + l] = f16_as_f32x4(sp.p[p]);
     }
   }
 }
@@ -523,12 +462,6 @@ __device__ __forceinline__ void packh_body(const float* __restrict__ B, int64_t 
   }
 }
 
-template <int KP>
-__global__ __launch_bounds__(256) void k_packh(const float* __restrict__ B, int64_t M, int K, int64_t nchunks,
-                                               _Float16* __restrict__ Bq, float* __restrict__ Bsc) {
-  packh_body<KP>(B, M, K, nchunks, Bq, Bsc, blockIdx.x);
-}
-
 __global__ void k_zero16(f32x4* p, int64_t n) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = f32x4{0, 0, 0, 0};
@@ -582,7 +515,7 @@ __global__ void k_zero_f32(float* p, int n) {
 template <int KP, bool WITH_H, typename XT, bool RW = false, int WPB = 4>
 __device__ __forceinline__ void colpass_body(const XT* __restrict__ X, int64_t M, int64_t N, int K,
                                              const f32x4* __restrict__ Cq, const _Float16* __restrict__ Bq,
-                                             const float* __restrict__ Bsc, float* __restrict__ Hout,
+                                             float* Bsc, float* __restrict__ Csc, float* __restrict__ Hout,
                                              double* __restrict__ fpart, int64_t nchunks, int vec4, int csplit,
                                              int64_t bid, const _Float16* __restrict__ BqE = nullptr,
                                              float* Rout = nullptr, int rvec4 = 0) {
@@ -611,6 +544,8 @@ __device__ __forceinline__ void colpass_body(const XT* __restrict__ X, int64_t M
   const XT* xtile = X + (tileok ? j0 : 0) * M;
   const uint32_t loff = (uint32_t)(lc * M + 4 * half);
 
+  // the maxima that this iteration's sweep and B update gather start from zero
+  if (WITH_H && bid == 0 && tid < KP) Csc[tid] = Bsc[tid] = 0.0f;
   f16x8 cP[KS][2];  // pieces of C[16s + 8*half + t][col] 2^t_col, from the packed tile
   float ct = 1.0f;  // 2^-t_col
   if (tileok) {
@@ -858,10 +793,10 @@ template <int KP, bool WITH_H, typename XT, int WPB>
 __global__ __launch_bounds__(64 * WPB, 8 / WPB) void k_colpass(const XT* __restrict__ X, int64_t M, int64_t N, int K,
                                                                const f32x4* __restrict__ Cq,
                                                                const _Float16* __restrict__ Bq,
-                                                               const float* __restrict__ Bsc, float* __restrict__ Hout,
-                                                               double* __restrict__ fpart, int64_t nchunks, int vec4,
-                                                               int csplit) {
-  colpass_body<KP, WITH_H, XT, false, WPB>(X, M, N, K, Cq, Bq, Bsc, Hout, fpart, nchunks, vec4, csplit, blockIdx.x);
+                                                               float* Bsc, float* __restrict__ Csc,
+                                                               float* __restrict__ Hout, double* __restrict__ fpart,
+                                                               int64_t nchunks, int vec4, int csplit) {
+  colpass_body<KP, WITH_H, XT, false, WPB>(X, M, N, K, Cq, Bq, Bsc, Csc, Hout, fpart, nchunks, vec4, csplit, blockIdx.x);
 }
 
 // The carried-residual form of the column pass (always forms H).
@@ -869,10 +804,10 @@ template <int KP, typename XT>
 __global__ __launch_bounds__(256, 2) void k_colpass_rw(const XT* X, int64_t M, int64_t N, int K,
                                                        const f32x4* __restrict__ Cq, const _Float16* __restrict__ Bq,
                                                        const _Float16* __restrict__ BqE,
-                                                       const float* __restrict__ Bsc, float* __restrict__ Hout,
+                                                       float* Bsc, float* __restrict__ Csc, float* __restrict__ Hout,
                                                        double* __restrict__ fpart, int64_t nchunks, int vec4,
                                                        int csplit, float* R, int rvec4) {
-  colpass_body<KP, true, XT, true>(X, M, N, K, Cq, Bq, Bsc, Hout, fpart, nchunks, vec4, csplit, blockIdx.x, BqE, R,
+  colpass_body<KP, true, XT, true>(X, M, N, K, Cq, Bq, Bsc, Csc, Hout, fpart, nchunks, vec4, csplit, blockIdx.x, BqE, R,
                                    rvec4);
 }
 
@@ -908,69 +843,69 @@ int column_split(const Shape& s, int64_t max_split) {
 }
 
 template <typename XT, int WPB>
-static void colpass_launch_w(const Shape& s, const XT* X, const f32x4* C, const _Float16* Bq, const float* Bsc,
+static void colpass_launch_w(const Shape& s, const XT* X, const f32x4* C, const _Float16* Bq, float* Bsc, float* Csc,
                              float* Hout, double* fpart, int with_h, hipStream_t st) {
   const unsigned g = (unsigned)colpass_blocks(s);
   if (s.KP == 32) {
     if (with_h)
-      k_colpass<32, true, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Hout, fpart, s.nchunks, s.vec4, s.csplit);
+      k_colpass<32, true, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Csc, Hout, fpart, s.nchunks, s.vec4, s.csplit);
     else
-      k_colpass<32, false, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Hout, fpart, s.nchunks, s.vec4, s.csplit);
+      k_colpass<32, false, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Csc, Hout, fpart, s.nchunks, s.vec4, s.csplit);
   } else {
     if (with_h)
-      k_colpass<64, true, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Hout, fpart, s.nchunks, s.vec4, s.csplit);
+      k_colpass<64, true, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Csc, Hout, fpart, s.nchunks, s.vec4, s.csplit);
     else
-      k_colpass<64, false, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Hout, fpart, s.nchunks, s.vec4, s.csplit);
+      k_colpass<64, false, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Csc, Hout, fpart, s.nchunks, s.vec4, s.csplit);
   }
 }
 
 template <typename XT>
-static void colpass_launch(const Shape& s, const XT* X, const f32x4* C, const _Float16* Bq, const float* Bsc,
+static void colpass_launch(const Shape& s, const XT* X, const f32x4* C, const _Float16* Bq, float* Bsc, float* Csc,
                            float* Hout, double* fpart, int with_h, hipStream_t st) {
   if (s.cwpb == 8)
-    colpass_launch_w<XT, 8>(s, X, C, Bq, Bsc, Hout, fpart, with_h, st);
+    colpass_launch_w<XT, 8>(s, X, C, Bq, Bsc, Csc, Hout, fpart, with_h, st);
   else
-    colpass_launch_w<XT, 4>(s, X, C, Bq, Bsc, Hout, fpart, with_h, st);
+    colpass_launch_w<XT, 4>(s, X, C, Bq, Bsc, Csc, Hout, fpart, with_h, st);
 }
 
 template <typename XT>
 static void colpass_rw_launch(const Shape& s, const XT* X, int vec4, const f32x4* C, const _Float16* Bq,
-                              const _Float16* BqE, const float* Bsc, float* Hout, double* fpart, float* R,
+                              const _Float16* BqE, float* Bsc, float* Csc, float* Hout, double* fpart, float* R,
                               hipStream_t st) {
   const unsigned g = (unsigned)colpass_blocks(s);
   const int rvec4 = (s.M % 4 == 0) && ((reinterpret_cast<uintptr_t>(R) & 15) == 0);
   if (s.KP == 32)
-    k_colpass_rw<32, XT><<<g, 256, 0, st>>>(X, s.M, s.N, s.K, C, Bq, BqE, Bsc, Hout, fpart, s.nchunks, vec4, s.csplit, R, rvec4);
+    k_colpass_rw<32, XT><<<g, 256, 0, st>>>(X, s.M, s.N, s.K, C, Bq, BqE, Bsc, Csc, Hout, fpart, s.nchunks, vec4, s.csplit, R, rvec4);
   else
-    k_colpass_rw<64, XT><<<g, 256, 0, st>>>(X, s.M, s.N, s.K, C, Bq, BqE, Bsc, Hout, fpart, s.nchunks, vec4, s.csplit, R, rvec4);
+    k_colpass_rw<64, XT><<<g, 256, 0, st>>>(X, s.M, s.N, s.K, C, Bq, BqE, Bsc, Csc, Hout, fpart, s.nchunks, vec4, s.csplit, R, rvec4);
 }
 
 hipError_t colpass_carry(const Shape& s, const void* X, int refresh, const void* Cqv, const _Float16* Bq,
-                         const _Float16* BqD, const float* Bsc, float* Hout, double* fpart, float* R,
+                         const _Float16* BqD, float* Bsc, float* Csc, float* Hout, double* fpart, float* R,
                          hipStream_t st) {
   const f32x4* C = static_cast<const f32x4*>(Cqv);
   if (!refresh) {  // E = R - delta B C, in place
     const int v4 = (s.M % 4 == 0) && ((reinterpret_cast<uintptr_t>(R) & 15) == 0);
-    colpass_rw_launch(s, static_cast<const float*>(R), v4, C, Bq, BqD, Bsc, Hout, fpart, R, st);
+    colpass_rw_launch(s, static_cast<const float*>(R), v4, C, Bq, BqD, Bsc, Csc, Hout, fpart, R, st);
   } else if (s.xbf16) {  // E = X - B C from the stored data
-    colpass_rw_launch(s, static_cast<const __bf16*>(X), 0, C, Bq, Bq, Bsc, Hout, fpart, R, st);
+    colpass_rw_launch(s, static_cast<const __bf16*>(X), 0, C, Bq, Bq, Bsc, Csc, Hout, fpart, R, st);
   } else if (s.xtiled) {
-    colpass_rw_launch(s, static_cast<const xtf32*>(X), 0, C, Bq, Bq, Bsc, Hout, fpart, R, st);
+    colpass_rw_launch(s, static_cast<const xtf32*>(X), 0, C, Bq, Bq, Bsc, Csc, Hout, fpart, R, st);
   } else {
-    colpass_rw_launch(s, static_cast<const float*>(X), s.vec4, C, Bq, Bq, Bsc, Hout, fpart, R, st);
+    colpass_rw_launch(s, static_cast<const float*>(X), s.vec4, C, Bq, Bq, Bsc, Csc, Hout, fpart, R, st);
   }
   return hipGetLastError();
 }
 
-hipError_t colpass(const Shape& s, const void* X, const void* Cqv, const _Float16* Bq, const float* Bsc,
+hipError_t colpass(const Shape& s, const void* X, const void* Cqv, const _Float16* Bq, float* Bsc, float* Csc,
                    float* Hout, double* fpart, int with_h, hipStream_t st) {
   const f32x4* C = static_cast<const f32x4*>(Cqv);
   if (s.xbf16)
-    colpass_launch(s, static_cast<const __bf16*>(X), C, Bq, Bsc, Hout, fpart, with_h, st);
+    colpass_launch(s, static_cast<const __bf16*>(X), C, Bq, Bsc, Csc, Hout, fpart, with_h, st);
   else if (s.xtiled)
-    colpass_launch(s, static_cast<const xtf32*>(X), C, Bq, Bsc, Hout, fpart, with_h, st);
+    colpass_launch(s, static_cast<const xtf32*>(X), C, Bq, Bsc, Csc, Hout, fpart, with_h, st);
   else
-    colpass_launch(s, static_cast<const float*>(X), C, Bq, Bsc, Hout, fpart, with_h, st);
+    colpass_launch(s, static_cast<const float*>(X), C, Bq, Bsc, Csc, Hout, fpart, with_h, st);
   return hipGetLastError();
 }
 
@@ -1536,7 +1471,7 @@ hipError_t bupdate(const Shape& s, float* B, const double* W, const double* V, _
     Bq = nullptr;
     Bsc = nullptr;
     BqD = nullptr;
-  } else {
+  } else if (!update) {  // an iteration's column pass clears the maxima of its B update
     k_zero_f32<<<1, 64, 0, st>>>(Bsc, s.KP);
   }
   if (s.K <= 16)
@@ -1547,49 +1482,19 @@ hipError_t bupdate(const Shape& s, float* B, const double* W, const double* V, _
     bupdate_launch<64, 3>(s, B, W, V, Bq, Bsc, Gpart, update, BqD, st);
   else
     bupdate_launch<64, 4>(s, B, W, V, Bq, Bsc, Gpart, update, BqD, st);
-  if (!s.thin) {
-    const unsigned g = (unsigned)bupdate_blocks(s);
-    if (s.KP == 32)
-      k_packh<32><<<g, 256, 0, st>>>(B, s.M, s.K, s.nchunks, Bq, Bsc);
-    else
-      k_packh<64><<<g, 256, 0, st>>>(B, s.M, s.K, s.nchunks, Bq, Bsc);
-  }
   return hipGetLastError();
 }
 
-// E order of 256 columns of C (block bid), and their contribution to the row maxima.
+// E order of 256 columns of C (block bid).
 template <int KP>
-__device__ __forceinline__ void packc_body(const float* __restrict__ C, f32x4* __restrict__ Cq,
-                                           float* __restrict__ Csc, int64_t N, int K, int64_t bid) {
+__global__ __launch_bounds__(256) void k_packc(const float* __restrict__ C, f32x4* __restrict__ Cq, int64_t N, int K) {
   extern __shared__ float Ct[];  // 256 * K floats
   __shared__ int cs[256];
-  const int64_t j0 = bid * 256;
+  const int64_t j0 = (int64_t)blockIdx.x * 256;
   const int nv = (int)((N - j0) < 256 ? (N - j0) : 256);
-  const int ne = nv * K;
-  block_copy(Ct, C + j0 * K, ne);
+  block_copy(Ct, C + j0 * K, nv * K);
   __syncthreads();
-  pack_block<KP>(Cq, Csc, j0, nv, Ct, K, (N + 31) / 32, cs);
-}
-
-template <int KP>
-__global__ __launch_bounds__(256) void k_packc(const float* __restrict__ C, f32x4* __restrict__ Cq,
-                                               float* __restrict__ Csc, int64_t N, int K) {
-  packc_body<KP>(C, Cq, Csc, N, K, blockIdx.x);
-}
-
-template <int KP>
-__global__ __launch_bounds__(256) void k_packw(const float* __restrict__ C, f32x4* __restrict__ Cq,
-                                               float* __restrict__ Csc, int64_t N, int K) {
-  packw_body<KP>(C, Cq, Csc, N, K, blockIdx.x);
-}
-
-static hipError_t packw(const Shape& s, const float* C, f32x4* Cq, float* Csc, hipStream_t st) {
-  const unsigned g = (unsigned)((s.N + 255) / 256);
-  if (s.KP == 32)
-    k_packw<32><<<g, 256, 0, st>>>(C, Cq, Csc, s.N, s.K);
-  else
-    k_packw<64><<<g, 256, 0, st>>>(C, Cq, Csc, s.N, s.K);
-  return hipGetLastError();
+  pack_block<KP>(Cq, j0, nv, Ct, K, (N + 31) / 32, cs);
 }
 
 template <int KP, int NT, int U>
@@ -1615,7 +1520,6 @@ hipError_t sweep(const Shape& s, const float* Hin, float* C, void* Cq, float* Cs
                  hipStream_t st, void* CqD) {
   f32x4* q = static_cast<f32x4*>(Cq);
   f32x4* qd = static_cast<f32x4*>(CqD);
-  k_zero_f32<<<1, 64, 0, st>>>(Csc, s.KP);
   if (s.K <= 16)
     sweep_launch<32, 1>(s, Hin, C, q, Csc, G, qd, st);
   else if (s.K <= 32)
@@ -1624,115 +1528,153 @@ hipError_t sweep(const Shape& s, const float* Hin, float* C, void* Cq, float* Cs
     sweep_launch<64, 3>(s, Hin, C, q, Csc, G, qd, st);
   else
     sweep_launch<64, 4>(s, Hin, C, q, Csc, G, qd, st);
-  return packw(s, C, q, Csc, st);
+  return hipGetLastError();
 }
 
-hipError_t packc(const Shape& s, const float* C, void* Cq, float* Csc, hipStream_t st) {
+hipError_t packc(const Shape& s, const float* C, void* Cq, hipStream_t st) {
   const unsigned g = (unsigned)((s.N + 255) / 256);
   f32x4* q = static_cast<f32x4*>(Cq);
-  k_zero_f32<<<1, 64, 0, st>>>(Csc, s.KP);
   if (s.KP == 32)
-    k_packc<32><<<g, 256, 256 * s.K * sizeof(float), st>>>(C, q, Csc, s.N, s.K);
+    k_packc<32><<<g, 256, 256 * s.K * sizeof(float), st>>>(C, q, s.N, s.K);
   else
-    k_packc<64><<<g, 256, 256 * s.K * sizeof(float), st>>>(C, q, Csc, s.N, s.K);
-  return packw(s, C, q, Csc, st);
+    k_packc<64><<<g, 256, 256 * s.K * sizeof(float), st>>>(C, q, s.N, s.K);
+  return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ V = tril(C C^T)
-// V = C C^T from the packed W-order units of C: a W unit holds, for one coordinate kk,
-// eight columns of a tile, which is both the A fragment (rows kk, reduction over columns)
-// and the B fragment (reduction over columns, columns kk') of the product.  Each block
-// takes a contiguous run of tiles; wave w takes every fourth tile of the run and forms the
-// lower 32x32 blocks (b1 >= b2) of the tile's contribution with scaled fp16 MFMAs (float32
-// within the tile, in units of 2^(w_a + w_b)), adding them to float64 accumulators.  The
-// four waves' partials are then unscaled (exactly), added in wave order and written as
-// tril pairs.
+// ------------------------------------------------------------------ W order of C and V = tril(C C^T)
+// Each block takes a contiguous run of 32-column tiles, wave w every eighth of them.  A wave
+// reads a tile of C (each load coalesced across the lanes, which take consecutive
+// coordinates; the next tile's loads are in flight while one is worked on), scales each row
+// by the power of two from its maximum in Csc[0, KP), splits it and stores the W-order units;
+// block 0 stores the inverse scales into Csc[KP, 2 KP).  The units in its registers are also
+// the MFMA operands of the tile's contribution to V: for one coordinate kk, eight columns,
+// which is both the A fragment (rows kk, reduction over columns) and the B fragment
+// (reduction over columns, columns kk').  The lower 32 x 32 blocks (b1 >= b2) are formed in
+// float32 within the tile, in units of 2^(w_a + w_b), and added to float64 accumulators; the
+// waves' sums are unscaled (exactly), added in a fixed order and written as tril pairs.
+// (As two kernels, the second reading the units back: 89 and 81 us at N = 10^6, K = 50; one:
+// 89 us, and one launch less.)
 constexpr int kVBlocks = 256;
+constexpr int kVWaves = 8;
 
 template <int KP>
-__device__ __forceinline__ void vgram_body(const f32x4* __restrict__ Cq, const float* __restrict__ Csc,
-                                           int64_t ntiles, double* __restrict__ Vpart, int64_t bid, int64_t nblk) {
+struct PackvLds {
+  double v[kVWaves / 2][KP * (KP + 1) / 2];
+  float inv[KP];  // 2^-w_kk
+};
+
+// AHEAD: the next tile's loads are issued before a tile is worked on (not in the grouped
+// kernel, where the registers would spill).
+template <int KP, bool AHEAD>
+__device__ __forceinline__ void packv_body(PackvLds<KP>& S, const float* __restrict__ C, f32x4* __restrict__ Cq,
+                                           float* __restrict__ Csc, int64_t N, int K, double* __restrict__ Vpart,
+                                           int64_t bid, int64_t nblk) {
   constexpr int NB = KP / 32;
   constexpr int UE = CqL<KP>::E;  // E-order units and scales of a packed C tile
   constexpr int UT = CqL<KP>::T;
   constexpr int NBL = NB * (NB + 1) / 2;  // lower blocks (b1 >= b2)
-  constexpr int NP = KP * (KP + 1) / 2;
-  __shared__ double Vs[4][NP];
   // the wave index is uniform: from a scalar register, so that wave-based addresses stay scalar
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, half = l >> 5,
             lc = l & 31;
-  const int64_t per = (ntiles + nblk - 1) / nblk;
+  const int NP = g_pairs(K);
+  const int64_t ntiles = (N + 31) / 32, per = (ntiles + nblk - 1) / nblk;
   const int64_t t0 = bid * per;
   const int64_t t1 = (t0 + per < ntiles) ? t0 + per : ntiles;
+  float ws[NB];  // 2^w_kk of this lane's coordinates
+#pragma unroll
+  for (int b = 0; b < NB; ++b) ws[b] = pow2f(32 * b + lc < K ? scale_exp(Csc[32 * b + lc]) : 0);
+  if (bid == 0 && tid < KP) Csc[KP + tid] = pow2f(-(tid < K ? scale_exp(Csc[tid]) : 0));
+  float x[2][NB][8];  // [q][b][t]: C[32 b + lc][column row32(8 q + t, half) of the tile]
+  auto load = [&](int64_t T) {
+    const float* const ct = C + T * 32 * K;
+    const int nv = N - T * 32 < 32 ? (int)(N - T * 32) : 32;
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+          x[q][b][t] = ct[(uint32_t)(min(row32(8 * q + t, half), nv - 1) * K + min(32 * b + lc, K - 1))];
+  };
   double acc[NBL][16];
 #pragma unroll
   for (int k = 0; k < NBL; ++k)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[k][i] = 0.0;
-  for (int64_t T = t0 + wave; T < t1; T += 4) {
-    const f32x4* wu = Cq + T * UT + UE + l;
-    f32x16 v[NBL];
+  if (AHEAD && t0 + wave < t1) load(t0 + wave);
+#pragma clang loop unroll(disable)
+  for (int64_t T = t0 + wave; T < t1; T += kVWaves) {
+    if (!AHEAD) load(T);
+    const int nv = N - T * 32 < 32 ? (int)(N - T * 32) : 32;
+    f32x4* const wu = Cq + T * UT + UE + l;
+    f16x8 w[2][NB][2];
 #pragma unroll
-    for (int k = 0; k < NBL; ++k)
+    for (int q = 0; q < 2; ++q)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) v[k][i] = 0.0f;
+      for (int b = 0; b < NB; ++b) {
+        float v[8];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      f16x8 w[NB][2];
+        for (int t = 0; t < 8; ++t)
+          v[t] = (32 * b + lc < K && row32(8 * q + t, half) < nv) ? x[q][b][t] * ws[b] : 0.0f;
+        const Split2 sp = split2(v);
+#pragma unroll
+        for (int p = 0; p < 2; ++p) w[q][b][p] = sp.p[p];
+      }
+    if (AHEAD && T + kVWaves < t1) load(T + kVWaves);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
 #pragma unroll
       for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int p = 0; p < 2; ++p) w[b][p] = as_f16x8(wu[((b * 2 + q) * 2 + p) * 64]);
-      int k = 0;
-#pragma unroll
-      for (int b1 = 0; b1 < NB; ++b1)
-#pragma unroll
-        for (int b2 = 0; b2 <= b1; ++b2, ++k) v[k] = mfma_x3(w[b1], w[b2], v[k]);
-    }
-#pragma unroll
-    for (int k = 0; k < NBL; ++k)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[k][i] += (double)v[k][i];
-  }
-  for (int q = l; q < NP; q += 64) Vs[wave][q] = 0.0;
-  __syncthreads();
-  {
-    const float* inv = Csc + KP;  // 2^-w_kk
+        for (int p = 0; p < 2; ++p) wu[((b * 2 + q) * 2 + p) * 64] = f16_as_f32x4(w[q][b][p]);
     int k = 0;
 #pragma unroll
     for (int b1 = 0; b1 < NB; ++b1)
 #pragma unroll
-      for (int b2 = 0; b2 <= b1; ++b2, ++k)
+      for (int b2 = 0; b2 <= b1; ++b2, ++k) {
+        f32x16 v;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int a = 32 * b1 + row32(i, half), b = 32 * b2 + lc;
-          if (a >= b) Vs[wave][a * (a + 1) / 2 + b] = acc[k][i] * (double)inv[a] * (double)inv[b];
-        }
+        for (int i = 0; i < 16; ++i) v[i] = 0.0f;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) v = mfma_x3(w[q][b1], w[q][b2], v);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[k][i] += (double)v[i];
+      }
   }
+  // unscaled sums: waves 4..7 through LDS, then waves 0..3 add theirs, then the four in order
+  if (tid < KP) S.inv[tid] = pow2f(-(tid < K ? scale_exp(Csc[tid]) : 0));
   __syncthreads();
-  for (int q = tid; q < NP; q += 256)
-    Vpart[bid * NP + q] = ((Vs[0][q] + Vs[1][q]) + Vs[2][q]) + Vs[3][q];
+#pragma clang loop unroll(disable)
+  for (int turn = 0; turn < 2; ++turn) {
+    if ((wave >= kVWaves / 2) == (turn == 0)) {
+      double* const vs = S.v[wave & (kVWaves / 2 - 1)];
+      int k = 0;
+#pragma unroll
+      for (int b1 = 0; b1 < NB; ++b1)
+#pragma unroll
+        for (int b2 = 0; b2 <= b1; ++b2, ++k)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const int a = 32 * b1 + row32(i, half), b = 32 * b2 + lc;
+            const double v = acc[k][i] * (double)S.inv[a] * (double)S.inv[b];
+            if (a >= b) vs[a * (a + 1) / 2 + b] = turn ? v + vs[a * (a + 1) / 2 + b] : v;
+          }
+    }
+    __syncthreads();
+  }
+  for (int q = tid; q < NP; q += 64 * kVWaves) {
+    double v = S.v[0][q];
+#pragma unroll
+    for (int w = 1; w < kVWaves / 2; ++w) v += S.v[w][q];
+    Vpart[bid * NP + q] = v;
+  }
 }
 
-template <int KP>
-__global__ __launch_bounds__(256) void k_vgram(const f32x4* __restrict__ Cq, const float* __restrict__ Csc,
-                                               int64_t ntiles, double* __restrict__ Vpart) {
-  vgram_body<KP>(Cq, Csc, ntiles, Vpart, blockIdx.x, gridDim.x);
-}
-
+// A tile per wave at least (blocks of one tile each, as for N <= 8192 before, spent most of a
+// batch's launch on their sums: 127 us for 9 jobs at K > 32, 61 us as whole blocks).
 int64_t vgram_blocks(const Shape& s) {
-  const int64_t t = n_tiles32(s);
+  const int64_t t = (n_tiles32(s) + kVWaves - 1) / kVWaves;
   return t < kVBlocks ? t : kVBlocks;
-}
-
-hipError_t vgram(const Shape& s, const void* Cq, const float* Csc, double* Vpart, hipStream_t st) {
-  const unsigned g = (unsigned)vgram_blocks(s);
-  const f32x4* q = static_cast<const f32x4*>(Cq);
-  if (s.KP == 32)
-    k_vgram<32><<<g, 256, 0, st>>>(q, Csc, n_tiles32(s), Vpart);
-  else
-    k_vgram<64><<<g, 256, 0, st>>>(q, Csc, n_tiles32(s), Vpart);
-  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ row pass
@@ -2053,17 +1995,6 @@ __device__ __forceinline__ void reduce_w_body(const float* __restrict__ Wpart, i
   W[i] = s;
 }
 
-__global__ __launch_bounds__(256) void k_reduce_w(const float* __restrict__ Wpart, int R, int64_t n,
-                                                  double* __restrict__ W) {
-  reduce_w_body(Wpart, R, n, W, blockIdx.x);
-}
-
-hipError_t reduce_w(const Shape& s, const float* Wpart, int R, double* W, hipStream_t st) {
-  const int64_t n = (int64_t)s.K * s.Mpad;
-  k_reduce_w<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(Wpart, R, n, W);
-  return hipGetLastError();
-}
-
 // full[a][b] = full[b][a] = sum_p part[p][pair(a,b)] over the NP pairs of the partials (a < KP;
 // entries of full past them keep their value), in a fixed order.  A block of 256
 // threads takes kSymPairs consecutive pairs with 32 threads each: thread (t, qi) =
@@ -2105,34 +2036,25 @@ __device__ __forceinline__ void reduce_sym_body(const double* __restrict__ part,
   }
 }
 
-__global__ __launch_bounds__(256) void k_reduce_sym(const double* __restrict__ part, int64_t P, int NP, int KP,
-                                                    double* __restrict__ full) {
-  reduce_sym_body(part, P, NP, KP, full, blockIdx.x);
-}
-
-hipError_t reduce_sym(const double* part, int64_t P, int NP, int KP, double* full, hipStream_t st) {
-  k_reduce_sym<<<(unsigned)((NP + kSymPairs - 1) / kSymPairs), 256, 0, st>>>(part, P, NP, KP, full);
-  return hipGetLastError();
-}
-
-// scale * sum_p part[p]: each thread sums a strided subset in order, then a fixed tree over
-// the block; the result is returned to every thread.
+// scale * sum_p part[p] by a block of TB threads: each thread sums a strided subset in order,
+// then a fixed tree over the block; the result is returned to every thread.
+template <int TB>
 __device__ __forceinline__ double reduce_f_body(const double* __restrict__ part, int64_t P, double scale) {
-  __shared__ double s[256];
+  __shared__ double s[TB];
   constexpr int G = 8;
   double a = 0.0;
   int64_t p = threadIdx.x;
-  for (; p + (G - 1) * 256 < P; p += G * 256) {
+  for (; p + (G - 1) * TB < P; p += G * TB) {
     double v[G];
 #pragma unroll
-    for (int u = 0; u < G; ++u) v[u] = part[p + u * 256];
+    for (int u = 0; u < G; ++u) v[u] = part[p + u * TB];
 #pragma unroll
     for (int u = 0; u < G; ++u) a += v[u];
   }
-  for (; p < P; p += 256) a += part[p];
+  for (; p < P; p += TB) a += part[p];
   s[threadIdx.x] = a;
   __syncthreads();
-  for (int w = 128; w >= 1; w >>= 1) {
+  for (int w = TB / 2; w >= 1; w >>= 1) {
     if ((int)threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
     __syncthreads();
   }
@@ -2143,7 +2065,7 @@ __device__ __forceinline__ double reduce_f_body(const double* __restrict__ part,
 
 __global__ __launch_bounds__(256) void k_reduce_f(const double* __restrict__ part, int64_t P, double* out,
                                                   double scale) {
-  const double r = reduce_f_body(part, P, scale);
+  const double r = reduce_f_body<256>(part, P, scale);
   if (threadIdx.x == 0) *out = r;
 }
 
@@ -2154,21 +2076,95 @@ hipError_t reduce_f(const double* part, int64_t P, double* out, double scale, hi
 
 // The objective of an iteration into the history ring at the device iteration counter,
 // which then advances: no host value is baked into the launch, so a captured iteration
-// can be replayed.
-__global__ __launch_bounds__(256) void k_reduce_f_hist(const double* __restrict__ part, int64_t P,
-                                                       double* __restrict__ fhist, int64_t cap,
-                                                       int64_t* __restrict__ tdev, double scale) {
-  const double r = reduce_f_body(part, P, scale);
+// can be replayed.  fcur (may be null) receives the objective too.
+template <int TB>
+__device__ __forceinline__ void f_hist_body(const double* __restrict__ part, int64_t P, double* __restrict__ fhist,
+                                            int64_t cap, int64_t* __restrict__ tdev, double* __restrict__ fcur) {
+  const double r = reduce_f_body<TB>(part, P, 0.5);
   if (threadIdx.x == 0) {
     const int64_t t = *tdev;
     fhist[t % cap] = r;
     *tdev = t + 1;
+    if (fcur) *fcur = r;
   }
 }
 
-hipError_t reduce_f_hist(const double* part, int64_t P, double* fhist, int64_t cap, int64_t* tdev, double scale,
-                         hipStream_t st) {
-  k_reduce_f_hist<<<1, 256, 0, st>>>(part, P, fhist, cap, tdev, scale);
+// Launches of several small stages that wait for the same one: the W order of C with V's
+// partials and the objective (last block); the sums of the W and V partials; the sum of G's
+// partials with the H order of B.  (As kernels of their own these and two clears of the maxima
+// made thirteen launches per iteration, 2 to 4.6 us each beside the work; now seven.)
+template <int KP>
+__global__ __launch_bounds__(64 * kVWaves, 2) void k_packv(const float* __restrict__ C, f32x4* __restrict__ Cq,
+                                                           float* __restrict__ Csc, int64_t N, int K,
+                                                           double* __restrict__ Vpart, int nblk,
+                                                           const double* __restrict__ fpart, int64_t P,
+                                                           double* __restrict__ fhist, int64_t cap,
+                                                           int64_t* __restrict__ tdev) {
+  __shared__ PackvLds<KP> S;
+  if ((int)blockIdx.x < nblk)
+    packv_body<KP, true>(S, C, Cq, Csc, N, K, Vpart, blockIdx.x, nblk);
+  else
+    f_hist_body<64 * kVWaves>(fpart, P, fhist, cap, tdev, nullptr);
+}
+
+hipError_t packv(const Shape& s, const float* C, void* Cq, float* Csc, double* Vpart, const double* fpart,
+                 double* fhist, int64_t cap, int64_t* tdev, hipStream_t st) {
+  const int g = (int)vgram_blocks(s);
+  f32x4* q = static_cast<f32x4*>(Cq);
+  if (s.KP == 32)
+    k_packv<32><<<g + 1, 64 * kVWaves, 0, st>>>(C, q, Csc, s.N, s.K, Vpart, g, fpart, colpass_blocks(s), fhist, cap, tdev);
+  else
+    k_packv<64><<<g + 1, 64 * kVWaves, 0, st>>>(C, q, Csc, s.N, s.K, Vpart, g, fpart, colpass_blocks(s), fhist, cap, tdev);
+  return hipGetLastError();
+}
+
+__global__ __launch_bounds__(256) void k_reduce_wv(const float* __restrict__ Wpart, int R, int64_t n,
+                                                   double* __restrict__ W, const double* __restrict__ Vpart,
+                                                   int64_t P, int NP, int KP, double* __restrict__ V) {
+  const int64_t nw = (n + 255) / 256;
+  if (blockIdx.x < nw)
+    reduce_w_body(Wpart, R, n, W, blockIdx.x);
+  else
+    reduce_sym_body(Vpart, P, NP, KP, V, blockIdx.x - nw);
+}
+
+hipError_t reduce_wv(const Shape& s, const float* Wpart, int R, double* W, const double* Vpart, double* V,
+                     hipStream_t st) {
+  const int64_t n = (int64_t)s.K * s.Mpad;
+  const int NP = g_pairs(s.K);
+  const int64_t g = (n + 255) / 256 + (NP + kSymPairs - 1) / kSymPairs;
+  k_reduce_wv<<<(unsigned)g, 256, 0, st>>>(Wpart, R, n, W, Vpart, vgram_blocks(s), NP, s.KP, V);
+  return hipGetLastError();
+}
+
+template <int KP>
+__device__ __forceinline__ void finish_b_body(const double* __restrict__ Gpart, int64_t P, double* __restrict__ G,
+                                              const float* __restrict__ B, int64_t M, int K, int64_t nchunks,
+                                              _Float16* __restrict__ Bq, float* __restrict__ Bsc, int64_t bid) {
+  const int np = g_pairs(K);
+  const int64_t ng = (np + kSymPairs - 1) / kSymPairs;
+  if (bid < ng)
+    reduce_sym_body(Gpart, P, np, KP, G, bid);
+  else
+    packh_body<KP>(B, M, K, nchunks, Bq, Bsc, bid - ng);
+}
+
+template <int KP>
+__global__ __launch_bounds__(256) void k_finish_b(const double* __restrict__ Gpart, int64_t P, double* __restrict__ G,
+                                                  const float* __restrict__ B, int64_t M, int K, int64_t nchunks,
+                                                  _Float16* __restrict__ Bq, float* __restrict__ Bsc) {
+  finish_b_body<KP>(Gpart, P, G, B, M, K, nchunks, Bq, Bsc, blockIdx.x);
+}
+
+hipError_t finish_b(const Shape& s, const double* Gpart, double* G, const float* B, _Float16* Bq, float* Bsc,
+                    hipStream_t st) {
+  const int64_t ng = (g_pairs(s.K) + kSymPairs - 1) / kSymPairs;
+  const int64_t P = bupdate_blocks(s);
+  const unsigned g = (unsigned)(ng + (s.thin ? 0 : P));  // the thin path packs nothing
+  if (s.KP == 32)
+    k_finish_b<32><<<g, 256, 0, st>>>(Gpart, P, G, B, s.M, s.K, s.nchunks, Bq, Bsc);
+  else
+    k_finish_b<64><<<g, 256, 0, st>>>(Gpart, P, G, B, s.M, s.K, s.nchunks, Bq, Bsc);
   return hipGetLastError();
 }
 
@@ -2220,21 +2216,7 @@ template <int KP, typename XT, int WPB>
 __global__ __launch_bounds__(64 * WPB, 8 / WPB) void kg_colpass(const GTable* __restrict__ g) {
   DID_GROUP_LOOP(GS_COL)
   colpass_body<KP, true, XT, false, WPB>(static_cast<const XT*>(d.X), d.M, d.N, d.K, static_cast<const f32x4*>(d.Cq),
-                                         d.Bq, d.Bsc, d.H, d.fpart, d.nchunks, d.vec4, d.csplit, bid);
-  DID_GROUP_END
-}
-
-__global__ __launch_bounds__(256) void kg_reduce_f(const GTable* __restrict__ g) {
-  DID_GROUP_LOOP(GS_REDF)
-  (void)bid;
-  // the row maxima of C start from zero for the sweep that follows
-  if ((int)threadIdx.x < d.K) d.Csc[threadIdx.x] = 0.0f;
-  const double r = reduce_f_body(d.fpart, d.colblocks, 0.5);
-  if (threadIdx.x == 0) {
-    const int64_t t = *d.tdev;
-    d.fhist[t % d.hist_cap] = r;
-    *d.fcur = r;
-  }
+                                         d.Bq, d.Bsc, d.Csc, d.H, d.fpart, d.nchunks, d.vec4, d.csplit, bid);
   DID_GROUP_END
 }
 
@@ -2267,23 +2249,14 @@ __global__ __launch_bounds__(256, 2) void kg_sweep(const GTable* __restrict__ g)
 }
 
 template <int KP>
-__global__ __launch_bounds__(256) void kg_packw(const GTable* __restrict__ g) {
-  DID_GROUP_LOOP(GS_PACKW)
-  packw_body<KP>(d.C, static_cast<f32x4*>(d.Cq), d.Csc, d.N, d.K, bid);
-  DID_GROUP_END
-}
-
-template <int KP>
-__global__ __launch_bounds__(256) void kg_vgram(const GTable* __restrict__ g) {
-  DID_GROUP_LOOP(GS_VGRAM)
-  vgram_body<KP>(static_cast<const f32x4*>(d.Cq), d.Csc, (d.N + 31) / 32, d.Vpart, bid, d.vblocks);
-  DID_GROUP_END
-}
-
-template <int KP>
-__global__ __launch_bounds__(256) void kg_reduce_v(const GTable* __restrict__ g) {
-  DID_GROUP_LOOP(GS_REDV)
-  reduce_sym_body(d.Vpart, d.vblocks, KP * (KP + 1) / 2, KP, d.V, bid);
+__global__ __launch_bounds__(64 * kVWaves, 2) void kg_packv(const GTable* __restrict__ g) {
+  __shared__ PackvLds<KP> S;
+  DID_GROUP_LOOP(GS_PACKV)
+  if (bid < d.vblocks)
+    packv_body<KP, false>(S, as_global(d.C), as_global(static_cast<f32x4*>(d.Cq)), as_global(d.Csc), d.N, d.K,
+                          d.Vpart, bid, d.vblocks);
+  else
+    f_hist_body<64 * kVWaves>(d.fpart, d.colblocks, d.fhist, d.hist_cap, d.tdev, d.fcur);
   DID_GROUP_END
 }
 
@@ -2297,11 +2270,13 @@ __global__ __launch_bounds__(256, 2) void kg_rowpass(const GTable* __restrict__ 
 }
 
 template <int KP>
-__global__ __launch_bounds__(256) void kg_reduce_w(const GTable* __restrict__ g) {
-  DID_GROUP_LOOP(GS_REDW)
-  // the column maxima of B start from zero for the B update that follows
-  if (bid == 0 && threadIdx.x < KP) d.Bsc[threadIdx.x] = 0.0f;
-  reduce_w_body(d.Wpart, d.R, (int64_t)d.K * d.Mpad, d.W, bid);
+__global__ __launch_bounds__(256) void kg_reduce_wv(const GTable* __restrict__ g) {
+  DID_GROUP_LOOP(GS_REDWV)
+  const int64_t n = (int64_t)d.K * d.Mpad, nw = (n + 255) / 256;
+  if (bid < nw)
+    reduce_w_body(d.Wpart, d.R, n, d.W, bid);
+  else
+    reduce_sym_body(d.Vpart, d.vblocks, g_pairs(d.K), KP, d.V, bid - nw);
   DID_GROUP_END
 }
 
@@ -2325,22 +2300,9 @@ __global__ __launch_bounds__(256, 2) void kg_bupdate(const GTable* __restrict__ 
 }
 
 template <int KP>
-__global__ __launch_bounds__(256) void kg_reduce_g(const GTable* __restrict__ g) {
-  DID_GROUP_LOOP(GS_REDG)
-  // the G reduction, then the H-order packing of B: both need only the B update
-  const int np = g_pairs(d.K);
-  const int64_t ng = (np + kSymPairs - 1) / kSymPairs;
-  if (bid < ng)
-    reduce_sym_body(d.Gpart, d.bupblocks, np, KP, d.G, bid);
-  else
-    packh_body<KP>(d.B, d.M, d.K, d.nchunks, d.Bq, d.Bsc, bid - ng);
-  DID_GROUP_END
-}
-
-__global__ __launch_bounds__(64) void kg_advance(const GTable* __restrict__ g) {
-  DID_GROUP_LOOP(GS_ADV)
-  (void)bid;
-  if (threadIdx.x == 0) *d.tdev = *d.tdev + 1;
+__global__ __launch_bounds__(256) void kg_finish_b(const GTable* __restrict__ g) {
+  DID_GROUP_LOOP(GS_FIN)
+  finish_b_body<KP>(d.Gpart, d.bupblocks, d.G, d.B, d.M, d.K, d.nchunks, d.Bq, d.Bsc, bid);
   DID_GROUP_END
 }
 
@@ -2348,19 +2310,15 @@ __global__ __launch_bounds__(64) void kg_advance(const GTable* __restrict__ g) {
 #undef DID_GROUP_END
 
 void ginst_items(const Shape& s, int R, int64_t items[GS_N]) {
-  const int64_t np = n_pairs(s.KP);
+  const int64_t ng = (g_pairs(s.K) + kSymPairs - 1) / kSymPairs;
   const int64_t nsg = (s.nchunks + 3) / 4;
   items[GS_COL] = colpass_blocks(s);
-  items[GS_REDF] = 1;
   items[GS_SWEEP] = sweep_blocks(s.N);
-  items[GS_PACKW] = (s.N + 255) / 256;
-  items[GS_VGRAM] = vgram_blocks(s);
-  items[GS_REDV] = (np + kSymPairs - 1) / kSymPairs;
+  items[GS_PACKV] = vgram_blocks(s) + 1;
   items[GS_ROW] = (nsg * R + 7) / 8 * 8;
-  items[GS_REDW] = ((int64_t)s.K * s.Mpad + 255) / 256;
+  items[GS_REDWV] = ((int64_t)s.K * s.Mpad + 255) / 256 + ng;
   items[GS_BUP] = bupdate_blocks(s);
-  items[GS_REDG] = (g_pairs(s.K) + kSymPairs - 1) / kSymPairs + bupdate_blocks(s);
-  items[GS_ADV] = 1;
+  items[GS_FIN] = ng + bupdate_blocks(s);
 }
 
 template <int KP, typename XT, int WPB>
@@ -2377,16 +2335,12 @@ static hipError_t group_grids_t(int64_t grids[GS_N]) {
     return r;
   };
   if ((e = occ((const void*)kg_colpass<KP, XT, WPB>, 64 * WPB, 0, &grids[GS_COL])) != hipSuccess) return e;
-  if ((e = occ((const void*)kg_reduce_f, 256, 0, &grids[GS_REDF])) != hipSuccess) return e;
   if ((e = occ((const void*)kg_sweep<KP>, 256, sweep_dyn_lds(KP, 4, false), &grids[GS_SWEEP])) != hipSuccess) return e;
-  if ((e = occ((const void*)kg_packw<KP>, 256, 0, &grids[GS_PACKW])) != hipSuccess) return e;
-  if ((e = occ((const void*)kg_vgram<KP>, 256, 0, &grids[GS_VGRAM])) != hipSuccess) return e;
-  if ((e = occ((const void*)kg_reduce_v<KP>, 256, 0, &grids[GS_REDV])) != hipSuccess) return e;
+  if ((e = occ((const void*)kg_packv<KP>, 64 * kVWaves, 0, &grids[GS_PACKV])) != hipSuccess) return e;
   if ((e = occ((const void*)kg_rowpass<KP, XT>, 256, 0, &grids[GS_ROW])) != hipSuccess) return e;
-  if ((e = occ((const void*)kg_reduce_w<KP>, 256, 0, &grids[GS_REDW])) != hipSuccess) return e;
+  if ((e = occ((const void*)kg_reduce_wv<KP>, 256, 0, &grids[GS_REDWV])) != hipSuccess) return e;
   if ((e = occ((const void*)kg_bupdate<KP>, 256, bup_dyn_lds(KP, false), &grids[GS_BUP])) != hipSuccess) return e;
-  if ((e = occ((const void*)kg_reduce_g<KP>, 256, 0, &grids[GS_REDG])) != hipSuccess) return e;
-  if ((e = occ((const void*)kg_advance, 64, 0, &grids[GS_ADV])) != hipSuccess) return e;
+  if ((e = occ((const void*)kg_finish_b<KP>, 256, 0, &grids[GS_FIN])) != hipSuccess) return e;
   return hipSuccess;
 }
 
@@ -2409,16 +2363,12 @@ hipError_t group_grids(int KP, int xkind, int cwpb, int64_t grids[GS_N]) {
 template <int KP, typename XT, int WPB>
 static void group_iteration_t(const GTable* t, const int64_t* gr, hipStream_t st) {
   kg_colpass<KP, XT, WPB><<<(unsigned)gr[GS_COL], 64 * WPB, 0, st>>>(t);
-  kg_reduce_f<<<(unsigned)gr[GS_REDF], 256, 0, st>>>(t);
   kg_sweep<KP><<<(unsigned)gr[GS_SWEEP], 256, sweep_dyn_lds(KP, 4, false), st>>>(t);
-  kg_packw<KP><<<(unsigned)gr[GS_PACKW], 256, 0, st>>>(t);
-  kg_vgram<KP><<<(unsigned)gr[GS_VGRAM], 256, 0, st>>>(t);
-  kg_reduce_v<KP><<<(unsigned)gr[GS_REDV], 256, 0, st>>>(t);
+  kg_packv<KP><<<(unsigned)gr[GS_PACKV], 64 * kVWaves, 0, st>>>(t);
   kg_rowpass<KP, XT><<<(unsigned)gr[GS_ROW], 256, 0, st>>>(t);
-  kg_reduce_w<KP><<<(unsigned)gr[GS_REDW], 256, 0, st>>>(t);
+  kg_reduce_wv<KP><<<(unsigned)gr[GS_REDWV], 256, 0, st>>>(t);
   kg_bupdate<KP><<<(unsigned)gr[GS_BUP], 256, bup_dyn_lds(KP, false), st>>>(t);
-  kg_reduce_g<KP><<<(unsigned)gr[GS_REDG], 256, 0, st>>>(t);
-  kg_advance<<<(unsigned)gr[GS_ADV], 64, 0, st>>>(t);
+  kg_finish_b<KP><<<(unsigned)gr[GS_FIN], 256, 0, st>>>(t);
 }
 
 template <int KP, typename XT>
