@@ -524,7 +524,7 @@ int objective_pass(did_ctx* h) {
   if (h->s.thin) {
     if ((e = didk::thin_pass(h->s, static_cast<const float*>(h->X), h->B, h->G, h->C, h->tpart, 1, h->st)) !=
             hipSuccess ||
-        (e = didk::thin_reduce(h->s, h->tpart, h->W, h->V, h->fobj, 0.5, 0, h->st)) != hipSuccess)
+        (e = didk::thin_finish(h->s, h->tpart, h->B, h->G, h->fobj, 0, h->st)) != hipSuccess)
       return dev_fail(h, e, "objective pass");
     return DID_OK;
   }
@@ -828,10 +828,10 @@ int did_init_from_factors(const void* X, int64_t M, int64_t N, int32_t K, const 
   return init_common(X, M, N, K, 0, B, C, opts, out);
 }
 
-// Thin-matrix iterations.  DID: one fused column pass (sweep, W/V/f partials), their
-// fixed-order reduction, the B update and G.  DBCD: the C half, then per column of B one
-// pass over X and one reduction, then G.  Stages are recorded at the same positions as the
-// main path's (column_pass, reduce_f/_v/_w, b_update, reduce_g); unused ones are empty.
+// Thin-matrix iterations.  DID: one fused column pass (sweep, W/V/f partials), then one block
+// sums the partials, updates B and forms G.  DBCD: the C half, then per column of B one pass
+// over X and one reduction, then G.  Stages are recorded at the same positions as the main
+// path's (column_pass, reduce_f, and for DBCD b_update); unused ones are empty.
 static int iterate_thin(did_ctx* h, int32_t n) {
   const Shape& s = h->s;
   hipError_t e;
@@ -851,25 +851,20 @@ static int iterate_thin(did_ctx* h, int32_t n) {
     if ((e = didk::thin_pass(s, X, h->B, h->G, h->C, h->tpart, mode, h->st)) != hipSuccess)
       return dev_fail(h, e, "thin column pass");
     if ((e = mark(1)) != hipSuccess) return dev_fail(h, e, "profile record");
-    if ((e = didk::thin_reduce(s, h->tpart, h->W, h->V, h->fhist + (h->t % h->hist_cap), 0.5, mode == 0, h->st)) !=
+    // the partials' sums and f; for DID also the B update and G
+    if ((e = didk::thin_finish(s, h->tpart, h->B, h->G, h->fhist + (h->t % h->hist_cap), mode == 0, h->st)) !=
         hipSuccess)
-      return dev_fail(h, e, "thin reduce");
+      return dev_fail(h, e, "thin finish");
     // the thin path has no separate sweep, V or row pass: their stages are empty
     for (int q = 2; q <= 6; ++q)
       if ((e = mark(q)) != hipSuccess) return dev_fail(h, e, "profile record");
-    if (mode == 0) {
-      if ((e = didk::bupdate(s, h->B, h->W, h->V, h->Bq, h->Bsc, h->Gpart, 1, h->st)) != hipSuccess)
-        return dev_fail(h, e, "B update");
-    } else {
+    if (mode != 0) {
       for (int i = 0; i < s.K; ++i)
         if ((e = didk::dbcd_b_step(s, X, h->B, h->C, h->tpart, h->W, i, h->st)) != hipSuccess)
           return dev_fail(h, e, "DBCD B step");
-      if ((e = didk::bupdate(s, h->B, h->W, h->V, h->Bq, h->Bsc, h->Gpart, 0, h->st)) != hipSuccess)
-        return dev_fail(h, e, "pack B");
+      if ((e = refresh_b_derived(h)) != hipSuccess) return dev_fail(h, e, "G of B");
     }
     if ((e = mark(7)) != hipSuccess) return dev_fail(h, e, "profile record");
-    if ((e = didk::finish_b(s, h->Gpart, h->G, h->B, h->Bq, h->Bsc, h->st)) != hipSuccess)
-      return dev_fail(h, e, "G reduce");
     if ((e = mark(8)) != hipSuccess) return dev_fail(h, e, "profile record");
     ++h->t;
   }

@@ -232,9 +232,9 @@ hipError_t group_iteration(int KP, int xkind, int cwpb, const GTable* dtab, cons
 // 2: DBCD C half (sweep, f partials).
 hipError_t thin_pass(const Shape& s, const float* X, const float* B, const double* G, float* C, double* part,
                      int mode, hipStream_t st);
-// W (KP x Mpad), V (KP x KP) and *fout = scale * f from the block partials (with_wv = 0: f only)
-hipError_t thin_reduce(const Shape& s, const double* part, double* W, double* V, double* fout, double scale,
-                       int with_wv, hipStream_t st);
+// from the block partials: *fout = f, and with full = 1 the B update and G = B^T B
+hipError_t thin_finish(const Shape& s, const double* part, float* B, double* G, double* fout, int full,
+                       hipStream_t st);
 // one DBCD column update b_i (a pass over X and a reduction); yz holds M + 1 doubles of
 // scratch (at least 17)
 hipError_t dbcd_b_step(const Shape& s, const float* X, float* B, const float* C, double* part, double* yz, int i,

@@ -11,7 +11,7 @@
 //   started from,
 // all in float64, accumulated per thread and then summed over the block in a fixed order
 // (the block partials are the paper's per-node messages; their fixed-order sum is the
-// single Allreduce).  The B update itself is the shared per-row kernel of the main path.
+// single Allreduce).  One more block sums the partials, updates B and forms G.
 //
 // The same path also runs DBCD (Alg. 2) as an ablation: the same C half, then for every
 // i = 1..K one pass over X forms y_j = (e_j + b_i c_ij) c_ij and z_j = c_ij^2 with e_j
@@ -33,13 +33,37 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// Sums of the wave's 64 lanes of N values each: lanes exchange halves of what they still hold,
+// so that a value costs about one exchange in all (24 for N = 22, against 6 for each value of
+// a butterfly per value).  This lane ends up with the sums of values base .. base + len - 1,
+// at most ceil(N / 64) of them, in v[0 ..].
+template <int N>
+__device__ __forceinline__ void wave_sums(double (&v)[N], int lane, int& base, int& len) {
+  base = 0;
+  len = N;
+#pragma unroll
+  for (int off = 32, n = N; off >= 1; n = (n + 1) / 2, off >>= 1) {
+    const int h = (n + 1) / 2;  // the lower lane of a pair keeps the first h of the n values
+    const bool up = (lane & off) != 0;
+#pragma unroll
+    for (int i = 0; i < h; ++i) {
+      const double a = v[i], b = i + h < n ? v[i + h] : 0.0;
+      v[i] = (up ? b : a) + __shfl_xor(up ? a : b, off, 64);
+    }
+    base += up ? h : 0;
+    len = up ? max(len - h, 0) : min(len, h);
+  }
+}
+
 // columns in flight per thread: fewer for the larger shapes, whose float64 accumulators
 // already take most of the registers
 constexpr int thin_pf(int MM, int KK) { return MM * KK <= 16 ? 3 : (MM * KK <= 32 ? 2 : 1); }
 
 }  // namespace
 
-int thin_slots(int MM, int KK) { return MM * KK + KK * KK + 1; }
+// slots of a block's partials: W (column k, row m at k MM + m), the lower triangle of V, f
+constexpr int thin_ns(int MM, int KK) { return MM * KK + KK * (KK + 1) / 2 + 1; }
+int thin_slots(int MM, int KK) { return thin_ns(MM, KK); }
 
 // One column's data as loaded: x_j (MM rows) and c_j (KK coordinates), float32.
 template <int MM, int KK>
@@ -58,7 +82,7 @@ template <int MM, int KK, int MODE, bool EXACT>
 __global__ __launch_bounds__(256) void k_thin(const float* __restrict__ X, int64_t M, int64_t N, int K,
                                              const float* __restrict__ B, const double* __restrict__ G, int KP,
                                              float* __restrict__ C, double* __restrict__ part) {
-  constexpr int NS = MM * KK + KK * KK + 1;
+  constexpr int NS = thin_ns(MM, KK);
   constexpr int PF = thin_pf(MM, KK);
   const int Mr = EXACT ? MM : (int)M;
   const int Kr = EXACT ? KK : K;
@@ -66,21 +90,9 @@ __global__ __launch_bounds__(256) void k_thin(const float* __restrict__ X, int64
   __shared__ double nk[KK];
   __shared__ double red[4][NS];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  for (int q = tid; q < MM * KK; q += 256) {
-    const int m = q % MM, k = q / MM;
-    Bs[q] = (m < Mr && k < Kr) ? (double)B[(int64_t)k * M + m] : 0.0;
-  }
-  if (tid < KK) nk[tid] = tid < Kr ? G[tid * KP + tid] : 0.0;
-  __syncthreads();
-  double Wacc[MM][KK], Vacc[KK][KK], facc = 0.0;
+  double sums[NS];  // this thread's share of every slot
 #pragma unroll
-  for (int m = 0; m < MM; ++m)
-#pragma unroll
-    for (int k = 0; k < KK; ++k) Wacc[m][k] = 0.0;
-#pragma unroll
-  for (int a = 0; a < KK; ++a)
-#pragma unroll
-    for (int b = 0; b < KK; ++b) Vacc[a][b] = 0.0;
+  for (int q = 0; q < NS; ++q) sums[q] = 0.0;
 
   auto load = [&](int64_t j) {
     ThinCol<MM, KK> v;
@@ -109,7 +121,7 @@ __global__ __launch_bounds__(256) void k_thin(const float* __restrict__ X, int64
 #pragma unroll
       for (int k = 0; k < KK; ++k) r -= Bs[k * MM + m] * c[k];
       e[m] = r;
-      facc += r * r;
+      sums[NS - 1] += r * r;
     }
     if (MODE != 1) {
 #pragma unroll
@@ -136,11 +148,11 @@ __global__ __launch_bounds__(256) void k_thin(const float* __restrict__ X, int64
 #pragma unroll
       for (int m = 0; m < MM; ++m)
 #pragma unroll
-        for (int k = 0; k < KK; ++k) Wacc[m][k] += e[m] * c[k];
+        for (int k = 0; k < KK; ++k) sums[k * MM + m] += e[m] * c[k];
 #pragma unroll
       for (int a = 0; a < KK; ++a)
 #pragma unroll
-        for (int b = 0; b <= a; ++b) Vacc[a][b] += c[a] * c[b];
+        for (int b = 0; b <= a; ++b) sums[MM * KK + a * (a + 1) / 2 + b] += c[a] * c[b];
     }
   };
 
@@ -149,6 +161,12 @@ __global__ __launch_bounds__(256) void k_thin(const float* __restrict__ X, int64
   ThinCol<MM, KK> ring[PF];
 #pragma unroll
   for (int p = 0; p < PF; ++p) ring[p] = load(j0 + p * stride);
+  for (int q = tid; q < MM * KK; q += 256) {  // while the first columns are on their way
+    const int m = q % MM, k = q / MM;
+    Bs[q] = (m < Mr && k < Kr) ? (double)B[(int64_t)k * M + m] : 0.0;
+  }
+  if (tid < KK) nk[tid] = tid < Kr ? G[tid * KP + tid] : 0.0;
+  __syncthreads();
   for (int64_t j = j0; j < N; j += PF * stride) {
 #pragma unroll
     for (int p = 0; p < PF; ++p) {
@@ -159,27 +177,21 @@ __global__ __launch_bounds__(256) void k_thin(const float* __restrict__ X, int64
       process(jj, cur);
     }
   }
-  // block partials: wave butterflies, then the four waves in order
-  auto put = [&](int slot, double v) {
-    v = wave_sum(v);
-    if (lane == 0) red[wave][slot] = v;
-  };
+  // block partials: the sums of each wave, then the four waves in order
   if (MODE == 0) {
+    int base, len;
+    wave_sums<NS>(sums, lane, base, len);
 #pragma unroll
-    for (int m = 0; m < MM; ++m)
-#pragma unroll
-      for (int k = 0; k < KK; ++k) put(k * MM + m, Wacc[m][k]);
-#pragma unroll
-    for (int a = 0; a < KK; ++a)
-#pragma unroll
-      for (int b = 0; b < KK; ++b) put(MM * KK + a * KK + b, b <= a ? Vacc[a][b] : 0.0);
-  } else if (lane == 0) {
-    for (int q = 0; q < NS - 1; ++q) red[wave][q] = 0.0;
+    for (int i = 0; i < (NS + 63) / 64; ++i)
+      if (i < len) red[wave][base + i] = sums[i];
+  } else {
+    const double v = wave_sum(sums[NS - 1]);
+    if (lane == 0) red[wave][NS - 1] = v;
   }
-  put(NS - 1, facc);
   __syncthreads();
   for (int q = tid; q < NS; q += 256)
-    part[(int64_t)blockIdx.x * NS + q] = ((red[0][q] + red[1][q]) + red[2][q]) + red[3][q];
+    if (MODE == 0 || q == NS - 1)
+      part[(int64_t)blockIdx.x * NS + q] = ((red[0][q] + red[1][q]) + red[2][q]) + red[3][q];
 }
 
 // Sum of slot q over the P block partials (stride NS), by one wave: lane l adds partials
@@ -200,30 +212,78 @@ __device__ __forceinline__ double slot_sum(const double* __restrict__ part, int6
   return wave_sum(s);
 }
 
-// One wave (block of 64) per slot: W (KP x Mpad, float64, row kk), V (KP x KP, symmetric)
-// and scale * f from the block partials; with_wv = 0 sums only f.
+// The rest of a DID iteration by one block: the fixed-order sums of the P block partials, f,
+// the B update (one thread per row, as the rows are independent) and G = B^T B.  full = 0 sums
+// only f.  (As three launches, one wave per slot, the general B update and G's reduction, this
+// took 14.5 us beside k_thin's 10.7 at N = 10^5; now 3.8 beside 5.3, k_thin's own part from
+// wave_sums and from loading its first columns before B.)
 template <int MM, int KK>
-__global__ __launch_bounds__(64) void k_thin_reduce(const double* __restrict__ part, int64_t P, int KP,
-                                                   int64_t Mpad, double* __restrict__ W, double* __restrict__ V,
-                                                   double* __restrict__ fout, double scale, int with_wv) {
-  constexpr int NS = MM * KK + KK * KK + 1;
-  const int q = with_wv ? (int)blockIdx.x : NS - 1;
-  const int lane = threadIdx.x;
-  if (q < MM * KK) {
-    const double s = slot_sum(part, P, NS, q, lane);
-    const int m = q % MM, k = q / MM;
-    if (lane == 0) W[(int64_t)k * Mpad + m] = s;
-  } else if (q < NS - 1) {
-    const int r = q - MM * KK, a = r / KK, b = r % KK;
-    if (b > a) return;
-    const double s = slot_sum(part, P, NS, q, lane);
-    if (lane == 0) {
-      V[a * KP + b] = s;
-      V[b * KP + a] = s;
+__global__ __launch_bounds__(1024) void k_thin_finish(const double* __restrict__ part, int64_t P, int64_t M, int K,
+                                                      int KP, float* __restrict__ B, double* __restrict__ G,
+                                                      double* __restrict__ fout, int full) {
+  constexpr int NS = thin_ns(MM, KK), NG = 1024 / NS;  // NG groups of NS threads, a slot each
+  __shared__ double acc[NG * NS], S[NS];
+  __shared__ float Bn[MM * KK];
+  const int tid = threadIdx.x, q = tid % NS, grp = tid / NS;
+  if (grp < NG) {
+    double s = 0.0;
+    if (full || q == NS - 1) {
+      constexpr int U = 8;  // loads issued ahead of the additions
+      int64_t p = grp;
+      for (; p + (U - 1) * NG < P; p += U * NG) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = part[(p + u * NG) * NS + q];
+#pragma unroll
+        for (int u = 0; u < U; ++u) s += v[u];
+      }
+      for (; p < P; p += NG) s += part[p * NS + q];
     }
-  } else {
-    const double s = slot_sum(part, P, NS, q, lane);
-    if (lane == 0) *fout = scale * s;
+    acc[tid] = s;
+  }
+  if (full && tid < MM * KK) {
+    const int m = tid % MM, k = tid / MM;
+    Bn[tid] = (m < M && k < K) ? B[(int64_t)k * M + m] : 0.0f;
+  }
+  __syncthreads();
+  if (tid < NS) {
+    double s = 0.0;
+#pragma unroll 8
+    for (int g = 0; g < NG; ++g) s += acc[g * NS + tid];
+    S[tid] = s;
+    if (tid == NS - 1) *fout = 0.5 * s;
+  }
+  if (!full) return;
+  __syncthreads();
+  if (tid < M) {  // b_mi := [b_mi + (w_mi - sum_{k < i} v_ik delta b_mk) / v_ii]_+, i ascending
+    double d[KK];
+#pragma unroll
+    for (int i = 0; i < KK; ++i) {
+      d[i] = 0.0;
+      if (i < K) {
+        const double* v = S + MM * KK + i * (i + 1) / 2;
+        double w = S[i * MM + tid];
+#pragma unroll
+        for (int k = 0; k < i; ++k) w -= v[k] * d[k];
+        const double old = (double)Bn[i * MM + tid];
+        double b = old;
+        if (v[i] > 0.0) {
+          b = old + w / v[i];
+          b = b > 0.0 ? b : 0.0;
+        }
+        d[i] = b - old;
+        Bn[i * MM + tid] = (float)b;
+        B[(int64_t)i * M + tid] = (float)b;
+      }
+    }
+  }
+  __syncthreads();
+  if (tid < K * K) {
+    const int a = tid / K, b = tid % K;
+    double g = 0.0;
+#pragma unroll
+    for (int m = 0; m < MM; ++m) g += (double)Bn[a * MM + m] * (double)Bn[b * MM + m];
+    G[a * KP + b] = g;
   }
 }
 
@@ -382,14 +442,13 @@ hipError_t thin_pass(const Shape& s, const float* X, const float* B, const doubl
   return hipGetLastError();
 }
 
-hipError_t thin_reduce(const Shape& s, const double* part, double* W, double* V, double* fout, double scale,
-                       int with_wv, hipStream_t st) {
+hipError_t thin_finish(const Shape& s, const double* part, float* B, double* G, double* fout, int full,
+                       hipStream_t st) {
   const int64_t P = thin_blocks(s);
-#define DID_THIN_RED(MM, KK, EX)                                                                   \
-  k_thin_reduce<MM, KK><<<with_wv ? thin_slots(MM, KK) : 1, 64, 0, st>>>(part, P, s.KP, s.Mpad, W, V, fout, \
-                                                                         scale, with_wv);
-  DID_THIN_SHAPES(DID_THIN_RED)
-#undef DID_THIN_RED
+#define DID_THIN_FIN(MM, KK, EX) \
+  k_thin_finish<MM, KK><<<1, 1024, 0, st>>>(part, P, s.M, s.K, s.KP, B, G, fout, full);
+  DID_THIN_SHAPES(DID_THIN_FIN)
+#undef DID_THIN_FIN
   return hipGetLastError();
 }
 

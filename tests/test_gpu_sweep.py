@@ -70,3 +70,31 @@ def test_column_pass_row_shares(M, N, K, cw):
     for t in (1, 3):
         np.testing.assert_array_equal(outs[1][t][0], out[t][0])
         np.testing.assert_array_equal(outs[1][t][1], out[t][1])
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (5, 65, 3),       # the 5 x 3 instance, one wave and one column over
+    (5, 300_000, 3),  # more block partials than the finishing block has groups
+    (2, 513, 1),      # 8 x 4, mostly padding
+    (8, 257, 4),      # 8 x 4, no padding
+    (8, 511, 8),      # 8 x 8: more slots than lanes
+    (16, 300, 4),     # 16 x 4: more slots than lanes
+    (9, 40_000, 2),   # 16 x 4 with padding
+])
+def test_thin_path_sums(M, N, K):
+    """The thin path's block sums and finishing block: factors and objectives against the
+    oracle, and the same bits from a second run."""
+    torch = require_gpu()
+    rng = np.random.default_rng(M * 100 + K)
+    X32 = to_f32_colmajor(rng.random((M, K)) @ rng.random((K, N)) + 0.01 * rng.random((M, N)))
+    X = as_oracle_input(X32)
+    announce(f"thin sums M={M} N={N} K={K}")
+    a, b = (run_gpu(torch, X32, K, iters=(1, 3)) for _ in range(2))
+    B0, C0 = a["init"]
+    Bo, Co, _ = oracle.did_run(X, B0, C0, 1)
+    check_factors(a[1][0], Bo, a[1][1], Co, label=f"thin {M}x{N} K={K}")
+    _, _, fo = oracle.did_run(X, B0, C0, 3)
+    check_trajectory(np.append(a["hist"], a["f"]), fo, label=f"thin {M}x{N} K={K}")
+    for t in (1, 3):
+        np.testing.assert_array_equal(a[t][0], b[t][0])
+        np.testing.assert_array_equal(a[t][1], b[t][1])
