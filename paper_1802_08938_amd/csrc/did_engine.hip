@@ -189,8 +189,12 @@ WorkPlan plan_work(Shape& s, int n_blocks, int row_blocks) {
   // resident blocks (5000 x 10^6: 9.77 ms per iteration at 4096 against 10.98 at 512),
   // narrower X fewer, longer ranges, whose W partials cost less to write and sum
   // (500 x 150000: 0.258 ms at 512 against 0.303 at 4096).
-  const int64_t target = row_blocks > 0 ? row_blocks : std::min<int64_t>(4096, std::max<int64_t>(512, s.N / 256));
-  const int64_t want = (target + slab_groups - 1) / slab_groups;
+  // Rounded down to whole blocks per CU, as are the ranges: a few blocks more than two per CU
+  // make some CUs run three (bf16 5000 x 62500: 520 blocks 287 us, 480 blocks 246; 1868 x
+  // 40000, K = 60: 525 blocks 104 us, 510 blocks 85).
+  int64_t target = row_blocks > 0 ? row_blocks : std::min<int64_t>(4096, std::max<int64_t>(512, s.N / 256));
+  if (target > 256) target = target / 256 * 256;
+  const int64_t want = std::max<int64_t>(1, target / slab_groups);
   // Ranges of at least max(4, K / 6) tiles, where the W partials (written and read: 8 K M
   // bytes a range) come to about 40 % of a range's X.  With 16 tiles a narrow X left the row
   // pass a few dozen blocks; us per row pass at 16, 8 and 4 tiles: 500 x 2000, K = 10: 31.2,

@@ -512,8 +512,60 @@ __global__ void k_zero_f32(float* p, int n) {
 // H-order operand comes from Bq, and E is stored to the column-major float32 residual
 // Rout (rvec4: 16-byte stores are aligned), so that the row pass can carry it on.  The
 // source X is then either the data (refresh) or Rout itself (carry: E = R - delta B C).
+//
+// The B run goes from global memory straight into LDS (global_load_lds_dwordx4: no staging
+// registers).  The chunk's closing barrier must wait for it, but not for the X tile of the
+// next chunk, whose loads are issued after it: stage_barrier leaves the last NX loads (those
+// of the X tile) in flight.  With __syncthreads, which waits for every load, each chunk waited
+// out the X tile's latency.
+// us per column pass before and after: 5000 x 10^6, K = 50, tiled float32: 4922, 4474 (and three
+// waves per SIMD, the staging registers gone); bf16 5000 x 62500: 286, 271; 24 jobs in a batch, K
+// <= 32: 398, 356.
+template <typename XT>
+struct x_loads {  // loads of one X tile per lane where their number is fixed, else 0
+  static constexpr int value = std::is_same<XT, xtf32>::value ? 4 : (std::is_same<XT, __bf16>::value ? 2 : 0);
+};
+// Keeps the loads before it ahead of those after it (X is not __restrict__ in the passes: the
+// loads of memory known not to change would move across).
+__device__ __forceinline__ void load_order() { asm volatile("" ::: "memory"); }
+// s_waitcnt with vmcnt(NX) and lgkmcnt(0) (the builtin, so that the compiler's own waits count
+// it), then the barrier.  tests/test_stage_waits.py checks the generated code: NX loads, and
+// no others, lie between the staging and each of these waits.
+template <int NX>
+__device__ __forceinline__ void stage_barrier() {
+  load_order();
+  __builtin_amdgcn_s_waitcnt(NX | 0x70);
+  __builtin_amdgcn_s_barrier();
+  load_order();
+}
+
+// U units (16 bytes each) to LDS at dst by a block of 64 WPB threads, 64 units per load; src(u)
+// is the address of unit u.  RUNS: the 64 units of a load are one contiguous run, which a
+// buffer load takes from its (wave-uniform) first unit.  Otherwise (the carried form, whose
+// units come from two buffers) each lane gives its own address to a global_load_lds, which the
+// compiler takes for a flat access, after which it waits for all loads at every use of one.
+template <int U, int WPB, bool RUNS, class Src>
+__device__ __forceinline__ void stage_units(f32x4* dst, int wave, int l, Src src) {
+  auto put = [&](int u0, int n) {
+    const auto to = (__attribute__((address_space(3))) void*)&dst[u0];
+    if constexpr (RUNS)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          __builtin_amdgcn_make_buffer_rsrc((void*)src(u0), 0, 16 * n, 0x00020000), to, 16, 16 * l, 0, 0, 0);
+    else
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src(u0 + l), to, 16, 0, 0);
+  };
+  constexpr int FULL = U / (64 * WPB);
+#pragma unroll
+  for (int v = 0; v < FULL; ++v) put(64 * (WPB * v + wave), 64);
+  constexpr int REST = U - FULL * 64 * WPB;  // by the first waves
+  if (64 * wave < REST) {
+    const int n = REST - 64 * wave < 64 ? REST - 64 * wave : 64;
+    if (l < n) put(FULL * 64 * WPB + 64 * wave, n);
+  }
+}
+
 template <int KP, bool WITH_H, typename XT, bool RW = false, int WPB = 4>
-__device__ __forceinline__ void colpass_body(const XT* __restrict__ X, int64_t M, int64_t N, int K,
+__device__ __forceinline__ void colpass_body(const XT* X, int64_t M, int64_t N, int K,
                                              const f32x4* __restrict__ Cq, const _Float16* __restrict__ Bq,
                                              float* Bsc, float* __restrict__ Csc, float* __restrict__ Hout,
                                              double* __restrict__ fpart, int64_t nchunks, int vec4, int csplit,
@@ -524,10 +576,9 @@ __device__ __forceinline__ void colpass_body(const XT* __restrict__ X, int64_t M
   constexpr int UE = BqL<KP>::E;      // 16-byte units of the E operand per chunk
   constexpr int US = BqL<KP>::S;      // the chunk's 32 row scales
   constexpr int U = BqL<KP>::C;       // the chunk's whole run
-  constexpr int NV = (U + 64 * WPB - 1) / (64 * WPB);  // units per thread per chunk
   constexpr int UCT = CqL<KP>::T;     // units per packed C tile
   constexpr int UCE0 = CqL<KP>::E0;   // the tile's inverse column scales
-  __shared__ f32x4 sb[2][U];
+  __shared__ f32x4 sb0[U], sb1[U];  // the two stages of B
   __shared__ double fw[WPB];
   // the wave index is uniform: from a scalar register, so that wave-based addresses stay scalar
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, half = l >> 5,
@@ -569,17 +620,14 @@ __device__ __forceinline__ void colpass_body(const XT* __restrict__ X, int64_t M
   int vcur = 126;  // current scale exponent of this column's E operand (never raised)
   double fs0 = 0.0, fs1 = 0.0;
 
-  f32x4 stg[NV];
-  auto gload = [&](int64_t c) {
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const int u = tid + 64 * WPB * v;
-      const int uu = u < U ? u : U - 1;  // threads past the end reload the last unit
+  constexpr int NX = RW ? 0 : x_loads<XT>::value;
+  auto cdma = [&](int64_t c, int buf) {
+    stage_units<U, WPB, !RW>(buf ? sb1 : sb0, wave, l, [&](int u) {
       const _Float16* base = Bq;
-      if constexpr (RW) base = (uu < UE || uu >= US) ? BqE : Bq;
-      const f32x4* src = reinterpret_cast<const f32x4*>(base) + c * U + uu;
-      stg[v] = *src;
-    }
+      if constexpr (RW) base = (u < UE || u >= US) ? BqE : Bq;
+      return reinterpret_cast<const f32x4*>(base) + c * U + u;
+    });
+    load_order();
   };
   // the residual store of the carried form: the accumulator layout of E, column-major
   float* const rtile = RW ? Rout + (tileok ? j0 : 0) * M : nullptr;
@@ -599,13 +647,6 @@ __device__ __forceinline__ void colpass_body(const XT* __restrict__ X, int64_t M
           const int64_t r = m0 + 8 * q + 4 * half + t;
           if (colok && r < M) rtile[(int64_t)lc * M + r] = e[4 * q + t];
         }
-    }
-  };
-  auto sstore = [&](int buf) {
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const int u = tid + 64 * WPB * v;
-      if (u < U) sb[buf][u] = stg[v];
     }
   };
   const bool tilefull = vec4 && (j0 + 32 <= N);  // wave-uniform
@@ -641,19 +682,19 @@ __device__ __forceinline__ void colpass_body(const XT* __restrict__ X, int64_t M
   };
 
   // One chunk: compute chunk c from the X tile in xc (loaded one chunk earlier) and the
-  // staged B operands in LDS buffer c & 1; meanwhile stage chunk c+1's B operands and load
+  // staged B operands in LDS buffer buf (a constant where step is called); meanwhile stage chunk c+1's B operands and load
   // its X tile into xn (the two tiles alternate roles from one chunk to the next, so
   // nothing is copied).
-  auto step = [&](int64_t c, const f32x16& xc, f32x16& xn) {
-    const int buf = (int)((c - c0) & 1);
+  auto step = [&](int64_t c, int buf, const f32x16& xc, f32x16& xn) {
     const int64_t cn = c + 1 < c1 ? c + 1 : c;
-    gload(cn);
+    cdma(cn, buf ^ 1);
     xn = xload(cn);
+    load_order();
     // E of the chunk, a value of its own (not written over the X tile, which would make the
     // two alternating tiles cost a copy per chunk)
     f32x16 acc;
     {  // E = X - B C: KS steps of three MFMAs, operands of step s+1 read from LDS during step s
-      const f32x4* ue = &sb[buf][0] + l;
+      const f32x4* ue = (buf ? sb1 : sb0) + l;
       f16x8 a[2], an[2];
       f32x16 P;
 #pragma unroll
@@ -675,7 +716,7 @@ __device__ __forceinline__ void colpass_body(const XT* __restrict__ X, int64_t M
       // rows row32(4q + e, half) = 8q + 4 half + e: their inverse scales are unit 2q + half.
       // A negative first scale flags a chunk whose rows share one scale (the B update):
       // one multiplier for the whole tile.
-      const f32x4* rs = &sb[buf][US];
+      const f32x4* rs = (buf ? sb1 : sb0) + US;
       const float s0 =
           __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, rs[0][0])));
       if (s0 < 0.0f) {
@@ -718,7 +759,7 @@ __device__ __forceinline__ void colpass_body(const XT* __restrict__ X, int64_t M
           for (int i = 0; i < 16; ++i) H[b][i] = ldexpf(H[b][i], v - vcur);
         vcur = v;
       }
-      const f32x4* uh = &sb[buf][UE] + l;
+      const f32x4* uh = (buf ? sb1 : sb0) + UE + l;
       f16x8 h[2], hn[2];
       f16x8 eP[2][2];
 #pragma unroll
@@ -748,18 +789,16 @@ __device__ __forceinline__ void colpass_body(const XT* __restrict__ X, int64_t M
         }
       }
     }
-    sstore(buf ^ 1);
-    __syncthreads();
+    stage_barrier<NX>();
   };
 
   f32x16 x0 = xload(c0);
-  gload(c0);
-  sstore(0);
-  __syncthreads();
+  cdma(c0, 0);
+  stage_barrier<0>();
   f32x16 x1;
   for (int64_t c = c0; c < c1; c += 2) {
-    step(c, x0, x1);
-    if (c + 1 < c1) step(c + 1, x1, x0);
+    step(c, 0, x0, x1);
+    if (c + 1 < c1) step(c + 1, 1, x1, x0);
   }
 
   if (WITH_H && tileok) {  // the tile's rows of H, 32 columns each (zeros past K and N)
@@ -790,7 +829,7 @@ __device__ __forceinline__ void colpass_body(const XT* __restrict__ X, int64_t M
 }
 
 template <int KP, bool WITH_H, typename XT, int WPB>
-__global__ __launch_bounds__(64 * WPB, 8 / WPB) void k_colpass(const XT* __restrict__ X, int64_t M, int64_t N, int K,
+__global__ __launch_bounds__(64 * WPB, 8 / WPB) void k_colpass(const XT* X, int64_t M, int64_t N, int K,
                                                                const f32x4* __restrict__ Cq,
                                                                const _Float16* __restrict__ Bq,
                                                                float* Bsc, float* __restrict__ Csc,
@@ -1699,7 +1738,7 @@ int64_t vgram_blocks(const Shape& s) {
 // CqL<KP>::E units per tile) while the W-order operand comes from Cq, so that
 // E' = R - B delta C, and E' is stored back into R in place.
 template <int KP, typename XT, bool RW = false>
-__device__ __forceinline__ void rowpass_body(const XT* __restrict__ X, int64_t M, int64_t N, int K,
+__device__ __forceinline__ void rowpass_body(const XT* X, int64_t M, int64_t N, int K,
                                              const f32x4* __restrict__ Cq, const float* __restrict__ Csc,
                                              const _Float16* __restrict__ Bq,
                                              float* __restrict__ Wpart, int64_t Mpad, int64_t nchunks,
@@ -1710,7 +1749,6 @@ __device__ __forceinline__ void rowpass_body(const XT* __restrict__ X, int64_t M
   constexpr int UE0 = CqL<KP>::E0;     // 16-byte units of the E'^T A operand per tile
   constexpr int UE = CqL<KP>::E;       // ... followed by the tile's inverse column scales
   constexpr int UT = CqL<KP>::T;       // then the W A operand
-  constexpr int NV = (UT + 255) / 256;
   constexpr int64_t UC = BqL<KP>::C;   // units per packed B chunk
   constexpr int UBS = BqL<KP>::S;      // the chunk's 32 row scales
   __shared__ f32x4 sc[2][UT];
@@ -1744,21 +1782,16 @@ __device__ __forceinline__ void rowpass_body(const XT* __restrict__ X, int64_t M
     for (int i = 0; i < 16; ++i) WT[b][i] = 0.0f;
   int vcur = 126;  // current scale exponent of this row's E' operand (never raised)
 
-  // tile T's packed C units straight from global memory into LDS buffer buf (no staging
-  // registers): lane l of wave w writes unit w*64 + 256 v + l, the unit it loads
+  // tile T's packed C units straight into LDS buffer buf, as the column pass stages B
+  constexpr int NX = RW ? 0 : x_loads<XT>::value;
   auto cdma = [&](int64_t T, int buf) {
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const int u = tid + 256 * v;
-      if (u < UT) {
-        const f32x4* src = Cq + T * UT + u;
-        if constexpr (RW)
-          if (u < UE) src = CqE + T * UE + u;
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                         (__attribute__((address_space(3))) void*)&sc[buf][wave * 64 + 256 * v], 16, 0,
-                                         0);
-      }
-    }
+    stage_units<UT, 4, !RW>(&sc[buf][0], wave, l, [&](int u) {
+      const f32x4* src = Cq + T * UT + u;
+      if constexpr (RW)
+        if (u < UE) src = CqE + T * UE + u;
+      return src;
+    });
+    load_order();
   };
   const uint32_t loff = (uint32_t)(4 * half * M + mrow);  // lane offset within a tile
   const bool rowsfull = active && m0 + 32 <= M;            // wave-uniform
@@ -1790,6 +1823,7 @@ __device__ __forceinline__ void rowpass_body(const XT* __restrict__ X, int64_t M
     const int64_t Tn = T + 1 < thi ? T + 1 : T;
     cdma(Tn, buf ^ 1);
     xn = xload(Tn);
+    load_order();
     if (active) {
       f32x16 acc;  // E' of the tile (the X tile in xc stays as loaded)
       {
@@ -1888,13 +1922,13 @@ __device__ __forceinline__ void rowpass_body(const XT* __restrict__ X, int64_t M
         }
       }
     }
-    __syncthreads();
+    stage_barrier<NX>();
   };
 
   if (tlo < thi) {
     f32x16 x0 = xload(tlo);
     cdma(tlo, 0);
-    __syncthreads();
+    stage_barrier<0>();
     f32x16 x1;
     for (int64_t T = tlo; T < thi; T += 2) {
       step(T, 0, x0, x1);
@@ -1915,7 +1949,7 @@ __device__ __forceinline__ void rowpass_body(const XT* __restrict__ X, int64_t M
 }
 
 template <int KP, typename XT>
-__global__ __launch_bounds__(256, 2) void k_rowpass(const XT* __restrict__ X, int64_t M, int64_t N, int K,
+__global__ __launch_bounds__(256, 2) void k_rowpass(const XT* X, int64_t M, int64_t N, int K,
                                                     const f32x4* __restrict__ Cq, const float* __restrict__ Csc,
                                                     const _Float16* __restrict__ Bq, float* __restrict__ Wpart,
                                                     int64_t Mpad, int64_t nchunks, const int64_t* __restrict__ tb,
@@ -2196,9 +2230,13 @@ __device__ __forceinline__ int ginst_find(const GTable* __restrict__ g, int st, 
   return lo;
 }
 
+// A pointer of the table (generic, wave-uniform) as one into global memory; through an integer
+// that the compiler cannot see through, or it folds the casts away and emits flat accesses.
 template <typename T>
 __device__ __forceinline__ T* as_global(T* p) {
-  return (T*)(__attribute__((address_space(1))) T*)p;
+  uint64_t u = (uint64_t)(uintptr_t)p;
+  asm("" : "+s"(u));
+  return (T*)(__attribute__((address_space(1))) T*)u;
 }
 
 #define DID_GROUP_LOOP(ST)                                                     \
@@ -2215,8 +2253,12 @@ __device__ __forceinline__ T* as_global(T* p) {
 template <int KP, typename XT, int WPB>
 __global__ __launch_bounds__(64 * WPB, 8 / WPB) void kg_colpass(const GTable* __restrict__ g) {
   DID_GROUP_LOOP(GS_COL)
-  colpass_body<KP, true, XT, false, WPB>(static_cast<const XT*>(d.X), d.M, d.N, d.K, static_cast<const f32x4*>(d.Cq),
-                                         d.Bq, d.Bsc, d.Csc, d.H, d.fpart, d.nchunks, d.vec4, d.csplit, bid);
+  // global pointers (the table's are generic): after a flat load every wait would be for all
+  // loads, and the passes count theirs
+  colpass_body<KP, true, XT, false, WPB>(as_global(static_cast<const XT*>(d.X)), d.M, d.N, d.K,
+                                         as_global(static_cast<const f32x4*>(d.Cq)), as_global(d.Bq), as_global(d.Bsc),
+                                         as_global(d.Csc), as_global(d.H), as_global(d.fpart), d.nchunks, d.vec4,
+                                         d.csplit, bid);
   DID_GROUP_END
 }
 
@@ -2263,9 +2305,9 @@ __global__ __launch_bounds__(64 * kVWaves, 2) void kg_packv(const GTable* __rest
 template <int KP, typename XT>
 __global__ __launch_bounds__(256, 2) void kg_rowpass(const GTable* __restrict__ g) {
   DID_GROUP_LOOP(GS_ROW)
-  rowpass_body<KP, XT>(static_cast<const XT*>(d.XR), d.M, d.N, d.K, static_cast<const f32x4*>(d.Cq), d.Csc, d.Bq,
-                       d.Wpart,
-                       d.Mpad, d.nchunks, d.tb, d.R, d.nsg, bid);
+  rowpass_body<KP, XT>(as_global(static_cast<const XT*>(d.XR)), d.M, d.N, d.K,
+                       as_global(static_cast<const f32x4*>(d.Cq)), as_global(d.Csc), as_global(d.Bq),
+                       as_global(d.Wpart), d.Mpad, d.nchunks, as_global(d.tb), d.R, d.nsg, bid);
   DID_GROUP_END
 }
 
