@@ -88,11 +88,11 @@ struct did_ctx {
   // DID_DEBUG_GUARD_ZONES: a patterned zone after each buffer carved from the arena
   bool guards = false;
   std::vector<std::pair<unsigned char*, int>> guard_zones;  // zone start, buffer index
-  // one captured iteration of the MFMA path, replayed by did_iterate (not in the carried
-  // form, not while profiling; never by did_iterate_static, which must not allocate)
+  // captured iterations of the MFMA path, one and a run of them, replayed by did_iterate (not in
+  // the carried form, not while profiling; never by did_iterate_static, which must not allocate)
   bool use_graph = true;
   bool graph_failed = false;
-  hipGraphExec_t gexec = nullptr;
+  hipGraphExec_t gexec = nullptr, gexec_run = nullptr;
   // per-stage timing: kStages+1 events per profiled iteration
   bool profiling = false;
   std::vector<hipEvent_t> prof_events;

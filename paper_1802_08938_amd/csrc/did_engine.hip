@@ -131,6 +131,7 @@ void release(did_ctx* h) {
   DeviceGuard g(h->dev);
   if (h->st) (void)hipStreamSynchronize(h->st);
   if (h->gexec) (void)hipGraphExecDestroy(h->gexec);
+  if (h->gexec_run) (void)hipGraphExecDestroy(h->gexec_run);
   for (hipEvent_t ev : h->prof_events) (void)hipEventDestroy(ev);
   h->prof_events.clear();
   for (void* p : h->allocs) (void)hipFree(p);
@@ -746,40 +747,54 @@ static int enqueue_iteration(did_ctx* h, hipEvent_t* ev) {
   return DID_OK;
 }
 
+// Captures q iterations into a graph of the handle, once; false where that is not possible
+// (rc: an error of the launches themselves).
+static bool iteration_graph(did_ctx* h, int q, hipGraphExec_t& exec, int& rc) {
+  rc = DID_OK;
+  if (exec || h->graph_failed) return exec != nullptr;
+  hipGraph_t g = nullptr;
+  hipError_t e = hipStreamBeginCapture(h->st, hipStreamCaptureModeThreadLocal);
+  if (e == hipSuccess) {
+    for (int k = 0; k < q && !rc; ++k) rc = enqueue_iteration(h, nullptr);
+    e = hipStreamEndCapture(h->st, &g);
+    if (!rc && e == hipSuccess && g) e = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
+    if (g) (void)hipGraphDestroy(g);
+    if (rc) return false;
+  }
+  if (e != hipSuccess || !exec) {
+    (void)hipGetLastError();
+    exec = nullptr;
+    h->graph_failed = true;
+  }
+  return exec != nullptr;
+}
+
 // Iterations of the MFMA path on the buffers of h (shared by did_iterate and the
 // allocation-free did_iterate_static).  Without profiling, two or more iterations of the
-// refresh-every-iteration form replay one captured iteration (a hipGraph kept by the handle),
-// which removes the host launch cost that bounds small shapes.
+// refresh-every-iteration form replay captured ones (hipGraphs kept by the handle).
+//
+// A graph's start and end cost about 8 us between its last kernel and the next graph's first
+// (inside a graph the kernels follow each other at once), so a handle from its 16th iteration
+// on replays kGraphRun iterations at a time.  Instantiating those takes about 60 us, which
+// shorter runs do not earn back: us per call of 20 iterations, 500 x 2000, K = 10: 1014 one at
+// a time, 941 four at a time; first call of 5 iterations, 10304 x 575, K = 25: 500, with the
+// longer graph from the start 538.
 int iterate_mfma(did_ctx* h, int32_t n) {
+  constexpr int32_t kGraphRun = 4, kGraphRunFrom = 16;
   hipError_t e;
   if (n <= 0) return DID_OK;
   if (h->use_graph && !h->profiling && h->refresh == 1 && n >= 2) {
-    if (!h->gexec && !h->graph_failed) {
-      hipGraph_t g = nullptr;
-      if ((e = hipStreamBeginCapture(h->st, hipStreamCaptureModeThreadLocal)) != hipSuccess) {
-        (void)hipGetLastError();
-        h->graph_failed = true;
-      } else {
-        const int rc = enqueue_iteration(h, nullptr);
-        e = hipStreamEndCapture(h->st, &g);
-        if (rc) {
-          if (g) (void)hipGraphDestroy(g);
-          return rc;
-        }
-        if (e != hipSuccess || !g || hipGraphInstantiate(&h->gexec, g, nullptr, nullptr, 0) != hipSuccess) {
-          (void)hipGetLastError();
-          h->gexec = nullptr;
-          h->graph_failed = true;
-        }
-        if (g) (void)hipGraphDestroy(g);
-      }
-    }
-    if (h->gexec) {
-      for (int32_t it = 0; it < n; ++it)
+    int rc = DID_OK;
+    int32_t it = 0;
+    if (n >= kGraphRun && h->t + n >= kGraphRunFrom && iteration_graph(h, kGraphRun, h->gexec_run, rc))
+      for (; it + kGraphRun <= n; it += kGraphRun, h->t += kGraphRun)
+        if ((e = hipGraphLaunch(h->gexec_run, h->st)) != hipSuccess) return dev_fail(h, e, "iteration graph launch");
+    if (rc) return rc;
+    if (it == 0 && iteration_graph(h, 1, h->gexec, rc))
+      for (; it < n; ++it, ++h->t)
         if ((e = hipGraphLaunch(h->gexec, h->st)) != hipSuccess) return dev_fail(h, e, "iteration graph launch");
-      h->t += n;
-      return DID_OK;
-    }
+    if (rc || it == n) return rc;
+    n -= it;  // up to three after the longer graphs
   }
   for (int32_t it = 0; it < n; ++it) {
     hipEvent_t* ev = nullptr;
