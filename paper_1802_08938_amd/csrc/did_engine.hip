@@ -419,45 +419,36 @@ int setup(did_ctx* h, const void* Xv, int64_t M, int64_t N, int32_t K, const did
     }
     xin = xtmp;
   }
-  if (h->defer_checks && !xtmp) {  // X must be finite and nonnegative: checked later
-    const int v4 = (M % 4 == 0) && ((reinterpret_cast<uintptr_t>(xin) & 15) == 0);
-    if ((e = hipMemsetAsync(h->flag, 0, sizeof(int), h->st)) != hipSuccess ||
-        (e = didk::validate(xin, M * N, v4, h->flag, h->st)) != hipSuccess)
-      return dev_fail(h, e, "validate X");
-    h->x_check_pending = true;
-  } else {  // X must be finite and nonnegative
-    const int v4 = (M % 4 == 0) && ((reinterpret_cast<uintptr_t>(xin) & 15) == 0);
-    int flag = 0;
-    if ((e = hipMemsetAsync(h->flag, 0, sizeof(int), h->st)) != hipSuccess ||
-        (e = didk::validate(xin, M * N, v4, h->flag, h->st)) != hipSuccess ||
-        (e = hipMemcpyAsync(&flag, h->flag, sizeof(int), hipMemcpyDeviceToHost, h->st)) != hipSuccess ||
-        (e = hipStreamSynchronize(h->st)) != hipSuccess) {
-      if (xtmp) (void)hipFree(xtmp);
-      return dev_fail(h, e, "validate X");
-    }
-    if (flag) {
-      if (xtmp) (void)hipFree(xtmp);
-      return fail(DID_EINVAL, "X must be finite and nonnegative");
-    }
-  }
-  if (s.xtiled) {  // the two tiled copies (one per pass) in one allocation
-    unsigned char* xb = nullptr;
-    const int64_t te = didk::tiled_x_elems(s), esz = s.xbf16 ? 2 : 4;
-    if ((rc = dalloc(h, &xb, 2 * te * esz))) {
-      if (xtmp) (void)hipFree(xtmp);
-      return rc;
-    }
-    e = didk::tile_x(s, xin, xb, xb + te * esz, h->st);
-    if (e == hipSuccess && (xtmp || !h->defer_checks)) e = hipStreamSynchronize(h->st);
+  // X must be finite and nonnegative: checked by the kernel that lays out the two tiled copies
+  // (one per pass, one allocation), or on its own; the answer is read here, or later where the
+  // caller asked for that and no upload has to be freed
+  const bool later = h->defer_checks && !xtmp;
+  unsigned char* xb = nullptr;
+  const int64_t te = s.xtiled ? didk::tiled_x_elems(s) : 0, esz = s.xbf16 ? 2 : 4;
+  if (s.xtiled && (rc = dalloc(h, &xb, 2 * te * esz))) {
     if (xtmp) (void)hipFree(xtmp);
-    if (e != hipSuccess) return dev_fail(h, e, "tiled storage of X");
+    return rc;
+  }
+  const bool v4 = (M % 4 == 0) && ((reinterpret_cast<uintptr_t>(xin) & 15) == 0);
+  int flag = 0;
+  if ((e = hipMemsetAsync(h->flag, 0, sizeof(int), h->st)) == hipSuccess)
+    e = s.xtiled ? didk::tile_x(s, xin, xb, xb + te * esz, h->flag, h->st)
+                 : didk::validate(xin, M * N, v4, h->flag, h->st);
+  if (e == hipSuccess && !later &&
+      (e = hipMemcpyAsync(&flag, h->flag, sizeof(int), hipMemcpyDeviceToHost, h->st)) == hipSuccess)
+    e = hipStreamSynchronize(h->st);
+  if (xtmp) (void)hipFree(xtmp);
+  if (e != hipSuccess) return dev_fail(h, e, "validate X");
+  if (flag) return fail(DID_EINVAL, "X must be finite and nonnegative");
+  h->x_check_pending = later;
+  if (s.xtiled) {
     h->X = xb;
     h->XR = xb + te * esz;
     s.vec4 = 0;  // the tiled copies are read with their own full-width loads
   } else {
     h->X = const_cast<float*>(xin);
     h->XR = h->X;
-    s.vec4 = (M % 4 == 0) && ((reinterpret_cast<uintptr_t>(xin) & 15) == 0);
+    s.vec4 = v4;
   }
 
   const int NP = didk::n_pairs(s.KP);

@@ -104,8 +104,9 @@ hipError_t validate(const float* p, int64_t n, int vec4, int* flag, hipStream_t 
 // fully used 1 kB runs.  bf16 values are rounded to nearest even.
 inline int64_t n_tiles(const Shape& s) { return (s.N + 31) / 32; }
 inline int64_t tiled_x_elems(const Shape& s) { return s.nchunks * n_tiles(s) * 1024; }
-// xc and xr each hold tiled_x_elems(s) values of the storage type (s.xbf16)
-hipError_t tile_x(const Shape& s, const float* src, void* xc, void* xr, hipStream_t st);
+// xc and xr each hold tiled_x_elems(s) values of the storage type (s.xbf16); flag |= 1 if an entry
+// of src is negative, NaN or infinite
+hipError_t tile_x(const Shape& s, const float* src, void* xc, void* xr, int* flag, hipStream_t st);
 hipError_t scale(float* p, int64_t n, float a, hipStream_t st);
 
 // Pack B into MFMA operand order (Bq, layout above; Bsc: its column scales), optionally
