@@ -85,10 +85,10 @@ __host__ __device__ inline int64_t range_bounds(int64_t T, int64_t P, int64_t S,
 }
 
 // ---- launchers (all asynchronous on `st`; they return the launch status) ----
-// zero `bytes` (a multiple of 16) bytes at the 16-byte aligned p with a fill kernel
-hipError_t zero16(void* p, int64_t bytes, hipStream_t st);
-// range_bounds on the device into tb (R + 1 entries)
-hipError_t ranges_on_device(int64_t* tb, int64_t T, int64_t P, int64_t S, hipStream_t st);
+// clears the packed operands, scales, V and W, writes range_bounds into tb (R + 1 entries) and
+// sets *tdev = 0, in one launch of stores
+hipError_t static_setup(const Shape& s, void* Bq, void* Cq, float* Bsc, float* Csc, double* V, double* W, int64_t* tb,
+                        int64_t T, int64_t P, int64_t S, int64_t* tdev, hipStream_t st);
 hipError_t fill_uniform(float* out, int64_t n, uint64_t key, hipStream_t st);
 hipError_t validate(const float* p, int64_t n, int vec4, int* flag, hipStream_t st);
 // Tiled storage of X (the bf16 form, and the float32 form on request): two copies in
@@ -174,8 +174,6 @@ hipError_t reduce_f(const double* part, int64_t P, double* out, double scale, hi
 // after the B update: G = B^T B from its partials, and B's H order (column scales in Bsc)
 hipError_t finish_b(const Shape& s, const double* Gpart, double* G, const float* B, _Float16* Bq, float* Bsc,
                     hipStream_t st);
-// *p = v from a kernel (no memset node, no host memory)
-hipError_t set_i64(int64_t* p, int64_t v, hipStream_t st);
 
 // ---- batched form: grouped persistent kernels over a device-resident instance table ----
 // One group holds instances of one (KP, X storage, column-pass block waves) triple.  Every stage of an iteration is a

@@ -194,17 +194,19 @@ __device__ __forceinline__ void block_copy(float* dst, const float* src, int n) 
   for (; e < n; e += 256) dst[e] = src[e];
 }
 
-// pack_block takes the (up to) eight tiles of columns j0 .. j0 + nv - 1, whose values sit
+// pack_block takes the (up to) kPackTiles tiles of columns j0 .. j0 + nv - 1, whose values sit
 // in LDS as Ct[j * K + kk] (j relative to j0); every thread builds whole 16-byte units, so
 // the global stores are coalesced.  All threads of the block call it, after Ct is
-// complete; it takes 256 ints of LDS scratch (cs) from the caller.
+// complete; it takes 256 ints of LDS scratch (cs) from the caller.  Two tiles a block: with
+// eight, 600 x 9000 had 36 blocks (K = 40: 13.1 us, now 8.0; at 10^6 columns 85 and 105).
+constexpr int kPackTiles = 2;
 template <int KP>
 __device__ __forceinline__ void pack_block(f32x4* __restrict__ Cq, int64_t j0, int nv, const float* Ct, int K,
                                            int64_t ntiles, int* cs) {
   constexpr int KS = KP / 16;
   constexpr int UE0 = CqL<KP>::E0;
   constexpr int UT = CqL<KP>::T;  // units per tile of the target buffer
-  constexpr int GE = 8 * KS * 64;  // E groups per block: (tile, s, half, jj)
+  constexpr int GE = kPackTiles * KS * 64;  // E groups per block: (tile, s, half, jj)
   const int tid = threadIdx.x;     // cs[j]: scale exponent of column j0 + j
   const int64_t T0 = j0 >> 5;
   {
@@ -244,7 +246,7 @@ __device__ __forceinline__ void pack_block(f32x4* __restrict__ Cq, int64_t j0, i
 #pragma unroll
     for (int p = 0; p < 2; ++p) tile[(s * 2 + p) * 64 + jj + 32 * h] = f16_as_f32x4(sp.p[p]);
   }
-  if (tid < 64) {  // inverse scales: tile tid / 8, unit tid % 8
+  if (tid < 8 * kPackTiles) {  // inverse scales: tile tid / 8, unit tid % 8
     const int tb = tid >> 3, u = tid & 7;
     if (T0 + tb < ntiles) {
       f32x4 w;
@@ -491,26 +493,45 @@ __device__ __forceinline__ void packh_body(const float* __restrict__ B, int64_t 
   }
 }
 
-__global__ void k_zero16(f32x4* p, int64_t n) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = f32x4{0, 0, 0, 0};
+// The buffers that an allocation-free call finds as the last one left them: the packed
+// operands, scales, V and W are cleared, the column ranges written and the iteration counter
+// reset, by fill kernels' stores (no memset node, so that the call can be captured).  One launch
+// instead of eight, each bound by its own latency (600 x 9000, K = 40: 19 us and 7 gaps, now
+// 6.7); the last block's one thread writes the ranges beside the others' fills.
+struct ZeroSpans {
+  f32x4* p[6];
+  int64_t n[6];  // 16-byte units
+};
+
+__global__ __launch_bounds__(256) void k_static_setup(ZeroSpans z, int64_t* tb, int64_t T, int64_t P, int64_t S,
+                                                      int64_t* tdev) {
+  if (blockIdx.x == gridDim.x - 1) {
+    if (threadIdx.x == 0) {
+      (void)range_bounds(T, P, S, tb);
+      *tdev = 0;
+    }
+    return;
+  }
+  const int64_t stride = (int64_t)(gridDim.x - 1) * 256;
+#pragma unroll
+  for (int q = 0; q < 6; ++q)
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < z.n[q]; i += stride) z.p[q][i] = f32x4{0, 0, 0, 0};
 }
 
-hipError_t zero16(void* p, int64_t bytes, hipStream_t st) {
-  const int64_t n = bytes / 16;
-  if (n <= 0) return hipSuccess;
-  int64_t blocks = (n + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  k_zero16<<<(unsigned)blocks, 256, 0, st>>>(static_cast<f32x4*>(p), n);
-  return hipGetLastError();
-}
-
-__global__ void k_ranges(int64_t* tb, int64_t T, int64_t P, int64_t S) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) (void)range_bounds(T, P, S, tb);
-}
-
-hipError_t ranges_on_device(int64_t* tb, int64_t T, int64_t P, int64_t S, hipStream_t st) {
-  k_ranges<<<1, 64, 0, st>>>(tb, T, P, S);
+hipError_t static_setup(const Shape& s, void* Bq, void* Cq, float* Bsc, float* Csc, double* V, double* W, int64_t* tb,
+                        int64_t T, int64_t P, int64_t S, int64_t* tdev, hipStream_t st) {
+  const int64_t bytes[6] = {packed_b_elems(s) * 2,        cq_bytes(s), bsc_floats(s.KP) * 4, bsc_floats(s.KP) * 4,
+                            (int64_t)s.KP * s.KP * 8, (int64_t)s.KP * s.Mpad * 8};
+  void* const p[6] = {Bq, Cq, Bsc, Csc, V, W};
+  ZeroSpans z;
+  int64_t most = 0;
+  for (int q = 0; q < 6; ++q) {
+    z.p[q] = static_cast<f32x4*>(p[q]);
+    z.n[q] = bytes[q] / 16;
+    most = std::max(most, z.n[q]);
+  }
+  const int64_t blocks = std::min<int64_t>((most + 255) / 256, 2048);
+  k_static_setup<<<(unsigned)(blocks + 1), 256, 0, st>>>(z, tb, T, P, S, tdev);
   return hipGetLastError();
 }
 
@@ -1563,10 +1584,11 @@ hipError_t bupdate(const Shape& s, float* B, const double* W, const double* V, _
 // E order of 256 columns of C (block bid).
 template <int KP>
 __global__ __launch_bounds__(256) void k_packc(const float* __restrict__ C, f32x4* __restrict__ Cq, int64_t N, int K) {
-  extern __shared__ float Ct[];  // 256 * K floats
+  constexpr int J = 32 * kPackTiles;
+  extern __shared__ float Ct[];  // J * K floats
   __shared__ int cs[256];
-  const int64_t j0 = (int64_t)blockIdx.x * 256;
-  const int nv = (int)((N - j0) < 256 ? (N - j0) : 256);
+  const int64_t j0 = (int64_t)blockIdx.x * J;
+  const int nv = (int)((N - j0) < J ? (N - j0) : J);
   block_copy(Ct, C + j0 * K, nv * K);
   __syncthreads();
   pack_block<KP>(Cq, j0, nv, Ct, K, (N + 31) / 32, cs);
@@ -1607,12 +1629,13 @@ hipError_t sweep(const Shape& s, const float* Hin, float* C, void* Cq, float* Cs
 }
 
 hipError_t packc(const Shape& s, const float* C, void* Cq, hipStream_t st) {
-  const unsigned g = (unsigned)((s.N + 255) / 256);
+  constexpr int J = 32 * kPackTiles;
+  const unsigned g = (unsigned)((s.N + J - 1) / J);
   f32x4* q = static_cast<f32x4*>(Cq);
   if (s.KP == 32)
-    k_packc<32><<<g, 256, 256 * s.K * sizeof(float), st>>>(C, q, s.N, s.K);
+    k_packc<32><<<g, 256, J * s.K * sizeof(float), st>>>(C, q, s.N, s.K);
   else
-    k_packc<64><<<g, 256, 256 * s.K * sizeof(float), st>>>(C, q, s.N, s.K);
+    k_packc<64><<<g, 256, J * s.K * sizeof(float), st>>>(C, q, s.N, s.K);
   return hipGetLastError();
 }
 
@@ -2240,15 +2263,6 @@ hipError_t finish_b(const Shape& s, const double* Gpart, double* G, const float*
     k_finish_b<32><<<g, 256, 0, st>>>(Gpart, P, G, B, s.M, s.K, s.nchunks, Bq, Bsc);
   else
     k_finish_b<64><<<g, 256, 0, st>>>(Gpart, P, G, B, s.M, s.K, s.nchunks, Bq, Bsc);
-  return hipGetLastError();
-}
-
-__global__ void k_set_i64(int64_t* p, int64_t v) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *p = v;
-}
-
-hipError_t set_i64(int64_t* p, int64_t v, hipStream_t st) {
-  k_set_i64<<<1, 64, 0, st>>>(p, v);
   return hipGetLastError();
 }
 

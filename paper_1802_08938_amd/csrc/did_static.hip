@@ -126,16 +126,9 @@ int did_iterate_static(const float* X, int64_t M, int64_t N, int32_t K, float* B
   c.hist_cap = f ? std::max<int64_t>(n, 1) : 1;
   const Shape& s = c.s;
   hipError_t e;
-  // the workspace keeps the last call's contents: clear the zero-padded packed operands
-  // and the maxima (fill kernels, no memset nodes, so that the call can be captured)
-  if ((e = didk::zero16(c.Bq, didk::packed_b_elems(s) * 2, c.st)) != hipSuccess ||
-      (e = didk::zero16(c.Cq, didk::cq_bytes(s), c.st)) != hipSuccess ||
-      (e = didk::zero16(c.Bsc, (int64_t)didk::bsc_floats(s.KP) * 4, c.st)) != hipSuccess ||
-      (e = didk::zero16(c.Csc, (int64_t)didk::bsc_floats(s.KP) * 4, c.st)) != hipSuccess ||
-      (e = didk::zero16(c.V, (int64_t)s.KP * s.KP * 8, c.st)) != hipSuccess ||
-      (e = didk::zero16(c.W, (int64_t)s.KP * s.Mpad * 8, c.st)) != hipSuccess ||
-      (e = didk::ranges_on_device(c.rbounds, p.T, p.P, p.S, c.st)) != hipSuccess ||
-      (e = didk::set_i64(c.tdev, 0, c.st)) != hipSuccess ||
+  // the workspace keeps the last call's contents
+  if ((e = didk::static_setup(s, c.Bq, c.Cq, c.Bsc, c.Csc, c.V, c.W, c.rbounds, p.T, p.P, p.S, c.tdev, c.st)) !=
+          hipSuccess ||
       (e = refresh_b_derived(&c)) != hipSuccess || (e = pack_c(&c)) != hipSuccess)
     return dev_fail(nullptr, e, "did_iterate_static setup");
   rc = iterate_mfma(&c, n);
