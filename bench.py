@@ -319,10 +319,9 @@ def launch_floor(torch, n_kernels, replays=200):
     return ev0.elapsed_time(ev1) / replays
 
 
-# kernels one iteration of the MFMA path launches: column pass, f reduction, clearing of
-# the C maxima, sweep, W-order packing, V partials, V reduction, row pass, W reduction,
-# clearing of the B maxima, B update, H-order packing, G reduction
-KERNELS_PER_ITERATION = 13
+# kernels one iteration of the MFMA path launches: column pass, sweep, W-order packing with V
+# partials and f, row pass, W and V sums, B update, G sum with the H-order packing
+KERNELS_PER_ITERATION = 7
 
 
 def emit(torch, line):

@@ -1,13 +1,16 @@
 // gfx950 kernels of the DID engine.
 //
 // One DID iteration (Alg. 3 of Gao & Chu, AAAI-18) is carried out as
-//   colpass column pass over X: E = X - B C (MFMA), f partial = sum E^2 (float64),
-//           H = B^T E (MFMA),
-//   sweep   the coordinate sweep over the rows of C (float64),
-//   vgram   V = tril(C C^T) partials of the updated C (MFMA, float64 sums),
-//   rowpass row pass over X: E' = X - B C' (MFMA) and W = E' C'^T per column range (MFMA),
-//   reduce  fixed-order sums of the V, W and f partials (the paper's one Allreduce),
-//   bupdate incremental update of the columns of B, one thread per row of B.
+//   colpass  column pass over X: E = X - B C (MFMA), f partials = sum E^2 (float64),
+//            H = B^T E (MFMA), by shares of the rows where X is narrow,
+//   sweep    the coordinate sweep over the rows of C (float64 MFMA chain), and C's E order,
+//   packv    C's W order, V = tril(C C^T) partials of the updated C (MFMA, float64 sums); the
+//            last block sums the f partials,
+//   rowpass  row pass over X: E' = X - B C' (MFMA) and W = E' C'^T per column range (MFMA),
+//   reduce   fixed-order sums of the W and V partials (the paper's one Allreduce),
+//   bupdate  incremental update of the columns of B (the sweep's chain, a wave per 16 rows),
+//            B's E order, partials of G = B^T B,
+//   finish   the sum of G's partials, and B's H order.
 // Every MFMA product is float32-accurate: each float32 operand is split into two fp16
 // pieces under a power-of-two scale and each product is formed from three fp16 MFMAs
 // (split2 and mfma_x3 below).
@@ -450,10 +453,10 @@ hipError_t validate(const float* p, int64_t n, int vec4, int* flag, hipStream_t 
 //       B[32c + row32(8q + t, l/32)][kk] * 2^u_kk, kk = 32b + l%32, with
 //       u_kk = scale_exp(max_m B[m][kk])   (A operand of H = B^T E);
 //   units c*UC + 2*UE + u, u < 8: 2^-s_m of rows m = 32c + 4u + e (float32, element e).
-// The per-row part is written by the B update (one thread per row); the per-column part
+// The per-row part is written by the B update; the per-column part
 // needs the column maxima over all rows, which the B update gathers into Bsc[0, KP) with
 // atomic maxima (exact, so the result does not depend on the order), and is written by
-// k_packh afterwards, which also stores 2^-u_kk into Bsc[KP + kk].
+// k_finish_b afterwards, which also stores 2^-u_kk into Bsc[KP + kk].
 constexpr int kBupRows = 64;  // rows of B per block of the update
 
 // H-order units of the two chunks 2*bid, 2*bid + 1 from B and the column maxima in
@@ -563,14 +566,18 @@ __global__ void k_zero_f32(float* p, int n) {
 // Rout (rvec4: 16-byte stores are aligned), so that the row pass can carry it on.  The
 // source X is then either the data (refresh) or Rout itself (carry: E = R - delta B C).
 //
-// The B run goes from global memory straight into LDS (global_load_lds_dwordx4: no staging
-// registers).  The chunk's closing barrier must wait for it, but not for the X tile of the
+// The B run goes from global memory straight into LDS (16 bytes a lane, no staging registers).  The chunk's closing barrier must wait for it, but not for the X tile of the
 // next chunk, whose loads are issued after it: stage_barrier leaves the last NX loads (those
 // of the X tile) in flight.  With __syncthreads, which waits for every load, each chunk waited
 // out the X tile's latency.
 // us per column pass before and after: 5000 x 10^6, K = 50, tiled float32: 4922, 4474 (and three
 // waves per SIMD, the staging registers gone); bf16 5000 x 62500: 286, 271; 24 jobs in a batch, K
 // <= 32: 398, 356.
+//
+// What bounds it now: large float32 X in tile order, memory (5000 x 10^6, K = 50: 21.9 GB counted
+// at 4.9 TB/s, 12 jobs of a serving run, K <= 32, 4.75 TB/s of X; a large copy reaches 4.75);
+// K > 32 with X in bf16, the matrix units and the clock they leave (24 MFMAs per chunk and wave:
+// busy 46 % of the cycles at 1.9 GHz; at 5000 x 10^6 58 % at 1.43 GHz); small X, latency.
 template <typename XT>
 struct x_loads {  // loads of one X tile per lane where their number is fixed, else 0
   static constexpr int value = std::is_same<XT, xtf32>::value ? 4 : (std::is_same<XT, __bf16>::value ? 2 : 0);
