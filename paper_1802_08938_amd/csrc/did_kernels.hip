@@ -308,6 +308,16 @@ hipError_t scale(float* p, int64_t n, float a, hipStream_t st) {
 // loads of memory known not to change would move across).
 __device__ __forceinline__ void load_order() { asm volatile("" ::: "memory"); }
 
+// threadIdx.x, anew for each item of a grouped kernel: what follows from it (lane addresses in
+// LDS and the like) would otherwise be computed ahead of the loop over the items and held in
+// registers beside the item's own (grouped column pass, K > 32: 240 VGPRs, now 160; W-order
+// packing 256 and spills, now 220; us in one batch of 24 jobs 479, 462, and, K <= 32, 33.9, 24.5).
+__device__ __forceinline__ int item_tid() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 // ------------------------------------------------------------------ tiled storage of X
 // Both tiled copies of X (layout in did_kernels.h), elements of type ET (bf16 rounded to
 // nearest even, or float32), zero outside M x N; and the check of its entries: flag |= 1 if
@@ -635,7 +645,7 @@ __device__ __forceinline__ void colpass_body(const XT* X, int64_t M, int64_t N, 
   __shared__ f32x4 sb0[U], sb1[U];  // the two stages of B
   __shared__ double fw[WPB];
   // the wave index is uniform: from a scalar register, so that wave-based addresses stay scalar
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, half = l >> 5,
+  const int tid = KP > 32 ? item_tid() : threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, half = l >> 5,
             lc = l & 31;
   // block bid: share bid / ncb of the rows (chunks c0 .. c1 - 1) of column block bid % ncb
   const int64_t ncb = (N + 32 * WPB - 1) / (32 * WPB), share = bid / ncb;
@@ -1679,7 +1689,7 @@ __device__ __forceinline__ void packv_body(PackvLds<KP>& S, const float* __restr
   constexpr int UT = CqL<KP>::T;
   constexpr int NBL = NB * (NB + 1) / 2;  // lower blocks (b1 >= b2)
   // the wave index is uniform: from a scalar register, so that wave-based addresses stay scalar
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, half = l >> 5,
+  const int tid = item_tid(), wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, half = l >> 5,
             lc = l & 31;
   const int NP = g_pairs(K);
   const int64_t ntiles = (N + 31) / 32, per = (ntiles + nblk - 1) / nblk;
