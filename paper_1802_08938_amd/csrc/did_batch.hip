@@ -157,7 +157,6 @@ void fill_inst(GInst& d, did_ctx* h, double* fcur) {
   d.colblocks = didk::colpass_blocks(s);
   d.bupblocks = didk::bupdate_blocks(s);
   d.K = s.K;
-  d.vec4 = s.vec4;
   d.R = h->R;
   d.nsg = (int)((s.nchunks + 3) / 4);
   d.csplit = s.csplit;

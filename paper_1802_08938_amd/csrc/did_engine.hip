@@ -444,11 +444,9 @@ int setup(did_ctx* h, const void* Xv, int64_t M, int64_t N, int32_t K, const did
   if (s.xtiled) {
     h->X = xb;
     h->XR = xb + te * esz;
-    s.vec4 = 0;  // the tiled copies are read with their own full-width loads
   } else {
     h->X = const_cast<float*>(xin);
     h->XR = h->X;
-    s.vec4 = v4;
   }
 
   const int NP = didk::n_pairs(s.KP);

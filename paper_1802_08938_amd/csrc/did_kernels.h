@@ -13,7 +13,6 @@ struct Shape {
   int KP;            // K padded to the MFMA output tile (32 or 64)
   int64_t nchunks;   // ceil(M / 32): 32-row chunks of the basis
   int64_t Mpad;      // nchunks * 32
-  int vec4;          // vector loads of X are aligned (M % 4 == 0 and X aligned)
   int xbf16;         // X is stored as bf16 (reduced-precision storage form), else float32
   int xtiled;        // X is stored in tile order (always for bf16; float32 on request)
   int thin;          // thin-matrix path (M <= 16, K <= 8, M <= 8 or K <= 4): one fused pass per iteration
@@ -205,7 +204,7 @@ struct GInst {
   int64_t* tdev;  // iteration counter (index into fhist)
   double* fcur;   // latest objective, for the host
   int64_t M, N, nchunks, Mpad, hist_cap, vblocks, colblocks, bupblocks;
-  int K, vec4, R, nsg, csplit;
+  int K, R, nsg, csplit;
 };
 
 struct GTable {

@@ -637,7 +637,7 @@ template <int KP, bool WITH_H, typename XT, bool RW = false, int WPB = 4>
 __device__ __forceinline__ void colpass_body(const XT* X, int64_t M, int64_t N, int K,
                                              const f32x4* __restrict__ Cq, const _Float16* __restrict__ Bq,
                                              float* Bsc, float* __restrict__ Csc, float* __restrict__ Hout,
-                                             double* __restrict__ fpart, int64_t nchunks, int vec4, int csplit,
+                                             double* __restrict__ fpart, int64_t nchunks, int csplit,
                                              int64_t bid, const _Float16* __restrict__ BqE = nullptr,
                                              float* Rout = nullptr, int rvec4 = 0) {
   constexpr int NB = KP / 32;
@@ -913,8 +913,8 @@ __global__ __launch_bounds__(64 * WPB, 8 / WPB) void k_colpass(const XT* X, int6
                                                                const _Float16* __restrict__ Bq,
                                                                float* Bsc, float* __restrict__ Csc,
                                                                float* __restrict__ Hout, double* __restrict__ fpart,
-                                                               int64_t nchunks, int vec4, int csplit) {
-  colpass_body<KP, WITH_H, XT, false, WPB>(X, M, N, K, Cq, Bq, Bsc, Csc, Hout, fpart, nchunks, vec4, csplit, blockIdx.x);
+                                                               int64_t nchunks, int csplit) {
+  colpass_body<KP, WITH_H, XT, false, WPB>(X, M, N, K, Cq, Bq, Bsc, Csc, Hout, fpart, nchunks, csplit, blockIdx.x);
 }
 
 // The carried-residual form of the column pass (always forms H).
@@ -923,9 +923,9 @@ __global__ __launch_bounds__(256, 2) void k_colpass_rw(const XT* X, int64_t M, i
                                                        const f32x4* __restrict__ Cq, const _Float16* __restrict__ Bq,
                                                        const _Float16* __restrict__ BqE,
                                                        float* Bsc, float* __restrict__ Csc, float* __restrict__ Hout,
-                                                       double* __restrict__ fpart, int64_t nchunks, int vec4,
-                                                       int csplit, float* R, int rvec4) {
-  colpass_body<KP, true, XT, true>(X, M, N, K, Cq, Bq, Bsc, Csc, Hout, fpart, nchunks, vec4, csplit, blockIdx.x, BqE, R,
+                                                       double* __restrict__ fpart, int64_t nchunks, int csplit,
+                                                       float* R, int rvec4) {
+  colpass_body<KP, true, XT, true>(X, M, N, K, Cq, Bq, Bsc, Csc, Hout, fpart, nchunks, csplit, blockIdx.x, BqE, R,
                                    rvec4);
 }
 
@@ -966,14 +966,14 @@ static void colpass_launch_w(const Shape& s, const XT* X, const f32x4* C, const 
   const unsigned g = (unsigned)colpass_blocks(s);
   if (s.KP == 32) {
     if (with_h)
-      k_colpass<32, true, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Csc, Hout, fpart, s.nchunks, s.vec4, s.csplit);
+      k_colpass<32, true, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Csc, Hout, fpart, s.nchunks, s.csplit);
     else
-      k_colpass<32, false, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Csc, Hout, fpart, s.nchunks, s.vec4, s.csplit);
+      k_colpass<32, false, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Csc, Hout, fpart, s.nchunks, s.csplit);
   } else {
     if (with_h)
-      k_colpass<64, true, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Csc, Hout, fpart, s.nchunks, s.vec4, s.csplit);
+      k_colpass<64, true, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Csc, Hout, fpart, s.nchunks, s.csplit);
     else
-      k_colpass<64, false, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Csc, Hout, fpart, s.nchunks, s.vec4, s.csplit);
+      k_colpass<64, false, XT, WPB><<<g, 64 * WPB, 0, st>>>(X, s.M, s.N, s.K, C, Bq, Bsc, Csc, Hout, fpart, s.nchunks, s.csplit);
   }
 }
 
@@ -987,15 +987,15 @@ static void colpass_launch(const Shape& s, const XT* X, const f32x4* C, const _F
 }
 
 template <typename XT>
-static void colpass_rw_launch(const Shape& s, const XT* X, int vec4, const f32x4* C, const _Float16* Bq,
+static void colpass_rw_launch(const Shape& s, const XT* X, const f32x4* C, const _Float16* Bq,
                               const _Float16* BqE, float* Bsc, float* Csc, float* Hout, double* fpart, float* R,
                               hipStream_t st) {
   const unsigned g = (unsigned)colpass_blocks(s);
   const int rvec4 = (s.M % 4 == 0) && ((reinterpret_cast<uintptr_t>(R) & 15) == 0);
   if (s.KP == 32)
-    k_colpass_rw<32, XT><<<g, 256, 0, st>>>(X, s.M, s.N, s.K, C, Bq, BqE, Bsc, Csc, Hout, fpart, s.nchunks, vec4, s.csplit, R, rvec4);
+    k_colpass_rw<32, XT><<<g, 256, 0, st>>>(X, s.M, s.N, s.K, C, Bq, BqE, Bsc, Csc, Hout, fpart, s.nchunks, s.csplit, R, rvec4);
   else
-    k_colpass_rw<64, XT><<<g, 256, 0, st>>>(X, s.M, s.N, s.K, C, Bq, BqE, Bsc, Csc, Hout, fpart, s.nchunks, vec4, s.csplit, R, rvec4);
+    k_colpass_rw<64, XT><<<g, 256, 0, st>>>(X, s.M, s.N, s.K, C, Bq, BqE, Bsc, Csc, Hout, fpart, s.nchunks, s.csplit, R, rvec4);
 }
 
 hipError_t colpass_carry(const Shape& s, const void* X, int refresh, const void* Cqv, const _Float16* Bq,
@@ -1003,14 +1003,13 @@ hipError_t colpass_carry(const Shape& s, const void* X, int refresh, const void*
                          hipStream_t st) {
   const f32x4* C = static_cast<const f32x4*>(Cqv);
   if (!refresh) {  // E = R - delta B C, in place
-    const int v4 = (s.M % 4 == 0) && ((reinterpret_cast<uintptr_t>(R) & 15) == 0);
-    colpass_rw_launch(s, static_cast<const float*>(R), v4, C, Bq, BqD, Bsc, Csc, Hout, fpart, R, st);
+    colpass_rw_launch(s, static_cast<const float*>(R), C, Bq, BqD, Bsc, Csc, Hout, fpart, R, st);
   } else if (s.xbf16) {  // E = X - B C from the stored data
-    colpass_rw_launch(s, static_cast<const __bf16*>(X), 0, C, Bq, Bq, Bsc, Csc, Hout, fpart, R, st);
+    colpass_rw_launch(s, static_cast<const __bf16*>(X), C, Bq, Bq, Bsc, Csc, Hout, fpart, R, st);
   } else if (s.xtiled) {
-    colpass_rw_launch(s, static_cast<const xtf32*>(X), 0, C, Bq, Bq, Bsc, Csc, Hout, fpart, R, st);
+    colpass_rw_launch(s, static_cast<const xtf32*>(X), C, Bq, Bq, Bsc, Csc, Hout, fpart, R, st);
   } else {
-    colpass_rw_launch(s, static_cast<const float*>(X), s.vec4, C, Bq, Bq, Bsc, Csc, Hout, fpart, R, st);
+    colpass_rw_launch(s, static_cast<const float*>(X), C, Bq, Bq, Bsc, Csc, Hout, fpart, R, st);
   }
   return hipGetLastError();
 }
@@ -2334,8 +2333,7 @@ __global__ __launch_bounds__(64 * WPB, 8 / WPB) void kg_colpass(const GTable* __
   // loads, and the passes count theirs
   colpass_body<KP, true, XT, false, WPB>(as_global(static_cast<const XT*>(d.X)), d.M, d.N, d.K,
                                          as_global(static_cast<const f32x4*>(d.Cq)), as_global(d.Bq), as_global(d.Bsc),
-                                         as_global(d.Csc), as_global(d.H), as_global(d.fpart), d.nchunks, d.vec4,
-                                         d.csplit, bid);
+                                         as_global(d.Csc), as_global(d.H), as_global(d.fpart), d.nchunks, d.csplit, bid);
   DID_GROUP_END
 }
 

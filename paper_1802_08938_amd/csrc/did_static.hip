@@ -118,7 +118,6 @@ int did_iterate_static(const float* X, int64_t M, int64_t N, int32_t K, float* B
   c.use_graph = false;  // a graph would allocate
   c.X = const_cast<float*>(X);
   c.XR = c.X;
-  c.s.vec4 = (M % 4 == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0);
   c.B = B;
   c.C = C;
   c.R = (int)p.R;
