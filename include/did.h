@@ -94,8 +94,9 @@ enum {
  *   algorithm      DID_ALG_DID (default) or DID_ALG_DBCD.  DBCD is available on the
  *                  thin-matrix path only (DID_EINVAL otherwise).
  *   row_blocks     tile shape of the row pass along N: about this many (column range,
- *                  32-row slab group) blocks per launch, which sets the number of column
- *                  ranges whose W partials are summed (in ascending order).  0 takes the
+ *                  32-row slab group) blocks per launch (past 512 rounded up to an even load
+ *                  of the compute units; fewer where X is narrow), which sets the number of
+ *                  column ranges whose W partials are summed (in ascending order).  0 takes the
  *                  value did_autotune recorded for the instance's shape class, else
  *                  N / 256 clamped to [512, 4096].
  *                  Results depend on it only through summation order.

@@ -190,20 +190,26 @@ WorkPlan plan_work(Shape& s, int n_blocks, int row_blocks) {
   // resident blocks (5000 x 10^6: 9.77 ms per iteration at 4096 against 10.98 at 512),
   // narrower X fewer, longer ranges, whose W partials cost less to write and sum
   // (500 x 150000: 0.258 ms at 512 against 0.303 at 4096).
-  // Rounded down to whole blocks per CU, as are the ranges: a few blocks more than two per CU
-  // make some CUs run three (bf16 5000 x 62500: 520 blocks 287 us, 480 blocks 246; 1868 x
-  // 40000, K = 60: 525 blocks 104 us, 510 blocks 85).
-  int64_t target = row_blocks > 0 ? row_blocks : std::min<int64_t>(4096, std::max<int64_t>(512, s.N / 256));
-  if (target > 256) target = target / 256 * 256;
-  const int64_t want = std::max<int64_t>(1, target / slab_groups);
+  const int64_t target = row_blocks > 0 ? row_blocks : std::min<int64_t>(4096, std::max<int64_t>(512, s.N / 256));
+  const int64_t need = (target + slab_groups - 1) / slab_groups, blocks = need * slab_groups;
+  // A few blocks more than two per CU make some CUs run three: rounded up to a whole number
+  // of blocks per CU up to three, past that to whole rounds of the blocks the GPU holds (three
+  // per CU, four for K <= 32 in tile order).  us per row pass at the rounded-down and the
+  // plain number and now: bf16 5000 x 62500, K = 50: 240, 282, 226; 784 x 70000, K = 16: 51, 57,
+  // 44; 1868 x 40000, K = 60: 81, 102, 82; 33000 x 20000, K = 20: 876, 664, 665; tiled 5000 x
+  // 10^6, K = 50: 4375, 4515, 4365.  Never rounded down: each float32 partial of W would sum
+  // more columns (B off the 64-bit result after one iteration: 1.03e-6 at bf16 5000 x 62500 and
+  // 3.9e-6 at 33000 x 20000, rounded up 6.8e-7 and 2.1e-6).
+  const int64_t unit = blocks <= 768 ? 256 : (s.KP == 32 && s.xtiled ? 1024 : 768);
+  const int64_t want = blocks <= 512 ? need : (blocks + unit - 1) / unit * unit / slab_groups;
   // Ranges of at least max(4, K / 6) tiles, where the W partials (written and read: 8 K M
   // bytes a range) come to about 40 % of a range's X.  With 16 tiles a narrow X left the row
   // pass a few dozen blocks; us per row pass at 16, 8 and 4 tiles: 500 x 2000, K = 10: 31.2,
   // 16.2, 11.2; 600 x 9000, K = 40: 35.2, 22.0, 18.6; 3809 x 2248, K = 49: 36.4, 31.4, 31.2.
   // 24 uneven jobs in one batch pay for their partials instead (row passes and W sums 886,
   // 925, 927 us).
-  auto ranges = [&](int64_t least, int64_t* S) {
-    const int64_t n = std::max<int64_t>(1, std::min<int64_t>(want, std::max<int64_t>(1, T / least)));
+  auto ranges = [&](int64_t count, int64_t least, int64_t* S) {
+    const int64_t n = std::max<int64_t>(1, std::min<int64_t>(count, std::max<int64_t>(1, T / least)));
     *S = std::max<int64_t>(1, (n + w.P - 1) / w.P);
     return didk::range_bounds(T, w.P, *S, nullptr);
   };
@@ -211,10 +217,10 @@ WorkPlan plan_work(Shape& s, int n_blocks, int row_blocks) {
   // write: an instance's footprint stays what pools and budgets were sized for)
   const int64_t vbytes = std::min<int64_t>(T, 256) * NP * 8, nb = (s.N + 127) / 128;
   int64_t S0;
-  const int64_t R0 = ranges(16, &S0);
+  const int64_t R0 = ranges(need, 16, &S0);
   const int64_t bound = s.KP * s.N * 4 + vbytes + R0 * s.KP * s.Mpad * 4 + R0 * 8;
   auto rows = [&](int64_t R) { return (R * s.K * s.Mpad * 4 + 255) / 256 * 256; };
-  w.R = ranges(std::max<int64_t>(4, s.K / 6), &w.S);
+  w.R = ranges(want, std::max<int64_t>(4, s.K / 6), &w.S);
   while (w.S > S0 && rows(w.R) + vbytes + w.R * 8 + 16384 > bound)  // (16 kB: more f partials)
     w.R = didk::range_bounds(T, w.P, --w.S, nullptr);
   const int64_t hs = didk::h_stride(s.N, s.K) * 4 + nb * 8;  // a share's H and f partials
