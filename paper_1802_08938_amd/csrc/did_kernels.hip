@@ -1054,7 +1054,8 @@ hipError_t colpass(const Shape& s, const void* X, const void* Cqv, const _Float1
 // Division: h / G_kk is formed from the correctly rounded reciprocal, one residual fma and
 // one correction (Markstein's method: the correctly rounded quotient, so that cancellations
 // the closed form makes exact stay exact), with v_div_fixup for the special operands.  A
-// skipped coordinate takes G_kk = inf: its quotient is 0.
+// skipped coordinate takes G_kk = inf: its quotient is 0 (NaN where h overflowed) and its change
+// is held to 0.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // 4 x 4 transpose of x[0..3] across the wave's four rows of 16 lanes: x[i] of row g becomes
@@ -1133,8 +1134,8 @@ __device__ __forceinline__ void tri_stage(TriOps<NT>& o, const double* __restric
 
 // The four coordinates of one step for one line: sums hv, old values co (float32); returns
 // the new float32 values in cn and minus the float64 changes in d.  The change is formed as
-// max(h / A_ii, -old) (what [old + h / A_ii]_+ - old is), which keeps the dependent chain at
-// six operations per coordinate.
+// max(h / A_ii, -old) (what [old + h / A_ii]_+ - old is; at least 0 for a skipped coordinate),
+// which keeps the dependent chain at six operations per coordinate.
 __device__ __forceinline__ void tri_step(const double (&gd)[14], double (&hv)[4], const f32x4& co, f32x4& cn,
                                          double (&d)[4]) {
 #pragma unroll
@@ -1143,7 +1144,8 @@ __device__ __forceinline__ void tri_step(const double (&gd)[14], double (&hv)[4]
     double q = hv[i] * gd[i];
     q = fma(fma(-q, gd[4 + i], hv[i]), gd[i], q);
     q = __builtin_amdgcn_div_fixup(q, gd[4 + i], hv[i]);
-    const double c = q > -old ? q : -old;
+    const double lo = gd[i] > 0.0 ? -old : 0.0;
+    const double c = q > lo ? q : lo;
     cn[i] = (float)(old + c);
     d[i] = -c;
 #pragma unroll
