@@ -524,7 +524,7 @@ int objective_pass(did_ctx* h) {
   if (h->s.thin) {
     if ((e = didk::thin_pass(h->s, static_cast<const float*>(h->X), h->B, h->G, h->C, h->tpart, 1, h->st)) !=
             hipSuccess ||
-        (e = didk::thin_finish(h->s, h->tpart, h->B, h->G, h->fobj, 0, h->st)) != hipSuccess)
+        (e = didk::reduce_f(h->tpart, didk::thin_blocks(h->s), h->fobj, 0.5, h->st)) != hipSuccess)
       return dev_fail(h, e, "objective pass");
     return DID_OK;
   }
@@ -865,9 +865,10 @@ static int iterate_thin(did_ctx* h, int32_t n) {
     if ((e = didk::thin_pass(s, X, h->B, h->G, h->C, h->tpart, mode, h->st)) != hipSuccess)
       return dev_fail(h, e, "thin column pass");
     if ((e = mark(1)) != hipSuccess) return dev_fail(h, e, "profile record");
-    // the partials' sums and f; for DID also the B update and G
-    if ((e = didk::thin_finish(s, h->tpart, h->B, h->G, h->fhist + (h->t % h->hist_cap), mode == 0, h->st)) !=
-        hipSuccess)
+    // DID: the partials' sums, f, the B update and G; DBCD: f
+    double* const f = h->fhist + (h->t % h->hist_cap);
+    if ((e = mode == 0 ? didk::thin_finish(s, h->tpart, h->B, h->G, f, h->st)
+                       : didk::reduce_f(h->tpart, didk::thin_blocks(s), f, 0.5, h->st)) != hipSuccess)
       return dev_fail(h, e, "thin finish");
     // the thin path has no separate sweep, V or row pass: their stages are empty
     for (int q = 2; q <= 6; ++q)

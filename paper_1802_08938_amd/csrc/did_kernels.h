@@ -226,13 +226,12 @@ hipError_t group_iteration(int KP, int xkind, int cwpb, const GTable* dtab, cons
                            hipStream_t st);
 
 // ---- thin-matrix path (did_thin.hip) ----
-// mode 0: DID column work (sweep, W/V/f block partials); 1: objective partials only;
-// 2: DBCD C half (sweep, f partials).
+// mode 0: DID column work (sweep, W/V/f block partials); 1: objective partials only (one double
+// per block); 2: DBCD C half (sweep, f partials as in mode 1).
 hipError_t thin_pass(const Shape& s, const float* X, const float* B, const double* G, float* C, double* part,
                      int mode, hipStream_t st);
-// from the block partials: *fout = f, and with full = 1 the B update and G = B^T B
-hipError_t thin_finish(const Shape& s, const double* part, float* B, double* G, double* fout, int full,
-                       hipStream_t st);
+// from the block partials of mode 0: *fout = f, the B update and G = B^T B
+hipError_t thin_finish(const Shape& s, const double* part, float* B, double* G, double* fout, hipStream_t st);
 // one DBCD column update b_i (a pass over X and a reduction); yz holds M + 1 doubles of
 // scratch (at least 17)
 hipError_t dbcd_b_step(const Shape& s, const float* X, float* B, const float* C, double* part, double* yz, int i,

@@ -88,7 +88,7 @@ __global__ __launch_bounds__(256) void k_thin(const float* __restrict__ X, int64
   const int Kr = EXACT ? KK : K;
   __shared__ double Bs[MM * KK];
   __shared__ double nk[KK];
-  __shared__ double red[4][NS];
+  __shared__ double red[4][MODE == 0 ? NS : 1];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   double sums[NS];  // this thread's share of every slot
 #pragma unroll
@@ -159,14 +159,22 @@ __global__ __launch_bounds__(256) void k_thin(const float* __restrict__ X, int64
   const int64_t stride = (int64_t)gridDim.x * 256;
   const int64_t j0 = (int64_t)blockIdx.x * 256 + tid;
   ThinCol<MM, KK> ring[PF];
+  // mode 0 takes B while its first columns are on their way; the others' loops come out slower
+  // so (us at 16 x 10^6, K = 4: DBCD's C half 47.0, B first 42.7; objective call 58.4, 56.2)
+  if (MODE == 0) {
 #pragma unroll
-  for (int p = 0; p < PF; ++p) ring[p] = load(j0 + p * stride);
-  for (int q = tid; q < MM * KK; q += 256) {  // while the first columns are on their way
+    for (int p = 0; p < PF; ++p) ring[p] = load(j0 + p * stride);
+  }
+  for (int q = tid; q < MM * KK; q += 256) {
     const int m = q % MM, k = q / MM;
     Bs[q] = (m < Mr && k < Kr) ? (double)B[(int64_t)k * M + m] : 0.0;
   }
   if (tid < KK) nk[tid] = tid < Kr ? G[tid * KP + tid] : 0.0;
   __syncthreads();
+  if (MODE != 0) {
+#pragma unroll
+    for (int p = 0; p < PF; ++p) ring[p] = load(j0 + p * stride);
+  }
   for (int64_t j = j0; j < N; j += PF * stride) {
 #pragma unroll
     for (int p = 0; p < PF; ++p) {
@@ -177,7 +185,8 @@ __global__ __launch_bounds__(256) void k_thin(const float* __restrict__ X, int64
       process(jj, cur);
     }
   }
-  // block partials: the sums of each wave, then the four waves in order
+  // block partials: the sums of each wave, then the four waves in order (f alone is one value
+  // per block: 13 threads of k_thin_finish's layout took 2 us longer than reduce_f)
   if (MODE == 0) {
     int base, len;
     wave_sums<NS>(sums, lane, base, len);
@@ -186,12 +195,12 @@ __global__ __launch_bounds__(256) void k_thin(const float* __restrict__ X, int64
       if (i < len) red[wave][base + i] = sums[i];
   } else {
     const double v = wave_sum(sums[NS - 1]);
-    if (lane == 0) red[wave][NS - 1] = v;
+    if (lane == 0) red[wave][0] = v;
   }
   __syncthreads();
-  for (int q = tid; q < NS; q += 256)
-    if (MODE == 0 || q == NS - 1)
-      part[(int64_t)blockIdx.x * NS + q] = ((red[0][q] + red[1][q]) + red[2][q]) + red[3][q];
+  constexpr int NOUT = MODE == 0 ? NS : 1;
+  for (int q = tid; q < NOUT; q += 256)
+    part[(int64_t)blockIdx.x * NOUT + q] = ((red[0][q] + red[1][q]) + red[2][q]) + red[3][q];
 }
 
 // Sum of slot q over the P block partials (stride NS), by one wave: lane l adds partials
@@ -213,35 +222,33 @@ __device__ __forceinline__ double slot_sum(const double* __restrict__ part, int6
 }
 
 // The rest of a DID iteration by one block: the fixed-order sums of the P block partials, f,
-// the B update (one thread per row, as the rows are independent) and G = B^T B.  full = 0 sums
-// only f.  (As three launches, one wave per slot, the general B update and G's reduction, this
-// took 14.5 us beside k_thin's 10.7 at N = 10^5; now 3.8 beside 5.3, k_thin's own part from
-// wave_sums and from loading its first columns before B.)
+// the B update (one thread per row, as the rows are independent) and G = B^T B.  (As three
+// launches, one wave per slot, the general B update and G's reduction, this took 14.5 us beside
+// k_thin's 10.7 at N = 10^5; now 3.8 beside 5.3, k_thin's own part from wave_sums and from
+// loading its first columns before B.)
 template <int MM, int KK>
 __global__ __launch_bounds__(1024) void k_thin_finish(const double* __restrict__ part, int64_t P, int64_t M, int K,
                                                       int KP, float* __restrict__ B, double* __restrict__ G,
-                                                      double* __restrict__ fout, int full) {
+                                                      double* __restrict__ fout) {
   constexpr int NS = thin_ns(MM, KK), NG = 1024 / NS;  // NG groups of NS threads, a slot each
   __shared__ double acc[NG * NS], S[NS];
   __shared__ float Bn[MM * KK];
   const int tid = threadIdx.x, q = tid % NS, grp = tid / NS;
   if (grp < NG) {
     double s = 0.0;
-    if (full || q == NS - 1) {
-      constexpr int U = 8;  // loads issued ahead of the additions
-      int64_t p = grp;
-      for (; p + (U - 1) * NG < P; p += U * NG) {
-        double v[U];
+    constexpr int U = 8;  // loads issued ahead of the additions
+    int64_t p = grp;
+    for (; p + (U - 1) * NG < P; p += U * NG) {
+      double v[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = part[(p + u * NG) * NS + q];
+      for (int u = 0; u < U; ++u) v[u] = part[(p + u * NG) * NS + q];
 #pragma unroll
-        for (int u = 0; u < U; ++u) s += v[u];
-      }
-      for (; p < P; p += NG) s += part[p * NS + q];
+      for (int u = 0; u < U; ++u) s += v[u];
     }
+    for (; p < P; p += NG) s += part[p * NS + q];
     acc[tid] = s;
   }
-  if (full && tid < MM * KK) {
+  if (tid < MM * KK) {
     const int m = tid % MM, k = tid / MM;
     Bn[tid] = (m < M && k < K) ? B[(int64_t)k * M + m] : 0.0f;
   }
@@ -253,7 +260,6 @@ __global__ __launch_bounds__(1024) void k_thin_finish(const double* __restrict__
     S[tid] = s;
     if (tid == NS - 1) *fout = 0.5 * s;
   }
-  if (!full) return;
   __syncthreads();
   if (tid < M) {  // b_mi := [b_mi + (w_mi - sum_{k < i} v_ik delta b_mk) / v_ii]_+, i ascending
     double d[KK];
@@ -442,11 +448,10 @@ hipError_t thin_pass(const Shape& s, const float* X, const float* B, const doubl
   return hipGetLastError();
 }
 
-hipError_t thin_finish(const Shape& s, const double* part, float* B, double* G, double* fout, int full,
-                       hipStream_t st) {
+hipError_t thin_finish(const Shape& s, const double* part, float* B, double* G, double* fout, hipStream_t st) {
   const int64_t P = thin_blocks(s);
 #define DID_THIN_FIN(MM, KK, EX) \
-  k_thin_finish<MM, KK><<<1, 1024, 0, st>>>(part, P, s.M, s.K, s.KP, B, G, fout, full);
+  k_thin_finish<MM, KK><<<1, 1024, 0, st>>>(part, P, s.M, s.K, s.KP, B, G, fout);
   DID_THIN_SHAPES(DID_THIN_FIN)
 #undef DID_THIN_FIN
   return hipGetLastError();
