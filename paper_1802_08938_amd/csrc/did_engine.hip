@@ -528,9 +528,16 @@ int objective_pass(did_ctx* h) {
       return dev_fail(h, e, "objective pass");
     return DID_OK;
   }
-  if ((e = didk::colpass(h->s, h->X, h->Cq, h->Bq, h->Bsc, h->Csc, h->H, h->fpart, 0, h->st)) != hipSuccess)
+  Shape s = h->s;
+  // Without H to form, shares of fewer than 11 chunks of X in tile order cost more than the even
+  // load gives where the column blocks fill the GPU anyway.  us per objective call whole and at
+  // the iterations' shares: bf16 455 x 82379, K = 4: 38.7, 43.4; 600 x 75000, K = 2: 40.9, 44.2;
+  // tiled float32 48.2, 51.8 and 53.0, 54.5; 784 x 70000, K = 16 (13 chunks): 61.4, 60.5; X as
+  // given 62.7, 61.6 at 455 x 82379.
+  if (s.xtiled && s.nchunks < 11 * s.csplit && didk::colpass_blocks(s) >= 512 * (int64_t)s.csplit) s.csplit = 1;
+  if ((e = didk::colpass(s, h->X, h->Cq, h->Bq, h->Bsc, h->Csc, h->H, h->fpart, 0, h->st)) != hipSuccess)
     return dev_fail(h, e, "objective pass");
-  if ((e = didk::reduce_f(h->fpart, didk::colpass_blocks(h->s), h->fobj, 0.5, h->st)) != hipSuccess)
+  if ((e = didk::reduce_f(h->fpart, didk::colpass_blocks(s), h->fobj, 0.5, h->st)) != hipSuccess)
     return dev_fail(h, e, "objective reduce");
   return DID_OK;
 }
