@@ -334,7 +334,8 @@ int setup(did_ctx* h, const void* Xv, int64_t M, int64_t N, int32_t K, const did
     const bool xdev0 = is_device_ptr(Xv);
     const bool x_copied = !s.xtiled && !(xdev0 && o.borrow_x);
     const size_t cap = (size_t)engine_bytes(s, w, x_copied, o.refresh_every) +
-                       64 * (256 + (h->guards ? (size_t)DID_GUARD_ZONE_BYTES : 0));
+                       64 * (256 + (h->guards ? (size_t)DID_GUARD_ZONE_BYTES : 0)) +
+                       (h->guards && !s.thin ? (size_t)w.bytes : 0);  // (the partials apart, below)
     void* q = nullptr;
     size_t qcap = cap;
     bool pooled = false;
@@ -469,11 +470,17 @@ int setup(did_ctx* h, const void* Xv, int64_t M, int64_t N, int32_t K, const did
   if (s.thin) {
     if ((rc = dalloc(h, &h->tpart, didk::thin_blocks(s) * didk::thin_slots_for(s)))) return rc;
   } else {
-    unsigned char* work = nullptr;
-    if ((rc = dalloc(h, &work, w.bytes))) return rc;
-    h->H = reinterpret_cast<float*>(work);
-    h->Wpart = reinterpret_cast<float*>(work + w.wofs);
-    h->Vpart = reinterpret_cast<double*>(work + w.vofs);
+    if (h->guards) {  // H and the partials of W and V each with a zone of its own
+      if ((rc = dalloc(h, &h->H, didk::h_elems(s)))) return rc;
+      if ((rc = dalloc(h, &h->Wpart, w.R * K * s.Mpad))) return rc;
+      if ((rc = dalloc(h, &h->Vpart, didk::vgram_blocks(s) * didk::g_pairs(s.K)))) return rc;
+    } else {
+      unsigned char* work = nullptr;
+      if ((rc = dalloc(h, &work, w.bytes))) return rc;
+      h->H = reinterpret_cast<float*>(work);
+      h->Wpart = reinterpret_cast<float*>(work + w.wofs);
+      h->Vpart = reinterpret_cast<double*>(work + w.vofs);
+    }
     unsigned char* cq = nullptr;
     if ((rc = dalloc(h, &cq, didk::cq_bytes(s)))) return rc;
     h->Cq = cq;
