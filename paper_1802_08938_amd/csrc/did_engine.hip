@@ -208,19 +208,17 @@ WorkPlan plan_work(Shape& s, int n_blocks, int row_blocks) {
   // 16.2, 11.2; 600 x 9000, K = 40: 35.2, 22.0, 18.6; 3809 x 2248, K = 49: 36.4, 31.4, 31.2.
   // 24 uneven jobs in one batch pay for their partials instead (row passes and W sums 886,
   // 925, 927 us).
-  auto ranges = [&](int64_t count, int64_t least, int64_t* S) {
-    const int64_t n = std::max<int64_t>(1, std::min<int64_t>(count, std::max<int64_t>(1, T / least)));
-    *S = std::max<int64_t>(1, (n + w.P - 1) / w.P);
-    return didk::range_bounds(T, w.P, *S, nullptr);
-  };
+  auto ranges = [&](int64_t count, int64_t least) { return std::min<int64_t>(count, std::max<int64_t>(1, T / least)); };
   // room for a V partial per tile up to 256, of KP coordinates (more than the blocks in use
   // write: an instance's footprint stays what pools and budgets were sized for)
   const int64_t vbytes = std::min<int64_t>(T, 256) * NP * 8, nb = (s.N + 127) / 128;
-  int64_t S0;
-  const int64_t R0 = ranges(need, 16, &S0);
+  const int64_t S0 = (ranges(need, 16) + w.P - 1) / w.P, R0 = didk::range_bounds(T, w.P, S0, nullptr);
   const int64_t bound = s.KP * s.N * 4 + vbytes + R0 * s.KP * s.Mpad * 4 + R0 * 8;
   auto rows = [&](int64_t R) { return (R * s.K * s.Mpad * 4 + 255) / 256 * 256; };
-  w.R = ranges(want, std::max<int64_t>(4, s.K / 6), &w.S);
+  // a shard's share of them, not rounded up past the even load (784 x 70000, K = 16, 4 shards: 784
+  // blocks 64 us, 756 57)
+  w.S = std::max<int64_t>(S0, ranges(want, std::max<int64_t>(4, s.K / 6)) / w.P);
+  w.R = didk::range_bounds(T, w.P, w.S, nullptr);
   while (w.S > S0 && rows(w.R) + vbytes + w.R * 8 + 16384 > bound)  // (16 kB: more f partials)
     w.R = didk::range_bounds(T, w.P, --w.S, nullptr);
   const int64_t hs = didk::h_stride(s.N, s.K) * 4 + nb * 8;  // a share's H and f partials
@@ -783,8 +781,8 @@ static bool iteration_graph(did_ctx* h, int q, hipGraphExec_t& exec, int& rc) {
 // refresh-every-iteration form replay captured ones (hipGraphs kept by the handle).
 //
 // A graph's start and end cost about 8 us between its last kernel and the next graph's first
-// (inside a graph the kernels follow each other at once), so a handle from its 16th iteration
-// on replays kGraphRun iterations at a time.  Instantiating those takes about 60 us, which
+// (inside a graph the kernels follow each other at once), so a call that reaches the handle's
+// 16th iteration, and each later one, replays kGraphRun iterations at a time from its start.  Instantiating those takes about 60 us, which
 // shorter runs do not earn back: us per call of 20 iterations, 500 x 2000, K = 10: 1014 one at
 // a time, 941 four at a time; first call of 5 iterations, 10304 x 575, K = 25: 500, with the
 // longer graph from the start 538.
