@@ -11,7 +11,7 @@ Prints one JSON line:
                  it: HBM (algorithmic bytes against 8 TB/s) or the float32-accurate MFMA
                  peak of its split-fp16 products, whichever time floor is larger; with
                  iter_frac (the whole iteration's algorithmic bytes against 8 TB/s) and
-                 limiter (what the committed SQ counters show stalls the pass),
+                 limiter (what the committed counters show stalls the pass),
   precision_form X stored as bf16 with the residual refreshed every iteration or carried
                  and refreshed every 10: iterations/s, speedup over the plain form, and the
                  objective error against the FP64 oracle (original X and bf16(X)) on the
@@ -74,6 +74,7 @@ PEAK_F16_MFMA_TFLOPS = 2500.0  # MI355X dense fp16 (and bf16) matrix peak
 SPLIT_PRODUCTS = 3
 PEAK_SPLIT_TFLOPS = PEAK_F16_MFMA_TFLOPS / SPLIT_PRODUCTS
 PEAK_HBM_GBS = 8000.0
+COPY_HBM_GBS = 4750.0  # read + write rate of a 4 GiB copy, measured on the card
 # the arithmetic the path computes in: products float32-accurate from three fp16 MFMAs of
 # scaled two-way splits with float32 accumulation; sweep, B update and objective in float64
 DTYPE = "f32 (split-fp16x3 MFMA, fp32 accumulate; fp64 sweep, B update, objective)"
@@ -160,10 +161,11 @@ def measured_traffic(kernel, workload):
         return None
 
 
-def sq_limiter(kernel):
+def sq_limiter(kernel, hbm_gbs=None):
     """What limits a pass, from the committed SQ counter summary (when it was taken on the
     current kernel sources): MFMA busy fraction, non-MFMA VALU instructions per MFMA and
-    the share of wave cycles spent waiting.  None when the summary is stale or absent."""
+    the share of wave cycles spent waiting; and from hbm_gbs, the counted HBM traffic over the
+    pass's time, where that is known.  None when the summary is stale or absent."""
     path = os.path.join(ROOT, "profiles", "sq_counters_large.md")
     if not os.path.exists(path):
         return None
@@ -187,8 +189,10 @@ def sq_limiter(kernel):
     # the two overlap only in part (a wave's VALU work runs beside an MFMA in flight)
     valu_busy = mfma * valu * 4.0 / 32.0
     issue = mfma + valu_busy
-    if issue >= 0.9:
-        kind = "issue (MFMA and VALU pipes saturated)"
+    if hbm_gbs is not None and hbm_gbs >= 0.95 * COPY_HBM_GBS:
+        kind = "memory (counted HBM traffic at the rate a large copy reaches), with the matrix units close behind"
+    elif issue >= 0.9:
+        kind = "issue (MFMA and VALU instructions fill the busy cycles)"
     elif wait >= 0.25:
         kind = "latency and issue (waves wait on memory/LDS while MFMA+VALU fill part of the cycles)"
     else:
@@ -1029,9 +1033,9 @@ def main():
         "iter_frac": round(iter_gbs / PEAK_HBM_GBS, 4), "iter_bytes": cnt["iter_bytes"],
         "iter_note": "iteration algorithmic bytes / ms_per_step / 8 TB/s; the two passes read X twice per "
                      "iteration (the sweep needs whole columns, the W messages whole rows)",
-        "limiter": sq_limiter(dom),
+        "limiter": sq_limiter(dom, None if traffic is None else traffic / secs / 1e9),
         "bound_note": "bound = the roof whose time floor is larger for the pass's algorithmic work; limiter = "
-                      "what the committed SQ counters show stalls the pass (null when they were taken on other "
+                      "what the committed counters show stalls the pass (null when they were taken on other "
                       "kernel sources)",
         "kernel_ms": round(dom_ms, 4), "bytes_per_launch": cnt["pass_bytes"], "flops_per_launch": cnt["pass_flops"],
         "f32_accurate_tflops": round(tflops, 3), "f32_accurate_peak_tflops": round(PEAK_SPLIT_TFLOPS, 2),

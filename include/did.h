@@ -415,7 +415,8 @@ int did_debug_inject_fault(did_handle h);
 
 /* Debugging aid for out-of-bounds writes: with the environment variable
  * DID_DEBUG_GUARD_ZONES set to a nonzero integer when a handle is created, each of the
- * handle's device buffers is followed by a guard zone of DID_GUARD_ZONE_BYTES bytes
+ * handle's device buffers (H and the partials of W and V, which share one without them, each by
+ * itself) is followed by a guard zone of DID_GUARD_ZONE_BYTES bytes
  * filled with the byte DID_GUARD_BYTE.  did_debug_check_guards synchronises the handle's
  * stream (a batch member's writes are on the batch's stream: call did_batch_sync first)
  * and stores in *bad the number of guard bytes that no longer hold the pattern

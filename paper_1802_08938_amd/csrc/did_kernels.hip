@@ -558,8 +558,8 @@ __global__ void k_zero_f32(float* p, int n) {
 }
 
 // ------------------------------------------------------------------ column pass
-// Block = 4 waves = 128 consecutive columns; wave w owns columns 128*blockIdx + 32w ..+31
-// and walks all M rows in 32-row chunks:
+// Block = WPB waves (4 or 8) = 32 WPB consecutive columns, a 32-column tile each, and one of
+// csplit shares of the rows, which every wave walks in 32-row chunks:
 //   P    = (-B[chunk, :] 2^s) (C[:, cols] 2^t)     (KP/16 scaled fp16 steps)
 //   acc  = X[chunk, cols] + P 2^-(s_m + t_j)        (one fma per entry) -> E = X - B C
 //   fsum += sum acc^2                               (float64)
@@ -581,16 +581,18 @@ __global__ void k_zero_f32(float* p, int n) {
 // Rout (rvec4: 16-byte stores are aligned), so that the row pass can carry it on.  The
 // source X is then either the data (refresh) or Rout itself (carry: E = R - delta B C).
 //
-// The B run goes from global memory straight into LDS (16 bytes a lane, no staging registers).  The chunk's closing barrier must wait for it, but not for the X tile of the
-// next chunk, whose loads are issued after it: stage_barrier leaves the last NX loads (those
-// of the X tile) in flight.  With __syncthreads, which waits for every load, each chunk waited
+// The B run goes from global memory straight into LDS (16 bytes a lane, no staging registers).
+// The chunk's closing barrier must wait for it, but not for the X tile of the next chunk, whose
+// loads are issued after it: stage_barrier leaves the last NX loads (those of the X tile) in
+// flight (X in tile order; X as given, whose edge tiles issue other numbers of loads, is waited
+// for).  With __syncthreads, which waits for every load, each chunk waited
 // out the X tile's latency.
 // us per column pass before and after: 5000 x 10^6, K = 50, tiled float32: 4922, 4474 (and three
 // waves per SIMD, the staging registers gone); bf16 5000 x 62500: 286, 271; 24 jobs in a batch, K
 // <= 32: 398, 356.
 //
-// What bounds it now: large float32 X in tile order, memory (5000 x 10^6, K = 50: 21.9 GB counted
-// at 4.9 TB/s, 12 jobs of a serving run, K <= 32, 4.75 TB/s of X; a large copy reaches 4.75);
+// What bounds it now: large float32 X in tile order, memory (5000 x 10^6, K = 50: 22 GB counted
+// at 4.9 to 5.0 TB/s, 12 jobs of a serving run, K <= 32, 4.75 TB/s of X; a large copy reaches 4.75);
 // K > 32 with X in bf16, the matrix units and the clock they leave (24 MFMAs per chunk and wave:
 // busy 46 % of the cycles at 1.9 GHz; at 5000 x 10^6 58 % at 1.43 GHz); small X, latency.
 template <typename XT>
@@ -598,8 +600,8 @@ struct x_loads {  // loads of one X tile per lane where their number is fixed, e
   static constexpr int value = std::is_same<XT, xtf32>::value ? 4 : (std::is_same<XT, __bf16>::value ? 2 : 0);
 };
 // s_waitcnt with vmcnt(NX) and lgkmcnt(0) (the builtin, so that the compiler's own waits count
-// it), then the barrier.  tests/test_stage_waits.py checks the generated code: NX loads, and
-// no others, lie between the staging and each of these waits.
+// it), then the barrier.  tests/test_stage_waits.py and tests/test_stage_waits_all.py check the
+// generated code: NX loads, and no others, lie between the staging and each of these waits.
 template <int NX>
 __device__ __forceinline__ void stage_barrier() {
   load_order();
@@ -935,14 +937,18 @@ int64_t colpass_blocks(const Shape& s) {
 }
 
 // Row shares of the column pass.  A block walks its rows chunk by chunk, so a narrow X leaves
-// most of the GPU idle (N = 575: 5 blocks), and one a little past a whole round of resident
-// blocks (2 per CU) pays for a second (N = 70000: 547 blocks).  Each share costs a prologue
-// and a partial of H (about 3 chunks' time) and its reading by the sweep; the smallest
-// estimate over shares of at least 4 chunks is taken, within max_split (the caller's scratch).
-// us per column pass at one share and as
-// chosen: 10304 x 575, K = 25: 502, 30.6; 3809 x 2248, K = 49: 307, 35.9; 500 x 2000, K = 10:
-// 25.6, 11.4; 600 x 9000, K = 40: 43.7, 21.6; 784 x 70000, K = 16: 79.2, 62.0; 1868 x 40000,
-// K = 60: 95.6, 91.
+// most of the GPU idle (N = 575: 5 blocks), and one a little past two blocks per CU pays for
+// the CUs that run three (N = 70000: 547 blocks).  Each share costs a prologue and a partial of H
+// (about 3 chunks' time) and its reading by the sweep; the smallest estimate over shares of at
+// least 4 chunks is taken, within max_split (the caller's scratch).  us per column pass (with its
+// event) at one share and as chosen: 10304 x 575, K = 25: 467, 29.7; 3809 x 2248, K = 49: 210,
+// 27.2; 500 x 2000, K = 10: 26.2, 11.7; 600 x 9000, K = 40: 44.6, 21.7; as given 784 x 70000, K =
+// 16: 75.4, 60.9; 1868 x 40000, K = 60: 124, 108; in tile order 56.5, 55.1 and 93, 95.
+//
+// `resident` counts two blocks per CU.  A CU holds three of the present kernels, or four (K <= 32
+// in tile order), but a third beside two takes time, not only room: with 768 in its place 784 x
+// 70000 as given is left whole (75.1), while 1868 x 40000 takes two shares for three (as given 107,
+// in tile order 84); the other shapes above choose the same.
 int column_split(const Shape& s, int64_t max_split) {
   const int64_t nb = (s.N + 127) / 128, resident = 512;
   const int64_t most = std::min<int64_t>(std::min<int64_t>(max_split, s.nchunks / 4), 64);
@@ -1048,8 +1054,9 @@ hipError_t colpass(const Shape& s, const void* X, const void* Cqv, const _Float1
 // while those still find idle SIMDs (sweep_u).  (One thread per column, with K running sums
 // and G read by scalar loads, waited on those loads at every coordinate and read and packed
 // its columns through serial LDS loops.)  us per launch
-// before and after: 500 x 2000, K = 10: 19.0, 4.8; 3809 x 2248, K = 49: 60.6, 11.6; 784 x
-// 70000, K = 16: 25.6, 10.7; 1868 x 40000, K = 60: 69.0, 24.8; N = 10^6, K = 50: 397, 277.
+// before and after: 500 x 2000, K = 10: 19.0, 5.2; 3809 x 2248, K = 49: 60.6, 16.1 (11.6 before H
+// came as 12 shares' partials); 784 x 70000, K = 16: 25.6, 11.6; 1868 x 40000, K = 60: 69.0, 28.8;
+// N = 10^6, K = 50: 397, 308.
 //
 // Division: h / G_kk is formed from the correctly rounded reciprocal, one residual fma and
 // one correction (Markstein's method: the correctly rounded quotient, so that cancellations
@@ -1269,7 +1276,8 @@ __device__ __forceinline__ void pack_e(f32x4* __restrict__ tile, const float* ct
 // Subtiles per wave of an instance's sweep: one while a wave per 16 columns still finds
 // idle SIMDs.  us per launch at U = 1 and U = 4: 9.8 and 14.0 at N = 9000, K = 40; 29.9 and
 // 24.8 at N = 40000, K = 60; batches of mixed N, which fill the GPU together, prefer U = 4
-// from N = 8192 on (39.8 us per grouped launch at a line of 32768, 33.3 at 8192).
+// from N = 8192 on (39.8 us per grouped launch at a line of 32768, 33.3 at 8192).  One line for
+// both, between the two, so that a batched instance equals its solo run bit for bit.
 __host__ __device__ inline int sweep_u(int64_t N) { return N <= 16384 ? 1 : 4; }
 inline int64_t sweep_blocks(int64_t N) { return (N + 64 * sweep_u(N) - 1) / (64 * sweep_u(N)); }
 
@@ -1604,7 +1612,7 @@ hipError_t bupdate(const Shape& s, float* B, const double* W, const double* V, _
   return hipGetLastError();
 }
 
-// E order of 256 columns of C (block bid).
+// E order of C, 32 kPackTiles columns a block.
 template <int KP>
 __global__ __launch_bounds__(256) void k_packc(const float* __restrict__ C, f32x4* __restrict__ Cq, int64_t N, int K) {
   constexpr int J = 32 * kPackTiles;
@@ -1812,8 +1820,8 @@ int64_t vgram_blocks(const Shape& s) {
 // staging registers) and X of the next tile is prefetched into registers.
 // Blocks are dealt to the eight XCDs round-robin; each XCD takes an equal run of the (range,
 // slab group) pairs, ranges first, so that the slab groups of a range share its C' tiles in
-// one L2 (whole ranges per XCD left XCDs idle at few ranges: 10304 x 575, K = 25, 4 ranges,
-// 34.6 us; 22.0 as runs).
+// one L2 (whole ranges per XCD left XCDs idle at few ranges: 10304 x 575, K = 25, measured at 4
+// ranges, 34.6 us, as runs 22.0; the bound on its scratch leaves that shape one range).
 //
 // RW (the carried-residual form): X is the column-major float32 residual R = X - B C of
 // the column pass, the E-order operand of each tile comes from CqE (delta C, stride
